@@ -26,13 +26,13 @@
 #include <cstdint>
 
 #include "teuk_coef.h"
+#include "teuk_device.h"
 #include "teuk_internal.h"
 
 namespace teuk {
 
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kRow = kWave + 5;   // staged positions j0-3 .. j0+65
 
 // What a stage launch writes.
@@ -50,270 +50,6 @@ constexpr int kChartH = TEUK_CHART_HYPERBOLOIDAL;
 // The tortoise chart with fourth-order theta differences (a launch class of
 // its own; the ABI's chart field stays TEUK_CHART_TORTOISE).
 constexpr int kChartT4 = kChartTortoise4;
-
-// 1/x from the hardware estimate refined by one Newton step.
-__device__ __forceinline__ double rcp64(double x)
-{
-    const double r = __builtin_amdgcn_rcp(x);
-    const double e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
-
-// 1/sqrt(x), x > 0, to full FP64 precision: estimate plus two Newton steps.
-__device__ __forceinline__ double rsq64(double x)
-{
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = y * __builtin_fma(-h * y, y, 1.5);
-    y = y * __builtin_fma(-h * y, y, 1.5);
-    return y;
-}
-
-// Six times the WENO5 flux f^+_{j+1/2} from v0..v4 = f_{j-2..j+2} (Sec. 3.1.2).
-// The f^- flux f^-_{j+1/2} is the same function of the mirrored stencil
-// (f_{j+3}, f_{j+2}, f_{j+1}, f_j, f_{j-1}).
-//
-// Arithmetic, rearranged by exact identities (only rounding differs from the
-// printed formulas):
-//  * with the second differences d_k and first differences e_k of IS_k,
-//    4 IS_k = (13/3) d_k^2 + e_k^2; eps is scaled by 4 as well, so every
-//    t_k = (eps + IS_k)^2 carries the same factor 16, which cancels in omega;
-//  * omega_k = alpha_k / sum alpha with alpha_k = d_k / t_k is taken over the
-//    common denominator, constants scaled by 10:
-//        omega_0 = t1 t2 / D,  omega_1 = 6 t0 t2 / D,  D = t1 t2 + 6 t0 t2 + 3 t0 t1,
-//    one reciprocal instead of four divisions;
-//  * omega_2 = 1 - omega_0 - omega_1, i.e. the flux is
-//        6 f = q2 + omega_0 (q0 - q2) + omega_1 (q1 - q2),
-//    so the weights sum to one exactly in the combination;
-//  * the candidates (times 6) reuse the differences:
-//        q2 = 3 (v2 + v3) - d2,  q1 - q2 = d2 - d1,  q0 = 2 d0 + 9 v2 - 3 v1.
-template <int WP>
-struct Weno;
-
-// Candidate part shared by every weight precision: 6 f from omega_0, omega_1.
-struct Candidates {
-    double q2, dq0, dq1;
-    __device__ __forceinline__ Candidates(double v0, double v1, double v2, double v3, double d0, double d1,
-                                          double d2)
-    {
-        (void)v0;
-        q2 = 3.0 * (v2 + v3) - d2;
-        dq1 = d2 - d1;
-        dq0 = (2.0 * d0 + (9.0 * v2 - 3.0 * v1)) - q2;
-    }
-};
-
-template <>
-struct Weno<TEUK_W_FP64> {
-    __device__ __forceinline__ static double flux6(double v0, double v1, double v2, double v3, double v4,
-                                                    double eps)
-    {
-        const double d0 = v0 - 2.0 * v1 + v2;
-        const double d1 = v1 - 2.0 * v2 + v3;
-        const double d2 = v2 - 2.0 * v3 + v4;
-        const double e0 = v0 - 4.0 * v1 + 3.0 * v2;
-        const double e1 = v1 - v3;
-        const double e2 = 3.0 * v2 - 4.0 * v3 + v4;
-        constexpr double c = 13.0 / 3.0;
-        const double eps4 = 4.0 * eps;
-        double t0 = __builtin_fma(c * d0, d0, __builtin_fma(e0, e0, eps4));
-        double t1 = __builtin_fma(c * d1, d1, __builtin_fma(e1, e1, eps4));
-        double t2 = __builtin_fma(c * d2, d2, __builtin_fma(e2, e2, eps4));
-        t0 *= t0;
-        t1 *= t1;
-        t2 *= t2;
-        const double p12 = t1 * t2, p02 = t0 * t2, p01 = t0 * t1;
-        const double inv = rcp64(p12 + (6.0 * p02 + 3.0 * p01));
-        const Candidates q(v0, v1, v2, v3, d0, d1, d2);
-        return q.q2 + inv * (p12 * q.dq0 + (6.0 * p02) * q.dq1);
-    }
-};
-
-// ---------------------------------------------------------------- reduced-precision weights
-// Sec. 3.1.3: the smoothness indicators and nonlinear weights are computed in a
-// lower precision and the weights are made to sum to one in FP64.  Here the six
-// stencil differences of IS_k are taken in FP64 (differencing first keeps the
-// information the low format would lose to cancellation), converted, and
-// IS_k, alpha_k and omega_0, omega_1 are formed in the low format; omega_2 is
-// the FP64 complement and the candidate fluxes stay FP64.
-//
-// The 16-bit weights use the ratio form
-//     alpha'_k = d_k (tau_min / tau_k)^2,   tau_k = eps + IS_k,
-// which equals alpha_k tau_min^2 (so omega is unchanged in exact arithmetic)
-// and keeps every intermediate in [0, 1] whatever the magnitude of the data.
-// rho_k = 1 where tau_k equals tau_min (also when both are zero).  FP32 has
-// the range for the FP64 form and takes it (Weno<TEUK_W_FP32> below).
-
-// Arithmetic in the low format: every result rounded to it.  ratio(a, b) is
-// a / b for 0 <= a < b, a true division: after the power-of-two scaling eps
-// can underflow to zero, so a flat stencil gives tau_min = 0 next to a tau_k
-// below 2^-16 whose reciprocal overflows, and 0 * inf would poison the weights.
-struct LowF16 {
-    typedef _Float16 T;
-    __device__ static T cvt(float x) { return (_Float16)x; }
-    __device__ static T rcp(T x) { return (_Float16)1.0 / x; }
-    __device__ static T ratio(T a, T b) { return a / b; }
-    __device__ static float f(T x) { return (float)x; }
-};
-// BF16 arithmetic: compute in FP32 and round each result to BF16 (round to
-// nearest even).  FP32 carries more than 2p+2 bits for p = 8, so this equals a
-// correctly rounded BF16 operation for +, -, * and /.
-struct Bf16Val {
-    float v;
-};
-__device__ __forceinline__ float bf16_round(float x)
-{
-    return (float)(__bf16)x;
-}
-__device__ __forceinline__ Bf16Val operator+(Bf16Val a, Bf16Val b) { return {bf16_round(a.v + b.v)}; }
-__device__ __forceinline__ Bf16Val operator*(Bf16Val a, Bf16Val b) { return {bf16_round(a.v * b.v)}; }
-__device__ __forceinline__ bool operator<(Bf16Val a, Bf16Val b) { return a.v < b.v; }
-__device__ __forceinline__ bool operator==(Bf16Val a, Bf16Val b) { return a.v == b.v; }
-struct LowBF16 {
-    typedef Bf16Val T;
-    __device__ static T cvt(float x) { return {bf16_round(x)}; }
-    __device__ static T rcp(T x) { return {bf16_round(1.0f / x.v)}; }
-    __device__ static T ratio(T a, T b) { return {bf16_round(a.v / b.v)}; }
-    __device__ static float f(T x) { return x.v; }
-};
-
-template <class L, bool kScale>
-__device__ __forceinline__ void low_weights(double d0, double d1, double d2, double e0, double e1, double e2,
-                                            double eps, double* w0, double* w1)
-{
-    typedef typename L::T T;
-    float fd0 = (float)d0, fd1 = (float)d1, fd2 = (float)d2;
-    float fe0 = (float)e0, fe1 = (float)e1, fe2 = (float)e2;
-    float feps = (float)eps;
-    if (kScale) {
-        // Scale by an exact power of two so that the largest of the differences
-        // and sqrt(eps) is O(1): IS' = sigma^2 IS and eps' = sigma^2 eps leave the
-        // weights unchanged and keep a 16-bit format away from overflow.
-        float m = fmaxf(fmaxf(fmaxf(fabsf(fd0), fabsf(fd1)), fmaxf(fabsf(fd2), fabsf(fe0))),
-                        fmaxf(fmaxf(fabsf(fe1), fabsf(fe2)), sqrtf(feps)));
-        const int ex = __builtin_amdgcn_frexp_expf(m);
-        fd0 = ldexpf(fd0, -ex); fd1 = ldexpf(fd1, -ex); fd2 = ldexpf(fd2, -ex);
-        fe0 = ldexpf(fe0, -ex); fe1 = ldexpf(fe1, -ex); fe2 = ldexpf(fe2, -ex);
-        feps = ldexpf(feps, -2 * ex);
-    }
-    const T c1312 = L::cvt(13.0f / 12.0f), c14 = L::cvt(0.25f);
-    const T D0 = L::cvt(fd0), D1 = L::cvt(fd1), D2 = L::cvt(fd2);
-    const T E0 = L::cvt(fe0), E1 = L::cvt(fe1), E2 = L::cvt(fe2);
-    const T ep = L::cvt(feps);
-    const T t0 = ep + (c1312 * (D0 * D0) + c14 * (E0 * E0));
-    const T t1 = ep + (c1312 * (D1 * D1) + c14 * (E1 * E1));
-    const T t2 = ep + (c1312 * (D2 * D2) + c14 * (E2 * E2));
-    T tm = t0 < t1 ? t0 : t1;
-    tm = t2 < tm ? t2 : tm;
-    const T one = L::cvt(1.0f);
-    const T r0 = t0 == tm ? one : L::ratio(tm, t0);
-    const T r1 = t1 == tm ? one : L::ratio(tm, t1);
-    const T r2 = t2 == tm ? one : L::ratio(tm, t2);
-    const T a0 = L::cvt(0.1f) * (r0 * r0);
-    const T a1 = L::cvt(0.6f) * (r1 * r1);
-    const T a2 = L::cvt(0.3f) * (r2 * r2);
-    const T inv = L::rcp(a0 + a1 + a2);
-    *w0 = (double)L::f(a0 * inv);
-    *w1 = (double)L::f(a1 * inv);
-}
-
-template <class L, bool kScale>
-struct WenoLow {
-    __device__ __forceinline__ static double flux6(double v0, double v1, double v2, double v3, double v4,
-                                                    double eps)
-    {
-        const double d0 = v0 - 2.0 * v1 + v2;
-        const double d1 = v1 - 2.0 * v2 + v3;
-        const double d2 = v2 - 2.0 * v3 + v4;
-        const double e0 = v0 - 4.0 * v1 + 3.0 * v2;
-        const double e1 = v1 - v3;
-        const double e2 = 3.0 * v2 - 4.0 * v3 + v4;
-        double w0, w1;
-        low_weights<L, kScale>(d0, d1, d2, e0, e1, e2, eps, &w0, &w1);
-        const Candidates q(v0, v1, v2, v3, d0, d1, d2);
-        return q.q2 + (w0 * q.dq0 + w1 * q.dq1);
-    }
-};
-
-// FP32 weights take the FP64 form above -- common denominator, one
-// reciprocal (v_rcp_f32, 1 ulp) -- evaluated in FP32 from the six FP64
-// stencil differences, with omega_2 the FP64 complement.  FP32 has the range
-// for it over most of the data: with t_k = (4 eps + 4 IS_k)^2 the denominator
-// is at least 2560 eps^4 and stays finite for differences up to about 1e4.  It
-// must also stay well above the subnormals, where the reciprocal overflows to
-// inf (and 0 * inf is a NaN) or loses its precision: below 2^-100 -- every
-// flat stencil once eps is under about 4e-9 -- and above 3e38 the lane takes
-// the FP64 weights instead.  From 2^-100 on, a product that is subnormal or
-// flushed to zero moves its weight by at most 2^-26 absolute.
-template <>
-struct Weno<TEUK_W_FP32> {
-    __device__ __forceinline__ static double flux6(double v0, double v1, double v2, double v3, double v4,
-                                                    double eps)
-    {
-        const double d0 = v0 - 2.0 * v1 + v2;
-        const double d1 = v1 - 2.0 * v2 + v3;
-        const double d2 = v2 - 2.0 * v3 + v4;
-        const double e0 = v0 - 4.0 * v1 + 3.0 * v2;
-        const double e1 = v1 - v3;
-        const double e2 = 3.0 * v2 - 4.0 * v3 + v4;
-        const float D0 = (float)d0, D1 = (float)d1, D2 = (float)d2;
-        const float E0 = (float)e0, E1 = (float)e1, E2 = (float)e2;
-        constexpr float c = 13.0f / 3.0f;
-        const float eps4 = (float)(4.0 * eps);
-        float t0 = __builtin_fmaf(c * D0, D0, __builtin_fmaf(E0, E0, eps4));
-        float t1 = __builtin_fmaf(c * D1, D1, __builtin_fmaf(E1, E1, eps4));
-        float t2 = __builtin_fmaf(c * D2, D2, __builtin_fmaf(E2, E2, eps4));
-        t0 *= t0;
-        t1 *= t1;
-        t2 *= t2;
-        const float p12 = t1 * t2, p02 = t0 * t2, p01 = t0 * t1;
-        const float den = p12 + (6.0f * p02 + 3.0f * p01);
-        const Candidates q(v0, v1, v2, v3, d0, d1, d2);
-        if (!(den >= 0x1p-100f && den <= 3.0e38f)) return Weno<TEUK_W_FP64>::flux6(v0, v1, v2, v3, v4, eps);
-        const float inv = __builtin_amdgcn_rcpf(den);
-        const double w0 = (double)(p12 * inv), w1 = (double)((6.0f * p02) * inv);
-        return q.q2 + (w0 * q.dq0 + w1 * q.dq1);
-    }
-};
-template <>
-struct Weno<TEUK_W_FP16> : WenoLow<LowF16, true> {};
-template <>
-struct Weno<TEUK_W_BF16> : WenoLow<LowBF16, true> {};
-
-// x of lane l + 1 (lane 63 keeps its own), by a DPP wavefront shift: no LDS
-// round trip, unlike __shfl_down.  Used wherever a lane takes the interface
-// flux of the lane after it.
-__device__ __forceinline__ double next_lane(double x)
-{
-    int lo = __double2loint(x), hi = __double2hiint(x);
-    lo = __builtin_amdgcn_update_dpp(lo, lo, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(hi, hi, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
-
-// Barrier that orders LDS only.  __syncthreads() is also a workgroup fence on
-// global memory, which makes every wave drain its outstanding global loads
-// (s_waitcnt vmcnt(0)) before the barrier: that would serialise the row
-// prefetch below with the arithmetic it is meant to overlap.
-__device__ __forceinline__ void lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Load a double at a byte offset from a uniform base: the 32-bit offset lets
-// the compiler use the scalar-base addressing form (no 64-bit address math).
-__device__ __forceinline__ double ldb(const double* base, unsigned off)
-{
-    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + off);
-}
-__device__ __forceinline__ void stb(double* base, unsigned off, double v)
-{
-    *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) = v;
-}
 
 // ---------------------------------------------------------------- chart-T row pipeline
 // The tortoise-chart stage streams each theta row of the four planes straight
@@ -408,6 +144,25 @@ __device__ __forceinline__ double ld_async_c(unsigned voff, const double* sbase)
     }
 }
 
+// The results of one point: what the launch's mode writes, from F(u^(k)), the
+// point's own values and (stages 2, 3 and the dual stage) those of u^n.
+template <int kMode, bool kCoh = false>
+__device__ __forceinline__ void write_point(const StageArgs& A, size_t row, unsigned oc, const Four& F, double phR,
+                                            double phI, double piR, double piI, double n0, double n1, double n2,
+                                            double n3)
+{
+    const double own[4] = {phR, phI, piR, piI}, un[4] = {n0, n1, n2, n3};
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        double* out = A.out + p * A.plane + row;
+        const double v = euler(own[p], A.dt, F.v[p]);
+        if (kMode == kRhsOnly) stb_c<kCoh>(out, oc, F.v[p]);
+        else if (kMode == kStageFirst) stb_c<kCoh>(out, oc, v);
+        else stb_c<kCoh>(out, oc, combine(A.ca, un[p], A.cb, v));
+        if (kMode == kStageDual) stb_c<kCoh>(A.out2 + p * A.plane + row, oc, combine(A.ca2, un[p], A.cb2, v));
+    }
+}
+
 // Hyperboloidal chart: one radial strip [j0, j0 + 63) marched over the theta
 // rows [k0, k1), upward (dir = +1, from k0) or downward (dir = -1, from
 // k1 - 1).  Rows are staged in a two-row LDS ring: while row k is computed
@@ -436,7 +191,8 @@ __device__ __forceinline__ void march_strip_h(const StageArgs& A, double (*s)[4]
     const bool halo = l < 5;
     const double* __restrict__ ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
     const double* unp[4] = {A.un, A.un + P, A.un + 2 * P, A.un + 3 * P};   // read where reads_un<kMode>()
-    double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
+
+    const WenoK K = weno_consts(A.eps);
 
     const int n = k1 - k0;
     const int first = dir > 0 ? k0 : k1 - 1;
@@ -491,7 +247,7 @@ __device__ __forceinline__ void march_strip_h(const StageArgs& A, double (*s)[4]
         // next rows' traffic, consumed at the end of this iteration
         const bool pre = i + 2 < nst;
         if (pre) load_row(k + 2 * dir);
-        double n0, n1, n2, n3;
+        double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0;
         if (reads_un<kMode>()) {
             n0 = ldb(unp[0] + row, oc);
             n1 = ldb(unp[1] + row, oc);
@@ -508,15 +264,15 @@ __device__ __forceinline__ void march_strip_h(const StageArgs& A, double (*s)[4]
             // upwind side per lane and row: speed >= 0 -> f^+, speed < 0 -> f^-
             const bool up1 = hc[kHLam1] >= 0.0, up2 = hc[kHLam2] >= 0.0;
             auto deriv = [&](int p, bool up, bool any_up, bool any_dn) {
-                double fp = 0.0, fm = 0.0, d = 0.0;
+                double d = 0.0;
                 if (any_up) {
-                    fp = Weno<WP>::flux6(s[b][p][l], s[b][p][l + 1], s[b][p][l + 2], s[b][p][l + 3], s[b][p][l + 4], A.eps);
-                    const double dp = next_lane(fp) - fp;
+                    const Flux f = Weno<WP>::flux(s[b][p][l], s[b][p][l + 1], s[b][p][l + 2], s[b][p][l + 3], s[b][p][l + 4], K);
+                    const double dp = plus_diff<WP>(K, f, next_lane(f.y));
                     if (up) d = dp;
                 }
                 if (any_dn) {
-                    fm = Weno<WP>::flux6(s[b][p][l + 5], s[b][p][l + 4], s[b][p][l + 3], s[b][p][l + 2], s[b][p][l + 1], A.eps);
-                    const double dm = next_lane(fm) - fm;
+                    const Flux f = Weno<WP>::flux(s[b][p][l + 5], s[b][p][l + 4], s[b][p][l + 3], s[b][p][l + 2], s[b][p][l + 1], K);
+                    const double dm = minus_diff<WP>(K, f, next_lane(f.y));
                     if (!up) d = dm;
                 }
                 return d * A.inv6dx;
@@ -540,53 +296,12 @@ __device__ __forceinline__ void march_strip_h(const StageArgs& A, double (*s)[4]
         }
 
         if (active) {
-            const double lam1 = hc[kHLam1], lam2n = -hc[kHLam2], m3r = hc[kHM3r], m3i = hc[kHM3i];
-            const double btr = hc[kHBtr], bti = hc[kHBti], cr = hc[kHCr], ci = hc[kHCi];
-            const double ath = hc[kHAth], bth = hc[kHBth];
-
             // rows k+1 and k-1
             const double upR = dir > 0 ? ahR : bhR, upI = dir > 0 ? ahI : bhI;
             const double dnR = dir > 0 ? bhR : ahR, dnI = dir > 0 ? bhI : ahI;
-            const double d1R = (upR - dnR) * A.ih1, d1I = (upI - dnI) * A.ih1;
-            const double d2R = (upR - 2.0 * phR + dnR) * A.ih2;
-            const double d2I = (upI - 2.0 * phI + dnI) * A.ih2;
+            const Four F = rhs_h(hc, A.ih1, A.ih2, dPhR, dPhI, dPiR, dPiI, phR, phI, piR, piI, upR, upI, dnR, dnI);
 
-            // d_t Phi = pi - lam1 d_x Phi
-            const double FphR = piR - lam1 * dPhR;
-            const double FphI = piI - lam1 * dPhI;
-            // d_t pi = -lam2 d_x pi - m3 d_x Phi + B~t pi + A~thth Phi_thth + B~th Phi_th + C~ Phi
-            const double FpiR = lam2n * dPiR - (m3r * dPhR - m3i * dPhI) + (btr * piR - bti * piI) +
-                                ath * d2R + bth * d1R + (cr * phR - ci * phI);
-            const double FpiI = lam2n * dPiI - (m3r * dPhI + m3i * dPhR) + (btr * piI + bti * piR) +
-                                ath * d2I + bth * d1I + (cr * phI + ci * phR);
-
-            if (kMode == kRhsOnly) {
-                stb(outp[0] + row, oc, FphR);
-                stb(outp[1] + row, oc, FphI);
-                stb(outp[2] + row, oc, FpiR);
-                stb(outp[3] + row, oc, FpiI);
-            } else if (kMode == kStageFirst) {
-                stb(outp[0] + row, oc, phR + A.dt * FphR);
-                stb(outp[1] + row, oc, phI + A.dt * FphI);
-                stb(outp[2] + row, oc, piR + A.dt * FpiR);
-                stb(outp[3] + row, oc, piI + A.dt * FpiI);
-            } else if (kMode == kStageLater) {
-                stb(outp[0] + row, oc, A.ca * n0 + A.cb * (phR + A.dt * FphR));
-                stb(outp[1] + row, oc, A.ca * n1 + A.cb * (phI + A.dt * FphI));
-                stb(outp[2] + row, oc, A.ca * n2 + A.cb * (piR + A.dt * FpiR));
-                stb(outp[3] + row, oc, A.ca * n3 + A.cb * (piI + A.dt * FpiI));
-            } else {
-                const double v0 = phR + A.dt * FphR, v1 = phI + A.dt * FphI;
-                const double v2 = piR + A.dt * FpiR, v3 = piI + A.dt * FpiI;
-                stb(outp[0] + row, oc, A.ca * n0 + A.cb * v0);
-                stb(outp[1] + row, oc, A.ca * n1 + A.cb * v1);
-                stb(outp[2] + row, oc, A.ca * n2 + A.cb * v2);
-                stb(outp[3] + row, oc, A.ca * n3 + A.cb * v3);
-                stb(A.out2 + row, oc, A.ca2 * n0 + A.cb2 * v0);
-                stb(A.out2 + P + row, oc, A.ca2 * n1 + A.cb2 * v1);
-                stb(A.out2 + 2 * P + row, oc, A.ca2 * n2 + A.cb2 * v2);
-                stb(A.out2 + 3 * P + row, oc, A.ca2 * n3 + A.cb2 * v3);
-            }
+            write_point<kMode>(A, row, oc, F, phR, phI, piR, piI, n0, n1, n2, n3);
         }
         bhR = phR;
         bhI = phI;
@@ -634,13 +349,9 @@ __device__ __forceinline__ void march_strip_t(const StageArgs& A, char* ring, in
     const unsigned lds0 = (unsigned)(size_t)ring;          // LDS byte address of the ring
     const double* ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
     const double* unp[4] = {A.un, A.un + P, A.un + 2 * P, A.un + 3 * P};
-    double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
 
-    double rt[kNRT];
-#pragma unroll
-    for (int i = 0; i < kNRT; ++i) rt[i] = ldb(A.rtab + (size_t)i * nr, oc);
-    const __attribute__((address_space(4))) double* tt =
-        (const __attribute__((address_space(4))) double*)A.ttab;
+    const Radial rt = load_radial(A, oc);
+    const WenoK K = weno_consts(A.eps);
 
     const int n = k1 - k0;
     const int first = dir > 0 ? k0 : k1 - 1;
@@ -704,10 +415,7 @@ __device__ __forceinline__ void march_strip_t(const StageArgs& A, char* ring, in
         }
         const int k = first + dir * i;
         const size_t row = (size_t)k * nr;
-        const double sn2 = tt[kSn2 * nth + k];
-        const double cs = tt[kCs * nth + k];
-        const double cot = tt[kCot * nth + k];
-        const double th = tt[kTh * nth + k];
+        const Polar pol = load_polar(A, k);
         double n0 = 0.0, n1 = 0.0, n2 = 0.0, n3 = 0.0;
         if (reads_un<kMode>()) {
             n0 = ld_async_c<kCoh>(oc, unp[0] + row);
@@ -721,7 +429,7 @@ __device__ __forceinline__ void march_strip_t(const StageArgs& A, char* ring, in
         // sinking it to its use); the batched launch, whose tiles start as
         // slots free up, measured 0.7 % slower on C4 with that, and leaves the
         // placement to the compiler.
-        const double vsig = rsq64(sigma2(rt, sn2));
+        const double vsig = point_vsig(rt, pol.sn2);
         if constexpr (kLevel) asm volatile("" : : "v"(vsig));
         issue_row(i + 3);
         constexpr int it = reads_un<kMode>() ? 16 : 12;
@@ -730,10 +438,10 @@ __device__ __forceinline__ void march_strip_t(const StageArgs& A, char* ring, in
         else vm_wait<2 * it>();
         const int b = i & (kRing - 1), bn = (i + 1) & (kRing - 1);
 
-        const double fR = Weno<WP>::flux6(sr[b][0][l], sr[b][0][l + 1], sr[b][0][l + 2], sr[b][0][l + 3], sr[b][0][l + 4], A.eps);
-        const double fI = Weno<WP>::flux6(sr[b][1][l], sr[b][1][l + 1], sr[b][1][l + 2], sr[b][1][l + 3], sr[b][1][l + 4], A.eps);
-        const double gR = Weno<WP>::flux6(sr[b][2][l + 5], sr[b][2][l + 4], sr[b][2][l + 3], sr[b][2][l + 2], sr[b][2][l + 1], A.eps);
-        const double gI = Weno<WP>::flux6(sr[b][3][l + 5], sr[b][3][l + 4], sr[b][3][l + 3], sr[b][3][l + 2], sr[b][3][l + 1], A.eps);
+        const Flux fR = Weno<WP>::flux(sr[b][0][l], sr[b][0][l + 1], sr[b][0][l + 2], sr[b][0][l + 3], sr[b][0][l + 4], K);
+        const Flux fI = Weno<WP>::flux(sr[b][1][l], sr[b][1][l + 1], sr[b][1][l + 2], sr[b][1][l + 3], sr[b][1][l + 4], K);
+        const Flux gR = Weno<WP>::flux(sr[b][2][l + 5], sr[b][2][l + 4], sr[b][2][l + 3], sr[b][2][l + 2], sr[b][2][l + 1], K);
+        const Flux gI = Weno<WP>::flux(sr[b][3][l + 5], sr[b][3][l + 4], sr[b][3][l + 3], sr[b][3][l + 2], sr[b][3][l + 1], K);
         const double phR = sr[b][0][l + 3], phI = sr[b][1][l + 3];
         const double piR = sr[b][2][l + 3], piI = sr[b][3][l + 3];
         double ahR, ahI;   // Phi on the row ahead (k + dir)
@@ -761,68 +469,27 @@ __device__ __forceinline__ void march_strip_t(const StageArgs& A, char* ring, in
         // the interface flux of the next lane: by DPP in the single-solve
         // launch; the batched launch measured 1.2 % slower on C4 with the DPP
         // moves (VALU work) than with ds_bpermute (LDS work)
-        const double fR1 = kLevel ? next_lane(fR) : __shfl_down(fR, 1);
-        const double fI1 = kLevel ? next_lane(fI) : __shfl_down(fI, 1);
-        const double gR1 = kLevel ? next_lane(gR) : __shfl_down(gR, 1);
-        const double gI1 = kLevel ? next_lane(gI) : __shfl_down(gI, 1);
+        const double fR1 = kLevel ? next_lane(fR.y) : __shfl_down(fR.y, 1);
+        const double fI1 = kLevel ? next_lane(fI.y) : __shfl_down(fI.y, 1);
+        const double gR1 = kLevel ? next_lane(gR.y) : __shfl_down(gR.y, 1);
+        const double gI1 = kLevel ? next_lane(gI.y) : __shfl_down(gI.y, 1);
 
         if (reads_un<kMode>()) vm_wait<12>(n0, n1, n2, n3);
         if (active) {
-            const double dPhR = (fR1 - fR) * A.inv6dx;
-            const double dPhI = (fI1 - fI) * A.inv6dx;
-            const double dPiR = (gR1 - gR) * A.inv6dx;
-            const double dPiI = (gI1 - gI) * A.inv6dx;
-            const PointCoef c = point_coef(rt, sn2, cs, cot, th, vsig);
+            const PointCoef c = point_coef_t(rt, pol, vsig);
             const double upR = dir > 0 ? ahR : bhR, upI = dir > 0 ? ahI : bhI;
             const double dnR = dir > 0 ? bhR : ahR, dnI = dir > 0 ? bhI : ahI;
-            double d1R, d1I, d2R, d2I;
+            Theta xR, xI;
             if constexpr (kTh4) {
-                // ih1 = 1/(12 dtheta), ih2 = 1/(12 dtheta^2)
-                const double up2R = dir > 0 ? ah2R : bh2R, up2I = dir > 0 ? ah2I : bh2I;
-                const double dn2R = dir > 0 ? bh2R : ah2R, dn2I = dir > 0 ? bh2I : ah2I;
-                d1R = (8.0 * (upR - dnR) - (up2R - dn2R)) * A.ih1;
-                d1I = (8.0 * (upI - dnI) - (up2I - dn2I)) * A.ih1;
-                d2R = (16.0 * (upR + dnR) - 30.0 * phR - (up2R + dn2R)) * A.ih2;
-                d2I = (16.0 * (upI + dnI) - 30.0 * phI - (up2I + dn2I)) * A.ih2;
+                xR = theta4(phR, upR, dnR, dir > 0 ? ah2R : bh2R, dir > 0 ? bh2R : ah2R);
+                xI = theta4(phI, upI, dnI, dir > 0 ? ah2I : bh2I, dir > 0 ? bh2I : ah2I);
             } else {
-                d1R = (upR - dnR) * A.ih1;
-                d1I = (upI - dnI) * A.ih1;
-                d2R = (upR - 2.0 * phR + dnR) * A.ih2;
-                d2I = (upI - 2.0 * phI + dnI) * A.ih2;
+                xR = theta2(phR, upR, dnR);
+                xI = theta2(phI, upI, dnI);
             }
-            const double FphR = piR - c.b * dPhR;
-            const double FphI = piI - c.b * dPhI;
-            const double FpiR = c.b * dPiR - (c.m3r * dPhR - c.m3i * dPhI) + (c.btr * piR - c.bti * piI) +
-                                c.ath * d2R + c.bth * d1R + (c.cr * phR - c.ci * phI);
-            const double FpiI = c.b * dPiI - (c.m3r * dPhI + c.m3i * dPhR) + (c.btr * piI + c.bti * piR) +
-                                c.ath * d2I + c.bth * d1I + (c.cr * phI + c.ci * phR);
-            if (kMode == kRhsOnly) {
-                stb_c<kCoh>(outp[0] + row, oc, FphR);
-                stb_c<kCoh>(outp[1] + row, oc, FphI);
-                stb_c<kCoh>(outp[2] + row, oc, FpiR);
-                stb_c<kCoh>(outp[3] + row, oc, FpiI);
-            } else if (kMode == kStageFirst) {
-                stb_c<kCoh>(outp[0] + row, oc, phR + A.dt * FphR);
-                stb_c<kCoh>(outp[1] + row, oc, phI + A.dt * FphI);
-                stb_c<kCoh>(outp[2] + row, oc, piR + A.dt * FpiR);
-                stb_c<kCoh>(outp[3] + row, oc, piI + A.dt * FpiI);
-            } else if (kMode == kStageLater) {
-                stb_c<kCoh>(outp[0] + row, oc, A.ca * n0 + A.cb * (phR + A.dt * FphR));
-                stb_c<kCoh>(outp[1] + row, oc, A.ca * n1 + A.cb * (phI + A.dt * FphI));
-                stb_c<kCoh>(outp[2] + row, oc, A.ca * n2 + A.cb * (piR + A.dt * FpiR));
-                stb_c<kCoh>(outp[3] + row, oc, A.ca * n3 + A.cb * (piI + A.dt * FpiI));
-            } else {
-                const double v0 = phR + A.dt * FphR, v1 = phI + A.dt * FphI;
-                const double v2 = piR + A.dt * FpiR, v3 = piI + A.dt * FpiI;
-                stb_c<kCoh>(outp[0] + row, oc, A.ca * n0 + A.cb * v0);
-                stb_c<kCoh>(outp[1] + row, oc, A.ca * n1 + A.cb * v1);
-                stb_c<kCoh>(outp[2] + row, oc, A.ca * n2 + A.cb * v2);
-                stb_c<kCoh>(outp[3] + row, oc, A.ca * n3 + A.cb * v3);
-                stb_c<kCoh>(A.out2 + row, oc, A.ca2 * n0 + A.cb2 * v0);
-                stb_c<kCoh>(A.out2 + P + row, oc, A.ca2 * n1 + A.cb2 * v1);
-                stb_c<kCoh>(A.out2 + 2 * P + row, oc, A.ca2 * n2 + A.cb2 * v2);
-                stb_c<kCoh>(A.out2 + 3 * P + row, oc, A.ca2 * n3 + A.cb2 * v3);
-            }
+            const Four F = rhs_t<bt_first<WP>()>(A, c, plus_diff<WP>(K, fR, fR1), plus_diff<WP>(K, fI, fI1), minus_diff<WP>(K, gR, gR1),
+                                 minus_diff<WP>(K, gI, gI1), phR, phI, piR, piI, xR, xI);
+            write_point<kMode, kCoh>(A, row, oc, F, phR, phI, piR, piI, n0, n1, n2, n3);
         }
         if constexpr (kTh4) {
             bh2R = bhR;
@@ -896,7 +563,7 @@ __global__ __launch_bounds__(kWave) void stage_kernel(StageArgs A)
 // hardware as slots free up), which measured faster than fewer workgroups
 // looping over tiles.  A tile runs exactly the single-solve code.
 template <int WP, int kMode, int kChart>
-__global__ __launch_bounds__(kWave) void group_stage_kernel(const StageArgs* __restrict__ args,
+__global__ __launch_bounds__(kWave, WP == TEUK_W_BF16 ? 3 : 4) void group_stage_kernel(const StageArgs* __restrict__ args,
                                                             const long long* __restrict__ start, int nmem,
                                                             long long tiles)
 {
@@ -986,7 +653,7 @@ __device__ __forceinline__ void pipe_wait(const PipeArgs& P, int strip, int seg,
 }
 
 template <int WP>
-__global__ __launch_bounds__(kWave) void pipe_kernel(PipeArgs P)
+__global__ __launch_bounds__(kWave, 4) void pipe_kernel(PipeArgs P)
 {
     __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
     const long long items = 3LL * P.nsteps * P.tiles;
@@ -1075,11 +742,8 @@ __global__ __launch_bounds__(kBThreads) void blocked_step_kernel(StageArgs A)
     const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
     const double* ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
     double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
-    double rt[kNRT];
-#pragma unroll
-    for (int i = 0; i < kNRT; ++i) rt[i] = ldb(A.rtab + (size_t)i * nr, oc);
-    const __attribute__((address_space(4))) double* tt =
-        (const __attribute__((address_space(4))) double*)A.ttab;
+    const Radial rt = load_radial(A, oc);
+    const WenoK K = weno_consts(A.eps);
 
     const int r1lo = max(k0 - 2, 0), r1hi = min(k1 + 2, nth);   // stage-1 rows
     const int r2lo = max(k0 - 1, 0), r2hi = min(k1 + 1, nth);   // stage-2 rows
@@ -1110,37 +774,18 @@ __global__ __launch_bounds__(kBThreads) void blocked_step_kernel(StageArgs A)
     struct Out { double v[4]; };
     auto stage = [&](const double (&w)[4][6], double dnR, double dnI, double upR, double upI, const PointCoef& c,
                      double ca, double cb, const double (&un)[4], bool first) {
-        const double fR = Weno<WP>::flux6(w[0][0], w[0][1], w[0][2], w[0][3], w[0][4], A.eps);
-        const double fI = Weno<WP>::flux6(w[1][0], w[1][1], w[1][2], w[1][3], w[1][4], A.eps);
-        const double gR = Weno<WP>::flux6(w[2][5], w[2][4], w[2][3], w[2][2], w[2][1], A.eps);
-        const double gI = Weno<WP>::flux6(w[3][5], w[3][4], w[3][3], w[3][2], w[3][1], A.eps);
-        const double fR1 = next_lane(fR), fI1 = next_lane(fI);
-        const double gR1 = next_lane(gR), gI1 = next_lane(gI);
-        const double phR = w[0][3], phI = w[1][3], piR = w[2][3], piI = w[3][3];
-        const double dPhR = (fR1 - fR) * A.inv6dx;
-        const double dPhI = (fI1 - fI) * A.inv6dx;
-        const double dPiR = (gR1 - gR) * A.inv6dx;
-        const double dPiI = (gI1 - gI) * A.inv6dx;
-        const double d1R = (upR - dnR) * A.ih1, d1I = (upI - dnI) * A.ih1;
-        const double d2R = (upR - 2.0 * phR + dnR) * A.ih2;
-        const double d2I = (upI - 2.0 * phI + dnI) * A.ih2;
-        const double FphR = piR - c.b * dPhR;
-        const double FphI = piI - c.b * dPhI;
-        const double FpiR = c.b * dPiR - (c.m3r * dPhR - c.m3i * dPhI) + (c.btr * piR - c.bti * piI) +
-                            c.ath * d2R + c.bth * d1R + (c.cr * phR - c.ci * phI);
-        const double FpiI = c.b * dPiI - (c.m3r * dPhI + c.m3i * dPhR) + (c.btr * piI + c.bti * piR) +
-                            c.ath * d2I + c.bth * d1I + (c.cr * phI + c.ci * phR);
+        const Flux fR = Weno<WP>::flux(w[0][0], w[0][1], w[0][2], w[0][3], w[0][4], K);
+        const Flux fI = Weno<WP>::flux(w[1][0], w[1][1], w[1][2], w[1][3], w[1][4], K);
+        const Flux gR = Weno<WP>::flux(w[2][5], w[2][4], w[2][3], w[2][2], w[2][1], K);
+        const Flux gI = Weno<WP>::flux(w[3][5], w[3][4], w[3][3], w[3][2], w[3][1], K);
+        const Four F = rhs_t<false>(A, c, plus_diff<WP>(K, fR, next_lane(fR.y)), plus_diff<WP>(K, fI, next_lane(fI.y)),
+                             minus_diff<WP>(K, gR, next_lane(gR.y)), minus_diff<WP>(K, gI, next_lane(gI.y)), w[0][3],
+                             w[1][3], w[2][3], w[3][3], theta2(w[0][3], upR, dnR), theta2(w[1][3], upI, dnI));
         Out o;
-        if (first) {
-            o.v[0] = phR + A.dt * FphR;
-            o.v[1] = phI + A.dt * FphI;
-            o.v[2] = piR + A.dt * FpiR;
-            o.v[3] = piI + A.dt * FpiI;
-        } else {
-            o.v[0] = ca * un[0] + cb * (phR + A.dt * FphR);
-            o.v[1] = ca * un[1] + cb * (phI + A.dt * FphI);
-            o.v[2] = ca * un[2] + cb * (piR + A.dt * FpiR);
-            o.v[3] = ca * un[3] + cb * (piI + A.dt * FpiI);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const double v = euler(w[p][3], A.dt, F.v[p]);
+            o.v[p] = first ? v : combine(ca, un[p], cb, v);
         }
         return o;
     };
@@ -1213,11 +858,10 @@ __global__ __launch_bounds__(kBThreads) void blocked_step_kernel(StageArgs A)
                 upI = A.parity * w[1][3];
             }
             const double none[4] = {0, 0, 0, 0};
-            const double sn2 = tt[kSn2 * nth + r], cs = tt[kCs * nth + r];
-            const double cot = tt[kCot * nth + r], th = tt[kTh * nth + r];
+            const Polar pol = load_polar(A, r);
             pc2 = pc1;
             pc1 = pc0;
-            pc0 = point_coef(rt, sn2, cs, cot, th, rsq64(sigma2(rt, sn2)));
+            pc0 = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
             const Out o = stage(w, nbR, nbI, upR, upI, pc0, 0.0, 1.0, none, true);
             if (!dup) {
 #pragma unroll
@@ -1449,6 +1093,11 @@ int stage_grid(int weight_prec, bool first, int chart)
     TEUK_OCC(TEUK_W_BF16, kChartT4)
 #undef TEUK_OCC
     if (e != hipSuccess || per_cu < 1) return 0;
+    // Whole waves per SIMD: a 17th workgroup (what the LDS of a compute unit
+    // holds where the registers allow it) gives one SIMD a fifth wave that the
+    // launch then waits for: FP32 weights on 4099 x 131, 49 us a step with 17
+    // per unit and 42 with 16.
+    if (per_cu > 4) per_cu &= ~3;
     return cus * per_cu;
 }
 
