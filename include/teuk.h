@@ -121,10 +121,14 @@ enum { TEUK_RK_SSP33 = 0, TEUK_RK_SSP104 = 1, TEUK_RK_SSP33_BLOCKED = 2, TEUK_RK
 /* TEUK_RK_SSP33_BLOCKED: SSP-RK(3,3), each step one launch that computes all
  * three stages of a tile (temporal blocking): u(1) and u(2) stay in LDS and
  * HBM sees one read of u^n and one write of u^{n+1} per point.  Tiles are 114
- * radial points by about nth / segs rows (one workgroup of two waves); a tile recomputes the stage-1
- * values two rows and six points beyond its outputs and the stage-2 values one
- * row and three points beyond (workgroups, when > 0, sets the tile count).
- * The result is the same arithmetic as TEUK_RK_SSP33, point by point.
+ * radial points by the rows of a workgroup's share (four waves, two marching up
+ * and two down from its middle row); a tile recomputes the stage-1 values two
+ * rows and six points beyond its outputs and the stage-2 values one row and
+ * three points beyond (workgroups, when > 0, sets the tile count).
+ * The result is the same arithmetic as TEUK_RK_SSP33, point by point (in one sum
+ * the two products are rounded in the other order).
+ * TEUK_RK_SSP33 takes the same launch where it is built, unless a budget of
+ * workgroups is asked for (see teuk_step); this integrator asks for it.
  * Tortoise chart, FP64 state, WENO5 with FP64 or FP32 weights.  In a group
  * such a solve is a cache block of its own, stepped by its own blocked
  * launches. */
@@ -275,6 +279,10 @@ teuk_status teuk_set_initial(teuk_solver* h, const double* u, int32_t on_device)
  * is three fused stage kernels
  *     u1 = u + dt F(u);  u2 = 3/4 u + 1/4 (u1 + dt F(u1));  u = 1/3 u + 2/3 (u2 + dt F(u2)),
  * SSP-RK(10,4) ten (see TEUK_RK_SSP104),
+ * or, for SSP-RK(3,3) with workgroups = 0 in the tortoise chart (FP64 state, WENO5,
+ * FP64 or FP32 weights, second-order theta differences), one temporally blocked
+ * launch a step with the same bits (unless teuk_tune measured the stage launches
+ * faster for this class),
  * with F(u) = -(M d_x u + L u + A u) of eq. evln and WENO5 radial derivatives
  * (Sec. 3.1.2).  A waveform sample is taken after every extract_every-th step.
  * Asynchronous on the solver's stream.  nsteps = 0 is a no-op.
@@ -361,7 +369,10 @@ teuk_status teuk_host_coefficients(const teuk_config* cfg, double* out, size_t c
  * smooth synthetic state of order one, and remembers the fastest budget for that launch class (device, chart
  * and theta order, weight and state precision, integrator, scheme, nr, ntheta) for the rest of
  * the process: a later teuk_create of that class with workgroups = 0 uses it
- * (teuk_info reports the workgroups in use).  The tiling does not change any
+ * (teuk_info reports the workgroups in use).  For a class that steps by the
+ * temporally blocked launch (see teuk_step) that launch is timed too; where it is
+ * the fastest, solvers go on stepping by it, us_per_step and us_per_step_default are
+ * its time, and the budget shapes the stage launch of TEUK_X_RHS.  The tiling does not change any
  * point's arithmetic, so results are bitwise independent of the choice.  The
  * scratch solver is allocated and freed inside the call; the stream is a
  * private one.  Errors: INVALID_ARG, UNSUPPORTED (double-double state), the

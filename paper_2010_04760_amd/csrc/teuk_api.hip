@@ -47,7 +47,8 @@ struct teuk_solver {
     int j_e = 0;
     int nstrips = 0;
     int segs[2] = {0, 0};                           // theta segments per strip: stage 1, stages 2-3
-    int bstrips = 0, bsegs = 0;                     // temporal blocking: tiles per launch = bstrips * bsegs
+    int bstrips = 0, bgrid = 0;                     // temporal blocking: radial strips, workgroups per launch
+    bool fused = false;                             // TEUK_RK_SSP33 stepped by the temporally blocked launch
     long long plane = 0;
     long long steps = 0, samples = 0;
     bool have_init = false;
@@ -268,6 +269,41 @@ int pick_segs(const teuk_config& c, int nstrips, int weight_prec, bool first)
     if (segs > 1) segs &= ~1LL;
     if (segs < 1) segs = 1;
     return (int)segs;
+}
+
+// Whether SSP-RK(3,3) steps of c are taken by the temporally blocked launch (one
+// launch and 64 B of traffic per point-step) instead of three stage launches (256 B):
+// wherever that kernel is built -- tortoise chart, FP64 state, WENO5 with FP64 or
+// FP32 weights, second-order theta differences -- unless the caller asks for a
+// budget of stage workgroups or the tuner found the stage launches faster.  The
+// results are the same to the bit.  Both measured, us a step, FP64 weights:
+// 16384 x 512 299 against 472, 8192 x 256 78.6 against 100.5, 4099 x 131 30.4
+// against 35.8, 2050 x 97 17.7 against 23.5, 1024 x 64 12.3 against 14.0, 512 x 32
+// 8.3 against 11.1, 200 x 12 8.4 against 11.0.
+bool fused_step(const teuk_config& c)
+{
+    return c.integrator == TEUK_RK_SSP33 && c.chart == TEUK_CHART_TORTOISE && c.state_prec == TEUK_S_FP64 &&
+           c.scheme == TEUK_SCHEME_WENO5 && (c.weight_prec == TEUK_W_FP64 || c.weight_prec == TEUK_W_FP32) &&
+           c.theta_order != 4 && c.workgroups == 0 && !tuned_stage_launches(c);
+}
+
+// Radial strips and workgroups of the temporally blocked launch: a budget of
+// workgroups gives whole tiles of equal height in every strip, without one the
+// rows of all strips are shared equally by the workgroups the GPU holds at once
+// (at least one strip-row each).  False if the kernel is not available.
+bool blocked_shape(const teuk_config& c, int budget, int* strips, int* grid)
+{
+    *strips = (c.nr + kBlockedPoints - 1) / kBlockedPoints;
+    const long long rows = (long long)*strips * c.ntheta;
+    long long g;
+    if (budget > 0) {
+        g = std::min((long long)budget / *strips, (long long)c.ntheta);
+        g = *strips * (g < 1 ? 1 : g);
+    } else {
+        g = blocked_grid(c.weight_prec);
+    }
+    *grid = (int)std::min(std::min(g, rows), (1LL << 31) - 1);
+    return *grid > 0;
 }
 
 teuk_status fail(teuk_solver* h, teuk_status st, const std::string& msg)
@@ -495,17 +531,11 @@ teuk_status teuk_create(const teuk_config* cfg, const teuk_device_ctx* ctx, teuk
             return fail(nullptr, TEUK_ERR_UNSUPPORTED, "pipelined steps: occupancy query failed");
         }
     }
-    if (cfg->integrator == TEUK_RK_SSP33_BLOCKED) {
-        h->bstrips = (cfg->nr + kBlockedPoints - 1) / kBlockedPoints;
-        long long cap = eff.workgroups > 0 ? eff.workgroups : blocked_grid(cfg->weight_prec);
-        long long segs = cap / h->bstrips;
-        if (segs > cfg->ntheta) segs = cfg->ntheta;
-        if (segs < 1) segs = 1;
-        h->bsegs = (int)segs;
-        if (cap <= 0 || (long long)h->bstrips * h->bsegs > (1LL << 31) - 1) {
-            free_solver(h);
-            return fail(nullptr, TEUK_ERR_UNSUPPORTED, "temporal blocking: occupancy query failed");
-        }
+    h->fused = fused_step(*cfg);
+    if ((h->fused || cfg->integrator == TEUK_RK_SSP33_BLOCKED) &&
+        !blocked_shape(*cfg, h->fused ? 0 : eff.workgroups, &h->bstrips, &h->bgrid)) {
+        free_solver(h);
+        return fail(nullptr, TEUK_ERR_UNSUPPORTED, "temporal blocking: occupancy query failed");
     }
     h->j_e = cfg->extract_every > 0 ? (int)std::floor((cfg->x_extract - cfg->x_min) / h->dx + 0.5) : 0;
     if (h->j_e > cfg->nr - 1) h->j_e = cfg->nr - 1;
@@ -699,14 +729,13 @@ static int blocked_step_once(teuk_solver* h, hipStream_t stream)
 {
     StageArgs a = stage_args(h);
     a.nstrips = h->bstrips;
-    a.segs = h->bsegs;
-    a.grid = h->bstrips * h->bsegs;
+    a.grid = h->bgrid;
     a.ca = 0.0;
     a.cb = 1.0;
     a.uk = h->u[0];
     a.un = h->u[0];
     a.out = h->u[1];
-    const int e = launch_blocked_step(a, h->cfg.weight_prec, stream);
+    const int e = launch_blocked_step(a, h->cfg.weight_prec, h->cfg.integrator == TEUK_RK_SSP33_BLOCKED, stream);
     if (!e) std::swap(h->u[0], h->u[1]);             // u^{n+1} is the new state buffer
     return e;
 }
@@ -717,6 +746,27 @@ static int run_stage(const teuk_solver* h, const StageArgs& a, int stage)
     const teuk_config& c = h->cfg;
     if (c.scheme != TEUK_SCHEME_WENO5) return launch_cmp_stage(a, stage, c.scheme, c.chart, h->stream);
     return launch_stage(a, stage, c.weight_prec, kernel_chart(c), h->stream);
+}
+
+// Step k of a run of n SSP-RK(3,3) steps of h on `stream`, a = stage_args(h): the
+// temporally blocked launch where the solver takes it, else three stage
+// launches.  keep: after the run the state has to be in the buffer that it was
+// in before it.  The blocked step moves the state to another buffer, so an odd
+// run takes three of them around the three buffers and then pairs, and a single
+// step the stage launches, which work in place (all of them give the same bits).
+static int rk3_step(teuk_solver* h, StageArgs& a, int64_t k, int64_t n, bool keep, hipStream_t stream)
+{
+    if (h->fused && !(keep && n == 1)) {
+        if (keep && (n & 1) && (k == 1 || k == 2)) std::swap(h->u[1], h->u[2]);
+        return blocked_step_once(h, stream);
+    }
+    int e = 0;
+    for (int stage = 1; stage <= 3 && !e; ++stage) {
+        rk3_stage(h, a, stage);
+        e = h->cfg.scheme != TEUK_SCHEME_WENO5 ? launch_cmp_stage(a, stage, h->cfg.scheme, h->cfg.chart, stream)
+                                               : launch_stage(a, stage, h->cfg.weight_prec, kernel_chart(h->cfg), stream);
+    }
+    return e;
 }
 
 // One SSP-RK(10,4) step (Sec. 3.2) in the three state buffers U = u^n,
@@ -846,12 +896,11 @@ static teuk_status step_eager(teuk_solver* h, int64_t nsteps)
         }
         return TEUK_OK;
     }
+    // A solver that a graph or a group's descriptors refer to keeps its state
+    // buffer over a call; the temporally blocked step moves it.
+    const bool keep = h->graph_chunk > 0 || h->group;
     for (int64_t n = 0; n < nsteps; ++n) {
-        int e = 0;
-        for (int stage = 1; stage <= 3 && !e; ++stage) {
-            rk3_stage(h, a, stage);
-            e = run_stage(h, a, stage);
-        }
+        const int e = rk3_step(h, a, n, nsteps, keep, h->stream);
         if (e) return hip_fail(h, e, "stage launch");
         ++h->steps;
         if (c.extract_every > 0 && h->steps % c.extract_every == 0) {
@@ -1056,7 +1105,7 @@ teuk_status teuk_info(teuk_solver* h, teuk_info_t* info)
     info->steps = h->steps;
     info->samples = h->samples;
     info->j_extract = h->j_e;
-    info->workgroups = h->cfg.integrator == TEUK_RK_SSP33_BLOCKED     ? h->bstrips * h->bsegs
+    info->workgroups = h->cfg.integrator == TEUK_RK_SSP33_BLOCKED     ? h->bgrid
                        : h->cfg.integrator == TEUK_RK_SSP33_PIPELINED ? h->pgrid
                                                                       : h->nstrips * h->segs[1];
     info->dt_bound = h->dt_bound;
@@ -1207,7 +1256,7 @@ static teuk_status group_upload(teuk_group* g)
             a.segs = group_segs(h->cfg.ntheta, g->rows);
             a.grid = 0;                                  // set per launch
             blk.tiles += (long long)h->nstrips * a.segs;
-            blk.solo_wg += bl ? (long long)h->bstrips * h->bsegs : (long long)h->nstrips * h->segs[1];
+            blk.solo_wg += bl ? (long long)h->bgrid : (long long)h->nstrips * h->segs[1];
             blk.units += (long long)h->nstrips * h->cfg.ntheta;
             if (blk.tiles > (1LL << 31) - 1)
                 return gfail(g, TEUK_ERR_CAPACITY, "group block too large for one launch (2^31 - 1 tiles)");
@@ -1328,8 +1377,12 @@ static teuk_status group_block_eager(teuk_group* g, size_t bi, int64_t nsteps, h
             int e = 0;
             if (b.solo) {
                 for (int k = b.first; k < b.first + b.n && !e; ++k) {
-                    const teuk_solver* h = g->order[(size_t)k];
+                    teuk_solver* h = g->order[(size_t)k];
                     StageArgs a = stage_args(h);
+                    if (h->fused) {
+                        if (stage == 1) e = rk3_step(h, a, n, nsteps, true, stream);
+                        continue;
+                    }
                     rk3_stage(h, a, stage);
                     e = launch_stage(a, stage, h->cfg.weight_prec, kernel_chart(h->cfg), stream);
                 }
@@ -1754,12 +1807,6 @@ extern "C" teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int6
             d.tables = true;
         }
     }
-    const int nstrips = (cfg->nr + kStripPoints - 1) / kStripPoints;
-    teuk_config eff = *cfg;
-    if (eff.workgroups == 0) eff.workgroups = tuned_workgroups(*cfg);
-    const int segs1 = pick_segs(eff, nstrips, cfg->weight_prec, true);
-    const int segs23 = pick_segs(eff, nstrips, cfg->weight_prec, false);
-    if (segs1 <= 0 || segs23 <= 0) return fail(nullptr, TEUK_ERR_UNSUPPORTED, "occupancy query failed");
     double* u1 = (double*)(base + kNaOffU1);
     double* u2 = (double*)(base + kNaOffU2);
     const double dx = (cfg->x_max - cfg->x_min) / (cfg->nr - 1);
@@ -1771,7 +1818,6 @@ extern "C" teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int6
     a.plane = (long long)cfg->nr * cfg->ntheta;
     a.nr = cfg->nr;
     a.nth = cfg->ntheta;
-    a.nstrips = nstrips;
     a.inv6dx = 1.0 / (6.0 * dx);
     theta_scales(cfg->theta_order, dth, &a.ih1, &a.ih2);
     a.dt = cfg->dt;
@@ -1782,6 +1828,35 @@ extern "C" teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int6
     a.eps = cfg->weno_eps;
     a.parity = ((cfg->m + cfg->s) % 2 != 0) ? -1.0 : 1.0;
     const int kchart = kernel_chart(*cfg);
+    int bstrips = 0, bgrid = 0;
+    if (nsteps > 1 && fused_step(*cfg) && blocked_shape(*cfg, 0, &bstrips, &bgrid)) {
+        // the temporally blocked step, from buffer to buffer: pairs u -> u1 -> u, and an
+        // odd count starts with three around u -> u1 -> u2 -> u
+        a.ca = 0.0;
+        a.cb = 1.0;
+        a.flip = 0;
+        a.nstrips = bstrips;
+        a.segs = 0;
+        a.grid = bgrid;
+        double* at = u;
+        for (int64_t n = 0; n < nsteps && !e; ++n) {
+            double* to = at != u ? u : u1;
+            if ((nsteps & 1) && n == 1) to = u2;
+            a.uk = a.un = at;
+            a.out = to;
+            e = launch_blocked_step(a, cfg->weight_prec, false, st);
+            at = to;
+        }
+        if (e) return fail(nullptr, TEUK_ERR_DEVICE, std::string("blocked step launch: ") + hipGetErrorString((hipError_t)e));
+        return TEUK_OK;
+    }
+    const int nstrips = (cfg->nr + kStripPoints - 1) / kStripPoints;
+    teuk_config eff = *cfg;
+    if (eff.workgroups == 0) eff.workgroups = tuned_workgroups(*cfg);
+    const int segs1 = pick_segs(eff, nstrips, cfg->weight_prec, true);
+    const int segs23 = pick_segs(eff, nstrips, cfg->weight_prec, false);
+    if (segs1 <= 0 || segs23 <= 0) return fail(nullptr, TEUK_ERR_UNSUPPORTED, "occupancy query failed");
+    a.nstrips = nstrips;
     for (int64_t n = 0; n < nsteps && !e; ++n) {
         // consecutive launches march their segments in opposite directions (see teuk_step)
         a.uk = u; a.un = u; a.out = u1; a.ca = 0.0; a.cb = 1.0; a.segs = segs1; a.grid = nstrips * segs1; a.flip = (int)(n & 1);

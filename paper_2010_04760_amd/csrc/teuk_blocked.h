@@ -1,0 +1,370 @@
+// Temporal blocking: one whole SSP-RK(3,3) step per launch.  The three stages
+// of a tile are computed in one workgroup, the intermediate states u(1) and
+// u(2) never leave LDS, and HBM sees one read of u^n and one write of u^{n+1} per
+// point (64 B instead of 256 B per point-step).  The price is recomputation at
+// the tile edges: a stage needs three radial neighbours and one theta neighbour
+// of its input on each side.  (Device code and its launchers, a part of
+// teuk_kernels.hip.)
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <type_traits>
+
+#include "teuk_coef.h"
+#include "teuk_device.h"
+#include "teuk_internal.h"
+
+namespace teuk {
+
+namespace {
+
+// Radially a tile spans 127 points q = 0 .. 126, point q standing for
+// j = 114 strip - 6 + q in all three stages, held by two waves: wave 0 points
+// 0 .. 63, wave 1 points 63 .. 126.  The two overlap by one point so that every
+// point but the last of each wave finds its j + 1/2 flux in the next lane of its
+// own wave; point 63 is computed by wave 1 (wave 0's copy, lacking that flux, is
+// never stored).  Stage 1 is valid on points 0 .. 125, stage 2 on 3 .. 122 and
+// stage 3 (the output) on 6 .. 119: 114 outputs per 128 lanes.
+constexpr int kBW = kBlockedPoints;      // output points per tile
+constexpr int kBLead = 6;                // first output point of a tile
+constexpr int kBPts = 2 * kWave - 1;     // points of a tile (the waves share one)
+constexpr int kBStage = kBPts + 6;       // staged u^n positions: q - 3 .. q + 3 of every point
+constexpr int kBHalf = 2 * kWave;        // threads of one half
+constexpr int kBThreads = 2 * kBHalf;    // two halves
+static_assert(kBLead + kBW + kBLead + 1 == kBPts, "tile geometry");
+
+// Along theta a tile of rows [k0, k1) is marched by two such pairs of waves from
+// its middle row kb outwards: half 1 takes kb, kb + 1, ... and half 0 kb - 1,
+// kb - 2, ....  At step i a half stages its u^n row i + 1 (LDS, three-slot ring),
+// computes u(1) at its row i, u(2) at i - 1 and u^{n+1} at i - 2.  Where the two
+// meet, each finds the other's u(1) and u(2) rows in LDS one step after they
+// were computed, so only the far ends recompute rows that belong to the
+// neighbouring tiles (u(1) on two rows beyond, u(2) on one; a pole takes the
+// parity ghost of the stage's own input): half the recomputation of a tile
+// marched from one end, for the same rows per wave.
+//
+// One barrier a step orders all LDS traffic: every row read in step i was written
+// in an earlier step, into a slot whose previous row was last read in an earlier
+// step (three slots in each ring).
+//
+// A workgroup takes an equal share of the grid's strip-rows (strip by strip, the
+// rows of a strip in order), in one tile per strip that its share touches, so
+// that the last round of tiles does not leave part of the GPU idle: on
+// 16384 x 512 whole tiles per strip would keep 432 of 512 workgroup slots busy.
+//
+// The arithmetic of each point and stage is the stage kernels', operation by
+// operation; the per-point coefficients of a row are built once, by stage 1, and
+// reused by stages 2 and 3 (a lane keeps its radial point through all three).
+//
+// Bound: FP64 VALU issue (HBM sees 75 B per point-step).  The march is unrolled
+// by three so that the values rolling over three rows (coefficients, u^n) and the
+// three-slot rings keep fixed registers and addresses.
+constexpr int kBS1 = 2 * 4 * 3 * kBStage;            // u(1) rings
+constexpr int kBS2 = 2 * 4 * 3 * kBPts;              // u(2) rings, from the u(1) rings on
+
+typedef const volatile __attribute__((address_space(3))) double* LdsLoad;
+typedef __attribute__((address_space(3))) double* LdsDouble;
+__device__ __forceinline__ LdsDouble lds_at(double* p)
+{
+    LdsDouble a = (LdsDouble)p;
+    asm("" : "+v"(a));
+    return a;
+}
+__device__ __forceinline__ double lds_get(LdsDouble p, int i) { return ((LdsLoad)p)[i]; }
+
+// A value of a uniform row pointer, which is kept in scalar registers (the loop
+// would otherwise carry it, and add to it, in vector registers).
+typedef __attribute__((address_space(1))) char* GlobalChar;
+__device__ __forceinline__ GlobalChar scalar(const double* p)
+{
+    GlobalChar g = (GlobalChar)const_cast<double*>(p);
+    asm("" : "+s"(g));
+    return g;
+}
+__device__ __forceinline__ double row_get(const double* row, unsigned off)
+{
+    return *(__attribute__((address_space(1))) const double*)(scalar(row) + off);
+}
+__device__ __forceinline__ void row_put(double* row, unsigned off, double v)
+{
+    *(__attribute__((address_space(1))) double*)(scalar(row) + off) = v;
+}
+
+template <int WP, bool kBtFirst>
+__global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
+{
+    // per half and plane, three-row rings of u^n (position s = point p0 - 3 + s) and
+    // of u(1) and u(2) (one value per point).  The planes are more than 255 values
+    // apart and the accesses go through opaque addresses plus immediate offsets:
+    // pairs of reads merged by the compiler would need an address of their own
+    // each (20 VALU instructions a step).
+    __shared__ double lds[2 * 4 * 3 * (kBStage + 2 * kBPts)];
+    const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBHalf);
+    const int tid = (int)threadIdx.x - half * kBHalf;
+    const int l = tid - (tid >= kWave ? 1 : 0);          // point of this lane in the tile
+    const bool dup = tid == kWave - 1;                    // wave 0's copy of point 63
+    const int nr = A.nr, nth = A.nth;
+    const long long P = A.plane;
+    const WenoK K = weno_consts(A.eps);
+    const double* ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
+    double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
+    const int dir = half ? 1 : -1;
+    const double ih1 = half ? A.ih1 : -A.ih1;
+
+    const int G = (int)gridDim.x;
+    const int rank = xcd_rank((int)blockIdx.x, G);
+    const long long total = (long long)A.nstrips * nth;
+    long long at = total * rank / G;
+    const long long end = total * (rank + 1) / G;
+    while (at < end) {                                    // uniform over the workgroup
+        const int strip = (int)(at / nth);
+        const int k0 = (int)(at - (long long)strip * nth);
+        const int k1 = (int)(end - at < nth - k0 ? k0 + (end - at) : nth);
+        at += k1 - k0;
+        // the middle row, with at least one grid row on either side of it
+        int kb = (k0 + k1) >> 1;
+        if (kb == 0) kb = 1;
+        const int n0 = kb - k0, n1 = k1 - kb;             // rows of the halves (one may be 0)
+        const int n = half ? n1 : n0;
+        const int first = half ? kb : kb - 1;
+        const int lim = half ? nth - kb : kb;             // grid rows from `first` on, in this half's direction
+        const int N1 = min(n + 2, lim), N2 = min(n + 1, lim), NS = min(N1 + 1, lim);
+        const int steps = max(n0, n1) + 2;
+
+        const int p0 = strip * kBW - kBLead;              // grid point of tile point 0
+        const int j = p0 + l;
+        const unsigned oc = (unsigned)clampi(j, 0, nr - 1) * 8u;
+        const unsigned oa = (unsigned)clampi(p0 - 3 + tid, 0, nr - 1) * 8u;            // staged position tid
+        const unsigned ob = (unsigned)clampi(p0 - 3 + kBHalf + tid, 0, nr - 1) * 8u;   // position 128 + tid
+        const bool halo = tid < kBStage - kBHalf;
+        // radial ghosts of u(1), u(2): the end values, by clamping to the points inside the grid
+        const int lo = clampi(-p0, 0, kBPts - 1), hi = clampi(nr - 1 - p0, 0, kBPts - 1);
+        LdsDouble q[6];
+#pragma unroll
+        for (int t = 0; t < 6; ++t) q[t] = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + clampi(l - 3 + t, lo, hi));
+        const LdsDouble own = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + l);
+        const LdsDouble across = lds_at(lds + kBS1 + (half ^ 1) * 4 * 3 * kBPts + l);
+        const LdsDouble rows = lds_at(lds + half * 4 * 3 * kBStage + l), put = lds_at(lds + half * 4 * 3 * kBStage + tid);
+        const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
+        const Radial rt = load_radial(A, oc);
+
+        double xa[4], xb[4] = {0, 0, 0, 0};
+        auto load_row = [&](int i) {
+            const size_t row = (size_t)(first + dir * i) * nr;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) xa[p] = row_get(ukp[p] + row, oa);
+            if (halo) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) xb[p] = row_get(ukp[p] + row, ob);
+            }
+        };
+        auto store_row = [&](int b) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage] = xa[p];
+            if (halo) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage + kBHalf] = xb[p];
+            }
+        };
+
+        // One stage at one row for this lane, from the window w[p][t] (input of plane p
+        // at j - 3 + t): the fluxes first, in the block that reads the window, so that
+        // a plane's flux starts as its values arrive and covers the reads of the next;
+        // then the rest with the input Phi at the own point on the rows ahead and behind.
+        struct Fluxes { Flux f[4]; double fn[4]; };
+        auto fluxes = [&](const double (&w)[4][6]) {
+            Fluxes r;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) r.f[p] = Weno<WP>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
+#pragma unroll
+            for (int p = 2; p < 4; ++p) r.f[p] = Weno<WP>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) r.fn[p] = next_lane(r.f[p].y);
+            return r;
+        };
+        auto finish = [&](const Fluxes& f, const double (&w)[4][6], double ahR, double ahI, double bhR, double bhI,
+                          const PointCoef& c) {
+            // second differences as (up - 2 own) + down; a branch, as selects would
+            // cost sixteen instructions
+            Theta xR, xI;
+            if (half) {
+                xR = theta2(w[0][3], ahR, bhR);
+                xI = theta2(w[1][3], ahI, bhI);
+                asm volatile("" : "+v"(xR.d2));
+            } else {
+                xR = theta2(w[0][3], bhR, ahR);
+                xI = theta2(w[1][3], bhI, ahI);
+                asm volatile("" : "+v"(xI.d2));
+            }
+            xR.d1 = ahR - bhR;
+            xI.d1 = ahI - bhI;
+            const Four F = rhs_t<kBtFirst>(A, ih1, c, plus_diff<WP>(K, f.f[0], f.fn[0]), plus_diff<WP>(K, f.f[1], f.fn[1]),
+                                           minus_diff<WP>(K, f.f[2], f.fn[2]), minus_diff<WP>(K, f.f[3], f.fn[3]), w[0][3],
+                                           w[1][3], w[2][3], w[3][3], xR, xI);
+            Four v;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) v.v[p] = euler(w[p][3], A.dt, F.v[p]);
+            return v;
+        };
+
+        PointCoef pc[3];
+        double un[3][4];                     // u^n at the own point, rows i, i - 1, i - 2
+        double b0R, b0I;                     // Phi of u^n on row i - 1
+        double a1R = 0, a1I = 0;             // Phi of u(1) on row i (its parity ghost beyond a pole)
+        double b1R = 0, b1I = 0;             // ... on row i - 2
+        double a2R = 0, a2I = 0;             // Phi of u(2) on row i - 1
+        double b2R = 0, b2I = 0;             // ... on row i - 3
+        {
+            const size_t row = (size_t)(first - dir) * nr;
+            b0R = ldb(ukp[0] + row, oc);
+            b0I = ldb(ukp[1] + row, oc);
+        }
+        load_row(0);
+        store_row(0);
+        if (NS > 1) {
+            load_row(1);
+            store_row(1);
+        }
+        if (NS > 2) load_row(2);
+
+        auto step = [&](auto phase, int i) {
+            constexpr int c0 = decltype(phase)::value, c1 = (c0 + 1) % 3, c2 = (c0 + 2) % 3;
+            lds_sync();
+            if (i < N1) {
+                // ---- stage 1 at row i: u(1) = u^n + dt F(u^n)
+                double w[4][6];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = lds_get(rows, (p * 3 + c0) * kBStage + t);
+                double ahR = lds_get(rows, c1 * kBStage + 3), ahI = lds_get(rows, (3 + c1) * kBStage + 3);
+                const Polar pol = load_polar(A, first + dir * i);
+                const Fluxes f = fluxes(w);
+                pc[c0] = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
+                if (i + 1 >= lim) {          // a ghost row (the ring holds an older one)
+                    ahR = A.parity * w[0][3];
+                    ahI = A.parity * w[1][3];
+                }
+                const Four o = finish(f, w, ahR, ahI, b0R, b0I, pc[c0]);
+                if (!dup) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) own[(p * 3 + c0) * kBPts] = o.v[p];
+                }
+#pragma unroll
+                for (int p = 0; p < 4; ++p) un[c0][p] = w[p][3];
+                b0R = w[0][3];
+                b0I = w[1][3];
+                a1R = o.v[0];
+                a1I = o.v[1];
+            } else {                         // beyond the pole (or no longer needed)
+                a1R *= A.parity;
+                a1I *= A.parity;
+            }
+            if (i >= 1 && i - 1 < N2) {
+                // ---- stage 2 at row i - 1: u(2) = 3/4 u^n + 1/4 (u(1) + dt F(u(1)))
+                if (c0 == 1 && i == 1) {     // across the middle: the other half's row 0
+                    b1R = lds_get(across, c2 * kBPts);
+                    b1I = lds_get(across, (3 + c2) * kBPts);
+                }
+                double w[4][6];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = lds_get(q[t], (p * 3 + c2) * kBPts);
+                const Fluxes f = fluxes(w);
+                const Four o = finish(f, w, a1R, a1I, b1R, b1I, pc[c2]);
+                Four u2;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) u2.v[p] = combine(0.75, un[c2][p], 0.25, o.v[p]);
+                if (!dup) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) own[kBS2 + (p * 3 + c2) * kBPts] = u2.v[p];
+                }
+                a2R = u2.v[0];
+                a2I = u2.v[1];
+                b1R = w[0][3];
+                b1I = w[1][3];
+            } else {
+                a2R *= A.parity;
+                a2I *= A.parity;
+            }
+            if (i >= 2 && i - 2 < n) {
+                // ---- stage 3 at row i - 2: u^{n+1} = 1/3 u^n + 2/3 (u(2) + dt F(u(2)))
+                if (c0 == 2 && i == 2) {
+                    b2R = lds_get(across, kBS2 + c1 * kBPts);
+                    b2I = lds_get(across, kBS2 + (3 + c1) * kBPts);
+                }
+                double w[4][6];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = lds_get(q[t], kBS2 + (p * 3 + c1) * kBPts);
+                const Fluxes f = fluxes(w);
+                const Four o = finish(f, w, a2R, a2I, b2R, b2I, pc[c1]);
+                if (out_lane) {
+                    const size_t row = (size_t)(first + dir * (i - 2)) * nr;
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) row_put(outp[p] + row, oc, combine(1.0 / 3.0, un[c1][p], 2.0 / 3.0, o.v[p]));
+                }
+                b2R = w[0][3];
+                b2I = w[1][3];
+            }
+            // row i + 2 into the slot of row i - 1
+            if (i + 2 < NS) {
+                store_row(c2);
+                if (i + 3 < NS) load_row(i + 3);
+            }
+        };
+        int i = 0;
+        for (;;) {
+            step(std::integral_constant<int, 0>{}, i);
+            if (++i >= steps) break;
+            step(std::integral_constant<int, 1>{}, i);
+            if (++i >= steps) break;
+            step(std::integral_constant<int, 2>{}, i);
+            if (++i >= steps) break;
+        }
+        lds_sync();   // before the next tile's rows go into the rings
+    }
+}
+
+}  // namespace
+
+int blocked_grid(int weight_prec)
+{
+    static ResidentCache cache[2];
+    int dev = 0;
+    if ((weight_prec != TEUK_W_FP64 && weight_prec != TEUK_W_FP32) || hipGetDevice(&dev) != hipSuccess) return 0;
+    return cache[weight_prec == TEUK_W_FP32].get(dev, [&] {
+        int cus = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        const hipError_t e =
+            weight_prec == TEUK_W_FP64
+                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, blocked_step_kernel<TEUK_W_FP64, true>, kBThreads, 0)
+                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, blocked_step_kernel<TEUK_W_FP32, false>, kBThreads, 0);
+        return e != hipSuccess || per_cu < 1 ? 0 : cus * per_cu;
+    });
+}
+
+int launch_blocked_step(const StageArgs& a, int weight_prec, bool own_order, void* stream)
+{
+    if (a.nr < 1 || a.nth < 2 || a.nstrips < 1 || a.grid < 1 || (long long)a.grid > (long long)a.nstrips * a.nth ||
+        (long long)a.nstrips * kBW < a.nr || a.uk == a.out)
+        return (int)hipErrorInvalidValue;
+    (void)hipGetLastError();
+    const dim3 grid((unsigned)a.grid), block(kBThreads);
+    hipStream_t st = (hipStream_t)stream;
+    if (weight_prec == TEUK_W_FP64 && own_order)
+        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP64, false>), grid, block, 0, st, a);
+    else if (weight_prec == TEUK_W_FP64)
+        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP64, true>), grid, block, 0, st, a);
+    else if (weight_prec == TEUK_W_FP32)
+        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP32, false>), grid, block, 0, st, a);
+    else
+        return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
+}
+
+}  // namespace teuk

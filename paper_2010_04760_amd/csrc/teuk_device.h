@@ -364,7 +364,8 @@ struct Four {
 };
 
 // F(u) of one point: dPh*, dPi* the radial derivatives times 6 dx, xR, xI the
-// theta differences of Phi.
+// theta differences of Phi, ih1 the scale of the first (negated by a caller that
+// took it backwards).
 //     d_t Phi = pi - b d_x Phi
 //     d_t pi  = b d_x pi - m3 d_x Phi + B~t pi + A~thth Phi_thth + B~th Phi_th + C~ Phi
 // kBtFirst: which product of Im(B~t pi) is fused into the other's rounding.  It
@@ -375,7 +376,7 @@ template <int WP>
 constexpr bool bt_first() { return WP == TEUK_W_FP64 || WP == TEUK_W_BF16; }
 
 template <bool kBtFirst>
-__device__ __forceinline__ Four rhs_t(const StageArgs& A, const PointCoef& c, double dPhR, double dPhI, double dPiR,
+__device__ __forceinline__ Four rhs_t(const StageArgs& A, double ih1, const PointCoef& c, double dPhR, double dPhI, double dPiR,
                                       double dPiI, double phR, double phI, double piR, double piI, const Theta& xR,
                                       const Theta& xI)
 {
@@ -390,8 +391,8 @@ __device__ __forceinline__ Four rhs_t(const StageArgs& A, const PointCoef& c, do
     sI += kBtFirst ? fmad(c.btr, piI, c.bti * piR) : fmad(c.bti, piR, c.btr * piI);
     sR = fmad(c.ath, xR.d2 * A.ih2, sR);
     sI = fmad(c.ath, xI.d2 * A.ih2, sI);
-    sR = fmad(c.bth, xR.d1 * A.ih1, sR);
-    sI = fmad(c.bth, xI.d1 * A.ih1, sI);
+    sR = fmad(c.bth, xR.d1 * ih1, sR);
+    sI = fmad(c.bth, xI.d1 * ih1, sI);
     sR += fmad(c.cr, phR, -(c.ci * phI));
     sI += fmad(c.ci, phR, c.cr * phI);
     return {{fmad(-c.b, dPhR, piR), fmad(-c.b, dPhI, piI), sR, sI}};
@@ -442,14 +443,13 @@ __device__ __forceinline__ double combine(double ca, double un, double cb, doubl
     return fmad(ca, un, cb * v);
 }
 
-// x of lane l + 1 (lane 63 keeps its own), by a DPP wavefront shift: no LDS
-// round trip, unlike __shfl_down.  Used wherever a lane takes the interface
-// flux of the lane after it.
+// x of lane l + 1 (0 in lane 63), by a DPP wavefront shift: no LDS round trip,
+// unlike __shfl_down.  Used wherever a lane takes the interface flux of the lane
+// after it; lane 63 never uses what it gets.
 __device__ __forceinline__ double next_lane(double x)
 {
-    int lo = __double2loint(x), hi = __double2hiint(x);
-    lo = __builtin_amdgcn_update_dpp(lo, lo, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(hi, hi, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0x130 /* wave_shl:1 */, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0x130 /* wave_shl:1 */, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 
@@ -475,6 +475,15 @@ __device__ __forceinline__ double ldb(const double* base, unsigned off)
 __device__ __forceinline__ void stb(double* base, unsigned off, double v)
 {
     *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) = v;
+}
+
+// Ranks are dealt so that each XCD (which receives every eighth workgroup id)
+// owns a contiguous block of ranks, i.e. whole strips and their neighbours.
+__device__ __forceinline__ int xcd_rank(int bid, int G)
+{
+    const int xcd = bid & 7, loc = bid >> 3;
+    const int q8 = G >> 3, r8 = G & 7;
+    return xcd * q8 + (xcd < r8 ? xcd : r8) + loc;
 }
 
 }  // namespace

@@ -2,6 +2,7 @@
 // (teuk_background.cpp) and the device kernels (teuk_kernels.hip).
 #pragma once
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 #include <string>
@@ -41,6 +42,24 @@ inline void theta_scales(int theta_order, double dth, double* ih1, double* ih2)
 // Points per radial strip of one stage workgroup (one wave of 64 lanes computes
 // 64 interface fluxes and 63 point updates).
 constexpr int kStripPoints = 63;
+
+// Resident workgroups of a kernel on each device, once asked for (they depend on
+// the code and the device alone; the query costs microseconds, which a caller
+// of short runs would pay at every call).
+struct ResidentCache {
+    std::atomic<int> of[64] = {};
+    template <class Query>
+    int get(int dev, Query query)
+    {
+        if (dev < 0 || dev >= 64) return query();
+        int n = of[dev].load(std::memory_order_relaxed);
+        if (n <= 0) {
+            n = query();
+            of[dev].store(n, std::memory_order_relaxed);
+        }
+        return n;
+    }
+};
 
 // Arguments of one fused SSP-RK stage launch.
 struct StageArgs {
@@ -84,6 +103,9 @@ struct DDStageArgs {
 // Workgroup budget that teuk_tune found fastest for c's launch class on the
 // current device, or 0 if it has not been tuned.
 int tuned_workgroups(const teuk_config& c);
+// Whether teuk_tune found c's launch class (SSP-RK(3,3)) faster by stage launches of
+// its tuned budget than by the temporally blocked launch.
+bool tuned_stage_launches(const teuk_config& c);
 
 // Resident workgroup count of a stage-kernel instantiation on the current
 // device (0 if the weight precision is not built).  The launch uses
@@ -107,14 +129,16 @@ int launch_dt_bound(const double* rtab, const double* ttab, const double* ctab, 
 int launch_guard(const double* u, long long n, int* flag, void* stream);
 int launch_coef_dump(const double* rtab, const double* ttab, const double* ctab, int nr, int nth, double* out,
                      void* stream);
-// Temporal blocking: one whole SSP-RK(3,3) step (tortoise chart, FP64 or
-// FP32 weights) from a.uk into a.out (distinct buffers), tiles of
-// kBlockedPoints radial points by a.nth / a.segs rows, a.grid = a.nstrips *
-// a.segs workgroups.  blocked_grid(weight_prec) is the resident workgroup
-// count (0 for a precision without a blocked kernel).
+// Temporal blocking: one whole SSP-RK(3,3) step (tortoise chart, FP64 or FP32
+// weights) from a.uk into a.out (distinct buffers) by a.grid workgroups, each an
+// equal share of the rows of the a.nstrips strips of kBlockedPoints radial points
+// (a.grid <= a.nstrips * a.nth).  own_order: the order of one sum that
+// TEUK_RK_SSP33_BLOCKED results have had, else the stage kernels'.
+// blocked_grid(weight_prec) is the resident workgroup count (0 for a precision
+// without a blocked kernel).
 constexpr int kBlockedPoints = 114;
 int blocked_grid(int weight_prec);
-int launch_blocked_step(const StageArgs& a, int weight_prec, void* stream);
+int launch_blocked_step(const StageArgs& a, int weight_prec, bool own_order, void* stream);
 // Pipelined steps (tortoise chart, FP64 state, WENO5): nsteps SSP-RK(3,3)
 // steps in one cooperative launch of `grid` workgroups (at most pipe_grid(),
 // the resident count, and at most the tile count st[0].nstrips * st[0].segs);

@@ -25,6 +25,7 @@
 
 #include <cstdint>
 
+#include "teuk_blocked.h"
 #include "teuk_coef.h"
 #include "teuk_device.h"
 #include "teuk_internal.h"
@@ -487,7 +488,7 @@ __device__ __forceinline__ void march_strip_t(const StageArgs& A, char* ring, in
                 xR = theta2(phR, upR, dnR);
                 xI = theta2(phI, upI, dnI);
             }
-            const Four F = rhs_t<bt_first<WP>()>(A, c, plus_diff<WP>(K, fR, fR1), plus_diff<WP>(K, fI, fI1), minus_diff<WP>(K, gR, gR1),
+            const Four F = rhs_t<bt_first<WP>()>(A, A.ih1, c, plus_diff<WP>(K, fR, fR1), plus_diff<WP>(K, fI, fI1), minus_diff<WP>(K, gR, gR1),
                                  minus_diff<WP>(K, gI, gI1), phR, phI, piR, piI, xR, xI);
             write_point<kMode, kCoh>(A, row, oc, F, phR, phI, piR, piI, n0, n1, n2, n3);
         }
@@ -530,15 +531,6 @@ __device__ __forceinline__ void run_tile(const StageArgs& A, char* lds, int rank
     const int k0 = (int)((long long)A.nth * seg / A.segs);
     const int k1 = (int)((long long)A.nth * (seg + 1) / A.segs);
     if (k1 > k0) march<WP, kMode, kChart, true>(A, lds, strip, k0, k1, ((seg ^ A.flip) & 1) ? -1 : 1);
-}
-
-// Ranks are dealt so that each XCD (which receives every eighth workgroup id)
-// owns a contiguous block of ranks, i.e. whole strips and their neighbours.
-__device__ __forceinline__ int xcd_rank(int bid, int G)
-{
-    const int xcd = bid & 7, loc = bid >> 3;
-    const int q8 = G >> 3, r8 = G & 7;
-    return xcd * q8 + (xcd < r8 ? xcd : r8) + loc;
 }
 
 template <int WP, int kMode, int kChart>
@@ -678,253 +670,6 @@ __global__ __launch_bounds__(kWave, 4) void pipe_kernel(PipeArgs P)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0)
             __hip_atomic_store(P.done + r, need + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// ---------------------------------------------------------------- temporal blocking
-// One whole SSP-RK(3,3) step per launch (tortoise chart): the three stages of a
-// tile are computed in one workgroup of two waves, the intermediate states u(1)
-// and u(2) never leave LDS, and HBM sees one read of u^n and one write of
-// u^{n+1} per point (64 B instead of 256 B per point-step).  The price is
-// recomputation at the tile edges: a stage needs three radial neighbours and one
-// theta neighbour of its input on each side, so
-//   - a tile spans 127 radial points q = 0 .. 126, point q standing for
-//     j = 114 strip - 6 + q in all three stages.  Wave 0 holds points 0..63 and
-//     wave 1 points 63..126: the two overlap by one point so that every point
-//     but the last of each wave finds its j + 1/2 flux in the next lane of its
-//     own wave.  Point 63 is computed by wave 1 (wave 0's copy, lacking that
-//     flux, is never stored);
-//   - stage 1 is valid on points 0..125, stage 2 on 3..122 and stage 3 (the
-//     output) on 6..119: 114 outputs per 128 lanes;
-//   - a tile of final rows [k0, k1) computes stage 1 on [k0-2, k1+2) and stage
-//     2 on [k0-1, k1+1) (clipped to the grid; a pole takes the parity ghost of
-//     the stage's own input, as in the three-launch step).
-// The workgroup marches the rows upward: at step r it stages u^n row r+1 (LDS),
-// computes u(1) at row r, u(2) at row r-1 and u^{n+1} at row r-2.  Radial
-// ghosts of u(1) and u(2) are the end values, read by clamping the point index
-// to the points inside the grid.  The arithmetic of each point and stage is
-// the three-launch stage kernel's, term for term, except that the per-point
-// coefficients of a row are built once, by stage 1, and reused by stages 2
-// and 3 when the march reaches that row for them (a lane keeps its radial
-// point through all three stages).
-constexpr int kBW = 114;                 // output points per tile
-constexpr int kBLead = 6;                // first output point of a tile
-constexpr int kBThreads = 2 * kWave;     // two waves
-constexpr int kBPts = 2 * kWave - 1;     // points of a tile (the waves share one)
-constexpr int kBStage = kBPts + 6;       // staged u^n positions: q - 3 .. q + 3 of every point
-static_assert(kBLead + kBW + kBLead + 1 == kBPts, "tile geometry");
-
-template <int WP>
-__global__ __launch_bounds__(kBThreads) void blocked_step_kernel(StageArgs A)
-{
-    __shared__ double sn[3][4][kBStage];   // u^n rows (three-slot ring), position s = point p0 - 3 + s
-    __shared__ double s1[2][4][kBPts];     // u(1) rows, one value per point
-    __shared__ double s2[2][4][kBPts];     // u(2) rows
-    const int tid = threadIdx.x;
-    const int l = tid - (tid >= kWave ? 1 : 0);          // point of this lane in the tile
-    const bool dup = tid == kWave - 1;                    // wave 0's copy of point 63
-    const int nr = A.nr, nth = A.nth;
-    const long long P = A.plane;
-    const int rank = xcd_rank((int)blockIdx.x, (int)gridDim.x);
-    const int strip = rank / A.segs;
-    const int seg = rank - strip * A.segs;
-    const int k0 = (int)((long long)nth * seg / A.segs);
-    const int k1 = (int)((long long)nth * (seg + 1) / A.segs);
-    if (k1 <= k0) return;                                 // uniform over the workgroup
-    const int p0 = strip * kBW - kBLead;                  // grid point of tile point 0
-    const int j = p0 + l;
-    const int jc = clampi(j, 0, nr - 1);
-    const unsigned oc = (unsigned)jc * 8u;
-    const unsigned oa = (unsigned)clampi(p0 - 3 + tid, 0, nr - 1) * 8u;               // staged position tid
-    const unsigned ob = (unsigned)clampi(p0 - 3 + kBThreads + tid, 0, nr - 1) * 8u;   // position 128 + tid
-    const bool halo = tid < kBStage - kBThreads;
-    const int lo = clampi(-p0, 0, kBPts - 1), hi = clampi(nr - 1 - p0, 0, kBPts - 1);   // points inside the grid
-    const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
-    const double* ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
-    double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
-    const Radial rt = load_radial(A, oc);
-    const WenoK K = weno_consts(A.eps);
-
-    const int r1lo = max(k0 - 2, 0), r1hi = min(k1 + 2, nth);   // stage-1 rows
-    const int r2lo = max(k0 - 1, 0), r2hi = min(k1 + 1, nth);   // stage-2 rows
-    const int nstage = min(r1hi + 1, nth);                       // u^n rows staged: [r1lo, nstage)
-
-    double xa[4], xb[4];
-    auto load_row = [&](int k) {
-        const size_t row = (size_t)k * nr;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) xa[p] = ldb(ukp[p] + row, oa);
-        if (halo) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p) xb[p] = ldb(ukp[p] + row, ob);
-        }
-    };
-    auto store_row = [&](int b) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) sn[b][p][tid] = xa[p];
-        if (halo) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p) sn[b][p][kBThreads + tid] = xb[p];
-        }
-    };
-    auto cl = [&](int q) { return clampi(q, lo, hi); };
-
-    // one stage at one row for this lane: w[p][t] = input of plane p at j - 3 + t,
-    // dn / up = input Phi at the own point on rows k - 1 / k + 1
-    struct Out { double v[4]; };
-    auto stage = [&](const double (&w)[4][6], double dnR, double dnI, double upR, double upI, const PointCoef& c,
-                     double ca, double cb, const double (&un)[4], bool first) {
-        const Flux fR = Weno<WP>::flux(w[0][0], w[0][1], w[0][2], w[0][3], w[0][4], K);
-        const Flux fI = Weno<WP>::flux(w[1][0], w[1][1], w[1][2], w[1][3], w[1][4], K);
-        const Flux gR = Weno<WP>::flux(w[2][5], w[2][4], w[2][3], w[2][2], w[2][1], K);
-        const Flux gI = Weno<WP>::flux(w[3][5], w[3][4], w[3][3], w[3][2], w[3][1], K);
-        const Four F = rhs_t<false>(A, c, plus_diff<WP>(K, fR, next_lane(fR.y)), plus_diff<WP>(K, fI, next_lane(fI.y)),
-                             minus_diff<WP>(K, gR, next_lane(gR.y)), minus_diff<WP>(K, gI, next_lane(gI.y)), w[0][3],
-                             w[1][3], w[2][3], w[3][3], theta2(w[0][3], upR, dnR), theta2(w[1][3], upI, dnI));
-        Out o;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const double v = euler(w[p][3], A.dt, F.v[p]);
-            o.v[p] = first ? v : combine(ca, un[p], cb, v);
-        }
-        return o;
-    };
-
-    // rolling own-point values: u^n (4 planes) at rows r, r-1, r-2; Phi of
-    // u^n at r-1; Phi of u(1) at r-2, r-1, r; Phi of u(2) at r-3, r-2, r-1
-    double un0[4] = {0, 0, 0, 0}, un1[4] = {0, 0, 0, 0}, un2[4] = {0, 0, 0, 0};
-    double nbR = 0, nbI = 0;                 // u^n Phi on row r - 1
-    double a2R = 0, a2I = 0, a1R = 0, a1I = 0, a0R = 0, a0I = 0;   // u(1) Phi on r-2, r-1, r
-    double c3R = 0, c3I = 0, c2R = 0, c2I = 0, c1R = 0, c1I = 0;   // u(2) Phi on r-3, r-2, r-1
-    // per-point coefficients of rows r, r - 1, r - 2, built by stage 1 and
-    // reused by stages 2 and 3 (the same point and row one and two steps of
-    // the march later)
-    PointCoef pc0{}, pc1{}, pc2{};
-    {
-        const int kb = r1lo - 1;
-        if (kb >= 0) {
-            nbR = ldb(ukp[0] + (size_t)kb * nr, oc);
-            nbI = ldb(ukp[1] + (size_t)kb * nr, oc);
-        } else {
-            nbR = A.parity * ldb(ukp[0] + (size_t)r1lo * nr, oc);
-            nbI = A.parity * ldb(ukp[1] + (size_t)r1lo * nr, oc);
-        }
-    }
-    // u^n row k sits in ring slot k mod 3: row r + 2 is stored during step r
-    // into the slot of row r - 1, which every wave finished reading before
-    // the barrier that opens step r, so one barrier per row orders all LDS
-    // traffic (u(1) and u(2) rows are likewise read one step after they are
-    // written, into slots last read one step before).
-    int sc = r1lo % 3;                            // slot of row r
-    load_row(r1lo);
-    store_row(sc);
-    if (r1lo + 1 < nstage) {
-        load_row(r1lo + 1);
-        store_row(sc == 2 ? 0 : sc + 1);
-    }
-    if (r1lo + 2 < nstage) load_row(r1lo + 2);
-
-    // Issue priority steps down from 3 to 0 at 1/2, 3/4 and 7/8 of the march,
-    // so that waves which started later keep pace with the older waves of
-    // their SIMD (see march_strip_t).  On C2 the steps took the blocked step
-    // from 0.97x to above 1.02x of the three-launch step; with two-wave tiles
-    // these late steps measured 0.8 % faster than steps at the quarters, and
-    // steps at the thirds (never reaching 0) 1.3 % slower.
-    const int nit = k1 + 2 - r1lo;
-    const int q1 = (nit + 1) / 2, q2 = (3 * nit + 3) / 4, q3 = (7 * nit + 7) / 8;
-    for (int r = r1lo; r < k1 + 2; ++r) {
-        const int it = r - r1lo;
-        if (it == 0) __builtin_amdgcn_s_setprio(3);
-        else if (it == q1) __builtin_amdgcn_s_setprio(2);
-        else if (it == q2) __builtin_amdgcn_s_setprio(1);
-        else if (it == q3) __builtin_amdgcn_s_setprio(0);
-        lds_sync();                                   // u^n rows r, r+1 staged; u(1) row r-1, u(2) row r-2
-        const int su = sc == 2 ? 0 : sc + 1;          // slot of row r + 1
-        const int r2 = r - 1, r3 = r - 2;
-        if (r < r1hi) {
-            // ---- stage 1 at row r: u(1) = u^n + dt F(u^n)
-            const int b = r & 1;
-            double w[4][6];
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int t = 0; t < 6; ++t) w[p][t] = sn[sc][p][l + t];
-            double upR, upI;
-            if (r + 1 < nth) {
-                upR = sn[su][0][l + 3];
-                upI = sn[su][1][l + 3];
-            } else {
-                upR = A.parity * w[0][3];
-                upI = A.parity * w[1][3];
-            }
-            const double none[4] = {0, 0, 0, 0};
-            const Polar pol = load_polar(A, r);
-            pc2 = pc1;
-            pc1 = pc0;
-            pc0 = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
-            const Out o = stage(w, nbR, nbI, upR, upI, pc0, 0.0, 1.0, none, true);
-            if (!dup) {
-#pragma unroll
-                for (int p = 0; p < 4; ++p) s1[b][p][l] = o.v[p];
-            }
-            un2[0] = un1[0]; un2[1] = un1[1]; un2[2] = un1[2]; un2[3] = un1[3];
-            un1[0] = un0[0]; un1[1] = un0[1]; un1[2] = un0[2]; un1[3] = un0[3];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) un0[p] = w[p][3];
-            nbR = w[0][3];
-            nbI = w[1][3];
-            a2R = a1R; a2I = a1I; a1R = a0R; a1I = a0I;
-            a0R = o.v[0]; a0I = o.v[1];
-        } else {
-            un2[0] = un1[0]; un2[1] = un1[1]; un2[2] = un1[2]; un2[3] = un1[3];
-            un1[0] = un0[0]; un1[1] = un0[1]; un1[2] = un0[2]; un1[3] = un0[3];
-            a2R = a1R; a2I = a1I; a1R = a0R; a1I = a0I;
-            pc2 = pc1;
-            pc1 = pc0;
-        }
-        if (r2 >= r2lo && r2 < r2hi) {
-            // ---- stage 2 at row r - 1: u(2) = 3/4 u^n + 1/4 (u(1) + dt F(u(1)))
-            const int b = r2 & 1;
-            double w[4][6];
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int t = 0; t < 6; ++t) w[p][t] = s1[b][p][cl(l - 3 + t)];
-            const double dnR = r2 - 1 >= 0 ? a2R : A.parity * a1R, dnI = r2 - 1 >= 0 ? a2I : A.parity * a1I;
-            const double upR = r2 + 1 < nth ? a0R : A.parity * a1R, upI = r2 + 1 < nth ? a0I : A.parity * a1I;
-            const Out o = stage(w, dnR, dnI, upR, upI, pc1, 0.75, 0.25, un1, false);
-            if (!dup) {
-#pragma unroll
-                for (int p = 0; p < 4; ++p) s2[b][p][l] = o.v[p];
-            }
-            c3R = c2R; c3I = c2I; c2R = c1R; c2I = c1I;
-            c1R = o.v[0]; c1I = o.v[1];
-        } else {
-            c3R = c2R; c3I = c2I; c2R = c1R; c2I = c1I;
-        }
-        if (r3 >= k0 && r3 < k1) {
-            // ---- stage 3 at row r - 2: u^{n+1} = 1/3 u^n + 2/3 (u(2) + dt F(u(2)))
-            const int b = r3 & 1;
-            double w[4][6];
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int t = 0; t < 6; ++t) w[p][t] = s2[b][p][cl(l - 3 + t)];
-            const double dnR = r3 - 1 >= 0 ? c3R : A.parity * c2R, dnI = r3 - 1 >= 0 ? c3I : A.parity * c2I;
-            const double upR = r3 + 1 < nth ? c1R : A.parity * c2R, upI = r3 + 1 < nth ? c1I : A.parity * c2I;
-            const Out o = stage(w, dnR, dnI, upR, upI, pc2, 1.0 / 3.0, 2.0 / 3.0, un2, false);
-            if (out_lane) {
-                const size_t row = (size_t)r3 * nr;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) stb(outp[p] + row, oc, o.v[p]);
-            }
-        }
-        // row r + 2 into the slot of row r - 1
-        if (r + 2 < nstage) {
-            store_row(sc == 0 ? 2 : sc - 1);
-            if (r + 3 < nstage) load_row(r + 3);
-        }
-        sc = su;
     }
 }
 
@@ -1068,11 +813,10 @@ __global__ __launch_bounds__(256) void coef_dump_kernel(const double* __restrict
 
 }  // namespace
 
-int stage_grid(int weight_prec, bool first, int chart)
+static int stage_grid_query(int dev, int weight_prec, bool first, int chart)
 {
-    // resident workgroups of one stage-kernel instantiation on the current device
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    // resident workgroups of one stage-kernel instantiation
+    int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     hipError_t e = hipErrorInvalidValue;
 #define TEUK_OCC(W, C)                                                                                            \
@@ -1099,6 +843,14 @@ int stage_grid(int weight_prec, bool first, int chart)
     // per unit and 42 with 16.
     if (per_cu > 4) per_cu &= ~3;
     return cus * per_cu;
+}
+
+int stage_grid(int weight_prec, bool first, int chart)
+{
+    static ResidentCache cache[4][2][3];
+    int dev = 0;
+    if (weight_prec < 0 || weight_prec > 3 || chart < 0 || chart > 2 || hipGetDevice(&dev) != hipSuccess) return 0;
+    return cache[weight_prec][first ? 1 : 0][chart].get(dev, [&] { return stage_grid_query(dev, weight_prec, first, chart); });
 }
 
 int pipe_grid(int weight_prec)
@@ -1172,37 +924,6 @@ int launch_stage(const StageArgs& a, int stage, int weight_prec, int chart, void
     TEUK_LAUNCH(TEUK_W_BF16, kChartT4)
 #undef TEUK_LAUNCH
     if (!done) return (int)hipErrorInvalidValue;
-    return (int)hipGetLastError();
-}
-
-int blocked_grid(int weight_prec)
-{
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    hipError_t e = hipErrorInvalidValue;
-    if (weight_prec == TEUK_W_FP64)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, blocked_step_kernel<TEUK_W_FP64>, kBThreads, 0);
-    else if (weight_prec == TEUK_W_FP32)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, blocked_step_kernel<TEUK_W_FP32>, kBThreads, 0);
-    if (e != hipSuccess || per_cu < 1) return 0;
-    return cus * per_cu;
-}
-
-int launch_blocked_step(const StageArgs& a, int weight_prec, void* stream)
-{
-    if (a.nr < 1 || a.nth < 1 || a.nstrips < 1 || a.segs < 1 || a.grid != a.nstrips * a.segs ||
-        (long long)a.nstrips * kBW < a.nr || a.uk == a.out)
-        return (int)hipErrorInvalidValue;
-    (void)hipGetLastError();
-    const dim3 grid((unsigned)a.grid), block(kBThreads);
-    hipStream_t st = (hipStream_t)stream;
-    if (weight_prec == TEUK_W_FP64)
-        hipLaunchKernelGGL(blocked_step_kernel<TEUK_W_FP64>, grid, block, 0, st, a);
-    else if (weight_prec == TEUK_W_FP32)
-        hipLaunchKernelGGL(blocked_step_kernel<TEUK_W_FP32>, grid, block, 0, st, a);
-    else
-        return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }
 

@@ -30,7 +30,11 @@ namespace {
 typedef std::tuple<int, int, int, int, int, int, int, int> TuneKey;
 
 std::mutex g_tune_mutex;
-std::map<TuneKey, int> g_tuned;
+struct Tuned {
+    int workgroups;    // fastest budget of stage workgroups (of tiles, for the blocked integrator)
+    bool stages;       // SSP-RK(3,3): stage launches of that budget beat the blocked launch
+};
+std::map<TuneKey, Tuned> g_tuned;
 thread_local std::string g_tune_err;
 
 TuneKey key_of(const teuk_config& c, int device)
@@ -109,7 +113,16 @@ int tuned_workgroups(const teuk_config& c)
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     auto it = g_tuned.find(key_of(c, dev));
-    return it == g_tuned.end() ? 0 : it->second;
+    return it == g_tuned.end() ? 0 : it->second.workgroups;
+}
+
+bool tuned_stage_launches(const teuk_config& c)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lock(g_tune_mutex);
+    auto it = g_tuned.find(key_of(c, dev));
+    return it != g_tuned.end() && it->second.stages;
 }
 
 }  // namespace teuk
@@ -189,11 +202,25 @@ teuk_status teuk_tune(const teuk_config* cfg, int32_t steps, teuk_tune_info_t* o
             best_us = us;
         }
     }
+    // the way that solvers of this class step without a budget, where that is
+    // another one than stage launches (SSP-RK(3,3) by the blocked launch)
+    bool stages = false;
+    if (st == TEUK_OK && cfg->integrator == TEUK_RK_SSP33) {
+        {
+            std::lock_guard<std::mutex> lock(g_tune_mutex);
+            g_tuned.erase(key_of(*cfg, dev));
+        }
+        double us = 0.0;
+        st = time_budget(base, 0, n, stream, zeros, &us);
+        stages = us > best_us;
+        if (!stages) best_us = us;
+        default_us = us;
+    }
     (void)hipStreamDestroy(stream);
     if (st != TEUK_OK) return st;
     {
         std::lock_guard<std::mutex> lock(g_tune_mutex);
-        g_tuned[key_of(*cfg, dev)] = best;
+        g_tuned[key_of(*cfg, dev)] = Tuned{best, stages};
     }
     out->workgroups = best;
     out->segs = segs_for(best, nstrips, cfg->ntheta, !blocked);

@@ -1,0 +1,79 @@
+"""GPU: SSP-RK(3,3) stepped by the temporally blocked launch (the default where
+that kernel is built) against stage launches (a solver with a budget of stage
+workgroups): the same bits, at the edges of the 114-point tiles, from two theta
+rows up, with more and fewer strip-rows than workgroups, over runs of one, two,
+three and more steps, and where the state has to keep its buffer (graph mode, an
+odd chunk; the caller's buffer of teuk_step_noalloc).
+
+The tolerance is zero: both write every operation out in the same order."""
+import numpy as np
+import pytest
+
+import paper_2010_04760_amd as T
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def cfg(nr, nth, wp="fp64", **kw):
+    return T.make_config(s=-2, m=1, a=0.9, nr=nr, ntheta=nth, x_min=-30.0, x_max=50.0, weight_prec=wp, **kw)
+
+
+def pair(nr, nth, wp, **kw):
+    strips = -(-nr // 63)
+    a, b = T.Solver(cfg(nr, nth, wp, **kw)), T.Solver(cfg(nr, nth, wp, workgroups=4 * strips, **kw))
+    u0 = W.random_state(nr, nth, seed=nr + nth, smooth=True)
+    a.set_initial(u0)
+    b.set_initial(u0)
+    return a, b, u0
+
+
+@pytest.mark.parametrize("wp", ["fp64", "fp32"])
+@pytest.mark.parametrize("nr,nth", [(7, 2), (64, 3), (114, 2), (115, 7), (127, 5), (228, 4), (229, 33), (1000, 190),
+                                    (3000, 61)])
+def test_equals_stage_launches(nr, nth, wp):
+    a, b, _ = pair(nr, nth, wp, x_extract=5.0, extract_every=3, max_samples=8)
+    print("case fused", nr, nth, wp, flush=True)
+    for n in (1, 2, 3, 7):
+        a.step(n)
+        b.step(n)
+        np.testing.assert_array_equal(a.state(), b.state())
+    ta, wa = a.waveform()
+    tb, wb = b.waveform()
+    np.testing.assert_array_equal(ta, tb)
+    np.testing.assert_array_equal(wa, wb)
+    np.testing.assert_array_equal(a.rhs(), b.rhs())
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("chunk", [1, 3, 5, 4])
+def test_odd_graph_chunks(chunk):
+    print("case fused graph", chunk, flush=True)
+    a, b, _ = pair(300, 12, "fp64", x_extract=5.0, extract_every=1, max_samples=64)
+    a.step(1)                        # the state sits in another buffer when graph mode starts
+    b.step(1)
+    a.set_graph(chunk)
+    for n in (chunk, 2 * chunk + 1, 3, 1, 2, chunk, 7):
+        a.step(n)
+        b.step(n)
+        np.testing.assert_array_equal(a.state(), b.state())
+    np.testing.assert_array_equal(a.waveform()[1], b.waveform()[1])
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7])
+def test_noalloc_keeps_the_callers_buffer(n):
+    import torch
+
+    print("case fused noalloc", n, flush=True)
+    dt = 0.01
+    c = cfg(230, 9, dt=dt)
+    u0 = W.random_state(230, 9, seed=n, smooth=True)
+    u = torch.from_numpy(u0).cuda()
+    T.teuk_step_noalloc(c, u, n)
+    with T.Solver(cfg(230, 9, dt=dt, workgroups=8)) as sv:
+        sv.set_initial(u0)
+        sv.step(n)
+        np.testing.assert_array_equal(u.cpu().numpy(), sv.state())
