@@ -273,16 +273,17 @@ int pick_segs(const teuk_config& c, int nstrips, int weight_prec, bool first)
 
 // Whether SSP-RK(3,3) steps of c are taken by the temporally blocked launch (one
 // launch and 64 B of traffic per point-step) instead of three stage launches (256 B):
-// wherever that kernel is built -- tortoise chart, FP64 state, WENO5 with FP64 or
-// FP32 weights, second-order theta differences -- unless the caller asks for a
+// wherever that kernel is built -- FP64 state, WENO5 with FP64 or FP32 weights,
+// second-order theta differences -- unless the caller asks for a
 // budget of stage workgroups or the tuner found the stage launches faster.  The
 // results are the same to the bit.  Both measured, us a step, FP64 weights:
 // 16384 x 512 299 against 472, 8192 x 256 78.6 against 100.5, 4099 x 131 30.4
 // against 35.8, 2050 x 97 17.7 against 23.5, 1024 x 64 12.3 against 14.0, 512 x 32
-// 8.3 against 11.1, 200 x 12 8.4 against 11.0.
+// 8.0 against 11.1, 200 x 12 7.8 against 11.0; hyperboloidal chart (144 B against
+// 496 B a point-step) 16384 x 64 48.5 against 87.8, 300 x 24 8.5 against 12.4.
 bool fused_step(const teuk_config& c)
 {
-    return c.integrator == TEUK_RK_SSP33 && c.chart == TEUK_CHART_TORTOISE && c.state_prec == TEUK_S_FP64 &&
+    return c.integrator == TEUK_RK_SSP33 && c.state_prec == TEUK_S_FP64 &&
            c.scheme == TEUK_SCHEME_WENO5 && (c.weight_prec == TEUK_W_FP64 || c.weight_prec == TEUK_W_FP32) &&
            c.theta_order != 4 && c.workgroups == 0 && !tuned_stage_launches(c);
 }
@@ -300,7 +301,7 @@ bool blocked_shape(const teuk_config& c, int budget, int* strips, int* grid)
         g = std::min((long long)budget / *strips, (long long)c.ntheta);
         g = *strips * (g < 1 ? 1 : g);
     } else {
-        g = blocked_grid(c.weight_prec);
+        g = blocked_grid(c.weight_prec, c.chart);
     }
     *grid = (int)std::min(std::min(g, rows), (1LL << 31) - 1);
     return *grid > 0;
@@ -735,7 +736,7 @@ static int blocked_step_once(teuk_solver* h, hipStream_t stream)
     a.uk = h->u[0];
     a.un = h->u[0];
     a.out = h->u[1];
-    const int e = launch_blocked_step(a, h->cfg.weight_prec, h->cfg.integrator == TEUK_RK_SSP33_BLOCKED, stream);
+    const int e = launch_blocked_step(a, h->cfg.weight_prec, h->cfg.chart, h->cfg.integrator == TEUK_RK_SSP33_BLOCKED, stream);
     if (!e) std::swap(h->u[0], h->u[1]);             // u^{n+1} is the new state buffer
     return e;
 }
@@ -1844,7 +1845,7 @@ extern "C" teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int6
             if ((nsteps & 1) && n == 1) to = u2;
             a.uk = a.un = at;
             a.out = to;
-            e = launch_blocked_step(a, cfg->weight_prec, false, st);
+            e = launch_blocked_step(a, cfg->weight_prec, cfg->chart, false, st);
             at = to;
         }
         if (e) return fail(nullptr, TEUK_ERR_DEVICE, std::string("blocked step launch: ") + hipGetErrorString((hipError_t)e));

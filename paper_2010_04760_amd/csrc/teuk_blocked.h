@@ -58,9 +58,17 @@ static_assert(kBLead + kBW + kBLead + 1 == kBPts, "tile geometry");
 // operation; the per-point coefficients of a row are built once, by stage 1, and
 // reused by stages 2 and 3 (a lane keeps its radial point through all three).
 //
-// Bound: FP64 VALU issue (HBM sees 75 B per point-step).  The march is unrolled
-// by three so that the values rolling over three rows (coefficients, u^n) and the
-// three-slot rings keep fixed registers and addresses.
+// Bound: FP64 VALU issue (HBM sees 75 B per point-step; 2.92e7 wave instructions a
+// step of 8192 x 256, the SIMDs issuing them 80 % of the time at the 1.8 GHz that
+// this load leaves).  The march is unrolled by three so that the values rolling
+// over three rows (coefficients, u^n) and the three-slot rings keep fixed registers
+// and addresses: with the copies, one-ended marches and 1024 one-tile workgroups
+// of the form before it the step took 3.57e7 instructions and 87.5 us, now 77.5.
+//
+// Hyperboloidal chart: the ten coefficients of a point are read once a step (loaded
+// one row ahead) instead of once a stage, 144 B a point-step against 496, and a
+// row's fluxes are taken on the side of its own speed: 16384 x 64 in 48.5 us where
+// three launches of the stage kernel take 87.8 at 5.9 TB/s.
 constexpr int kBS1 = 2 * 4 * 3 * kBStage;            // u(1) rings
 constexpr int kBS2 = 2 * 4 * 3 * kBPts;              // u(2) rings, from the u(1) rings on
 
@@ -92,8 +100,8 @@ __device__ __forceinline__ void row_put(double* row, unsigned off, double v)
     *(__attribute__((address_space(1))) double*)(scalar(row) + off) = v;
 }
 
-template <int WP, bool kBtFirst>
-__global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
+template <int WP, bool kBtFirst, bool kHyp>
+__global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A, unsigned share, unsigned extra)
 {
     // per half and plane, three-row rings of u^n (position s = point p0 - 3 + s) and
     // of u(1) and u(2) (one value per point).  The planes are more than 255 values
@@ -107,22 +115,23 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
     const bool dup = tid == kWave - 1;                    // wave 0's copy of point 63
     const int nr = A.nr, nth = A.nth;
     const long long P = A.plane;
-    const WenoK K = weno_consts(A.eps);
+    constexpr int W = kHyp && WP == TEUK_W_FP64 ? kWeno64H : WP;
+    const auto K = weno_consts_for<W>(A.eps);
     const double* ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
     double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
     const int dir = half ? 1 : -1;
     const double ih1 = half ? A.ih1 : -A.ih1;
 
-    const int G = (int)gridDim.x;
-    const int rank = xcd_rank((int)blockIdx.x, G);
-    const long long total = (long long)A.nstrips * nth;
-    long long at = total * rank / G;
-    const long long end = total * (rank + 1) / G;
+    // strip-rows [at, end): share, and one more for the first `extra` ranks (at most
+    // 2^34 / 114 + 2^16 strip-rows, so 32 bits)
+    const unsigned rank = (unsigned)xcd_rank((int)blockIdx.x, (int)gridDim.x);
+    unsigned at = rank * share + min(rank, extra);
+    const unsigned end = at + share + (rank < extra ? 1u : 0u);
     while (at < end) {                                    // uniform over the workgroup
-        const int strip = (int)(at / nth);
-        const int k0 = (int)(at - (long long)strip * nth);
-        const int k1 = (int)(end - at < nth - k0 ? k0 + (end - at) : nth);
-        at += k1 - k0;
+        const int strip = (int)(at / (unsigned)nth);
+        const int k0 = (int)(at - (unsigned)strip * (unsigned)nth);
+        const int k1 = min(k0 + (int)(end - at), nth);
+        at += (unsigned)(k1 - k0);
         // the middle row, with at least one grid row on either side of it
         int kb = (k0 + k1) >> 1;
         if (kb == 0) kb = 1;
@@ -148,86 +157,149 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
         const LdsDouble across = lds_at(lds + kBS1 + (half ^ 1) * 4 * 3 * kBPts + l);
         const LdsDouble rows = lds_at(lds + half * 4 * 3 * kBStage + l), put = lds_at(lds + half * 4 * 3 * kBStage + tid);
         const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
-        const Radial rt = load_radial(A, oc);
+        Radial rt;
+        if constexpr (!kHyp) rt = load_radial(A, oc);
 
-        double xa[4], xb[4] = {0, 0, 0, 0};
-        auto load_row = [&](int i) {
+        struct Row { double a[4], b[4]; };
+        auto load_row = [&](Row& x, int i) {
             const size_t row = (size_t)(first + dir * i) * nr;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) xa[p] = row_get(ukp[p] + row, oa);
+            for (int p = 0; p < 4; ++p) x.a[p] = row_get(ukp[p] + row, oa);
             if (halo) {
 #pragma unroll
-                for (int p = 0; p < 4; ++p) xb[p] = row_get(ukp[p] + row, ob);
+                for (int p = 0; p < 4; ++p) x.b[p] = row_get(ukp[p] + row, ob);
             }
         };
-        auto store_row = [&](int b) {
+        auto store_row = [&](const Row& x, int b) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage] = xa[p];
+            for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage] = x.a[p];
             if (halo) {
 #pragma unroll
-                for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage + kBHalf] = xb[p];
+                for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage + kBHalf] = x.b[p];
             }
         };
 
+        // The point's factors on one row.
+        struct Point {
+            PointCoef t;             // tortoise chart, built by stage 1
+            double hc[kNCH];         // hyperboloidal chart, from the table
+        };
         // One stage at one row for this lane, from the window w[p][t] (input of plane p
         // at j - 3 + t): the fluxes first, in the block that reads the window, so that
         // a plane's flux starts as its values arrive and covers the reads of the next;
         // then the rest with the input Phi at the own point on the rows ahead and behind.
-        struct Fluxes { Flux f[4]; double fn[4]; };
-        auto fluxes = [&](const double (&w)[4][6]) {
-            Fluxes r;
+        // (hyperboloidal chart: each plane on the side of its own speed at the point, both
+        // sides in a wave whose lanes disagree; c holds the row's coefficients)
+        struct Diffs { double d[4]; };
+        auto fluxes = [&](auto read, double (&w)[4][6], const Point& c) {
+            Diffs r;
+            if constexpr (!kHyp) {
+                Flux f[4];
+                double fn[4];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) r.f[p] = Weno<WP>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
+                for (int p = 0; p < 4; ++p)
 #pragma unroll
-            for (int p = 2; p < 4; ++p) r.f[p] = Weno<WP>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
+                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = read(p, t);
 #pragma unroll
-            for (int p = 0; p < 4; ++p) r.fn[p] = next_lane(r.f[p].y);
+                for (int p = 0; p < 2; ++p) f[p] = Weno<W>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
+#pragma unroll
+                for (int p = 2; p < 4; ++p) f[p] = Weno<W>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
+#pragma unroll
+                for (int p = 0; p < 4; ++p) fn[p] = next_lane(f[p].y);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) r.d[p] = plus_diff<W>(K, f[p], fn[p]);
+#pragma unroll
+                for (int p = 2; p < 4; ++p) r.d[p] = minus_diff<W>(K, f[p], fn[p]);
+            } else {
+                const bool up[2] = {c.hc[kHLam1] >= 0.0, c.hc[kHLam2] >= 0.0};
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    r.d[2 * q] = r.d[2 * q + 1] = 0.0;
+                    if (__any(up[q])) {
+#pragma unroll
+                        for (int p = 2 * q; p < 2 * q + 2; ++p) {
+#pragma unroll
+                            for (int t = 0; t < 5; ++t) w[p][t] = read(p, t);
+                            const Flux f = Weno<W>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
+                            const double d = plus_diff<W>(K, f, next_lane(f.y));
+                            if (up[q]) r.d[p] = d;
+                        }
+                    }
+                    if (__any(!up[q])) {
+#pragma unroll
+                        for (int p = 2 * q; p < 2 * q + 2; ++p) {
+#pragma unroll
+                            for (int t = 1; t < 6; ++t) w[p][t] = read(p, t);
+                            const Flux f = Weno<W>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
+                            const double d = minus_diff<W>(K, f, next_lane(f.y));
+                            if (!up[q]) r.d[p] = d;
+                        }
+                    }
+                    r.d[2 * q] *= A.inv6dx;
+                    r.d[2 * q + 1] *= A.inv6dx;
+                }
+            }
             return r;
         };
-        auto finish = [&](const Fluxes& f, const double (&w)[4][6], double ahR, double ahI, double bhR, double bhI,
-                          const PointCoef& c) {
-            // second differences as (up - 2 own) + down; a branch, as selects would
-            // cost sixteen instructions
-            Theta xR, xI;
-            if (half) {
-                xR = theta2(w[0][3], ahR, bhR);
-                xI = theta2(w[1][3], ahI, bhI);
-                asm volatile("" : "+v"(xR.d2));
+        auto finish = [&](const Diffs& r, const double (&w)[4][6], double ahR, double ahI, double bhR, double bhI,
+                          const Point& c) {
+            Four F;
+            if constexpr (kHyp) {
+                // symmetric in the rows ahead and behind but for the sign of ih1
+                F = rhs_h(c.hc, ih1, A.ih2, r.d[0], r.d[1], r.d[2], r.d[3], w[0][3], w[1][3], w[2][3], w[3][3], ahR, ahI,
+                          bhR, bhI);
             } else {
-                xR = theta2(w[0][3], bhR, ahR);
-                xI = theta2(w[1][3], bhI, ahI);
-                asm volatile("" : "+v"(xI.d2));
+                // second differences as (up - 2 own) + down; a branch, as selects would
+                // cost sixteen instructions
+                Theta xR, xI;
+                if (half) {
+                    xR = theta2(w[0][3], ahR, bhR);
+                    xI = theta2(w[1][3], ahI, bhI);
+                    asm volatile("" : "+v"(xR.d2));
+                } else {
+                    xR = theta2(w[0][3], bhR, ahR);
+                    xI = theta2(w[1][3], bhI, ahI);
+                    asm volatile("" : "+v"(xI.d2));
+                }
+                xR.d1 = ahR - bhR;
+                xI.d1 = ahI - bhI;
+                F = rhs_t<kBtFirst>(A, ih1, c.t, r.d[0], r.d[1], r.d[2], r.d[3], w[0][3], w[1][3], w[2][3], w[3][3], xR, xI);
             }
-            xR.d1 = ahR - bhR;
-            xI.d1 = ahI - bhI;
-            const Four F = rhs_t<kBtFirst>(A, ih1, c, plus_diff<WP>(K, f.f[0], f.fn[0]), plus_diff<WP>(K, f.f[1], f.fn[1]),
-                                           minus_diff<WP>(K, f.f[2], f.fn[2]), minus_diff<WP>(K, f.f[3], f.fn[3]), w[0][3],
-                                           w[1][3], w[2][3], w[3][3], xR, xI);
             Four v;
 #pragma unroll
             for (int p = 0; p < 4; ++p) v.v[p] = euler(w[p][3], A.dt, F.v[p]);
             return v;
         };
 
-        PointCoef pc[3];
+        Point pc[3];
         double un[3][4];                     // u^n at the own point, rows i, i - 1, i - 2
         double b0R, b0I;                     // Phi of u^n on row i - 1
         double a1R = 0, a1I = 0;             // Phi of u(1) on row i (its parity ghost beyond a pole)
         double b1R = 0, b1I = 0;             // ... on row i - 2
         double a2R = 0, a2I = 0;             // Phi of u(2) on row i - 1
         double b2R = 0, b2I = 0;             // ... on row i - 3
+        // hyperboloidal chart: the coefficients of the next row, loaded one row ahead
+        double hn[kNCH];
+        auto load_coefs = [&](int i) {
+            const double* c = A.ctab + (size_t)(first + dir * i) * nr;
+#pragma unroll
+            for (int q2 = 0; q2 < kNCH; ++q2) hn[q2] = row_get(c + (size_t)q2 * P, oc);
+        };
+        if constexpr (kHyp) load_coefs(0);
+        // every load of the first rows is under way before the first is waited for (rows
+        // past the last staged one are read again and not stored)
+        Row ahead;
         {
+            Row r0, r1;
+            load_row(r0, 0);
+            load_row(r1, min(1, NS - 1));
+            load_row(ahead, min(2, NS - 1));
             const size_t row = (size_t)(first - dir) * nr;
-            b0R = ldb(ukp[0] + row, oc);
-            b0I = ldb(ukp[1] + row, oc);
+            b0R = row_get(ukp[0] + row, oc);
+            b0I = row_get(ukp[1] + row, oc);
+            store_row(r0, 0);
+            if (NS > 1) store_row(r1, 1);
         }
-        load_row(0);
-        store_row(0);
-        if (NS > 1) {
-            load_row(1);
-            store_row(1);
-        }
-        if (NS > 2) load_row(2);
 
         auto step = [&](auto phase, int i) {
             constexpr int c0 = decltype(phase)::value, c1 = (c0 + 1) % 3, c2 = (c0 + 2) % 3;
@@ -235,14 +307,16 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
             if (i < N1) {
                 // ---- stage 1 at row i: u(1) = u^n + dt F(u^n)
                 double w[4][6];
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-#pragma unroll
-                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = lds_get(rows, (p * 3 + c0) * kBStage + t);
                 double ahR = lds_get(rows, c1 * kBStage + 3), ahI = lds_get(rows, (3 + c1) * kBStage + 3);
-                const Polar pol = load_polar(A, first + dir * i);
-                const Fluxes f = fluxes(w);
-                pc[c0] = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
+                Polar pol;
+                if constexpr (!kHyp) pol = load_polar(A, first + dir * i);
+                if constexpr (kHyp) {
+#pragma unroll
+                    for (int q2 = 0; q2 < kNCH; ++q2) pc[c0].hc[q2] = hn[q2];
+                    if (i + 1 < N1) load_coefs(i + 1);
+                }
+                const Diffs f = fluxes([&](int p, int t) { return lds_get(rows, (p * 3 + c0) * kBStage + t); }, w, pc[c0]);
+                if constexpr (!kHyp) pc[c0].t = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
                 if (i + 1 >= lim) {          // a ghost row (the ring holds an older one)
                     ahR = A.parity * w[0][3];
                     ahI = A.parity * w[1][3];
@@ -269,11 +343,7 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
                     b1I = lds_get(across, (3 + c2) * kBPts);
                 }
                 double w[4][6];
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-#pragma unroll
-                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = lds_get(q[t], (p * 3 + c2) * kBPts);
-                const Fluxes f = fluxes(w);
+                const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], (p * 3 + c2) * kBPts); }, w, pc[c2]);
                 const Four o = finish(f, w, a1R, a1I, b1R, b1I, pc[c2]);
                 Four u2;
 #pragma unroll
@@ -297,11 +367,7 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
                     b2I = lds_get(across, kBS2 + (3 + c1) * kBPts);
                 }
                 double w[4][6];
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-#pragma unroll
-                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = lds_get(q[t], kBS2 + (p * 3 + c1) * kBPts);
-                const Fluxes f = fluxes(w);
+                const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], kBS2 + (p * 3 + c1) * kBPts); }, w, pc[c1]);
                 const Four o = finish(f, w, a2R, a2I, b2R, b2I, pc[c1]);
                 if (out_lane) {
                     const size_t row = (size_t)(first + dir * (i - 2)) * nr;
@@ -313,8 +379,8 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
             }
             // row i + 2 into the slot of row i - 1
             if (i + 2 < NS) {
-                store_row(c2);
-                if (i + 3 < NS) load_row(i + 3);
+                store_row(ahead, c2);
+                if (i + 3 < NS) load_row(ahead, i + 3);
             }
         };
         int i = 0;
@@ -332,38 +398,47 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A)
 
 }  // namespace
 
-int blocked_grid(int weight_prec)
+int blocked_grid(int weight_prec, int chart)
 {
-    static ResidentCache cache[2];
+    static ResidentCache cache[2][2];
     int dev = 0;
-    if ((weight_prec != TEUK_W_FP64 && weight_prec != TEUK_W_FP32) || hipGetDevice(&dev) != hipSuccess) return 0;
-    return cache[weight_prec == TEUK_W_FP32].get(dev, [&] {
+    const bool f32 = weight_prec == TEUK_W_FP32, hyp = chart == TEUK_CHART_HYPERBOLOIDAL;
+    if ((weight_prec != TEUK_W_FP64 && !f32) || (chart != TEUK_CHART_TORTOISE && !hyp) || hipGetDevice(&dev) != hipSuccess)
+        return 0;
+    return cache[f32][hyp].get(dev, [&] {
         int cus = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        const hipError_t e =
-            weight_prec == TEUK_W_FP64
-                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, blocked_step_kernel<TEUK_W_FP64, true>, kBThreads, 0)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, blocked_step_kernel<TEUK_W_FP32, false>, kBThreads, 0);
+        const void* fn = hyp ? (f32 ? (const void*)blocked_step_kernel<TEUK_W_FP32, false, true>
+                                    : (const void*)blocked_step_kernel<TEUK_W_FP64, false, true>)
+                             : (f32 ? (const void*)blocked_step_kernel<TEUK_W_FP32, false, false>
+                                    : (const void*)blocked_step_kernel<TEUK_W_FP64, true, false>);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBThreads, 0);
         return e != hipSuccess || per_cu < 1 ? 0 : cus * per_cu;
     });
 }
 
-int launch_blocked_step(const StageArgs& a, int weight_prec, bool own_order, void* stream)
+int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own_order, void* stream)
 {
     if (a.nr < 1 || a.nth < 2 || a.nstrips < 1 || a.grid < 1 || (long long)a.grid > (long long)a.nstrips * a.nth ||
-        (long long)a.nstrips * kBW < a.nr || a.uk == a.out)
+        (long long)a.nstrips * kBW < a.nr || (long long)a.nstrips * a.nth > (1LL << 31) - 1 || a.uk == a.out)
         return (int)hipErrorInvalidValue;
     (void)hipGetLastError();
     const dim3 grid((unsigned)a.grid), block(kBThreads);
     hipStream_t st = (hipStream_t)stream;
-    if (weight_prec == TEUK_W_FP64 && own_order)
-        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP64, false>), grid, block, 0, st, a);
-    else if (weight_prec == TEUK_W_FP64)
-        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP64, true>), grid, block, 0, st, a);
-    else if (weight_prec == TEUK_W_FP32)
-        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP32, false>), grid, block, 0, st, a);
-    else
-        return (int)hipErrorInvalidValue;
+    const unsigned rows = (unsigned)((long long)a.nstrips * a.nth), g = (unsigned)a.grid;
+    bool done = false;
+#define TEUK_BLAUNCH(W, F, H)                                                                                         \
+    if (!done && weight_prec == W && (chart == TEUK_CHART_HYPERBOLOIDAL) == H && (W != TEUK_W_FP64 || H || own_order != F)) { \
+        hipLaunchKernelGGL((blocked_step_kernel<W, F, H>), grid, block, 0, st, a, rows / g, rows % g);                \
+        done = true;                                                                                                  \
+    }
+    TEUK_BLAUNCH(TEUK_W_FP64, true, false)
+    TEUK_BLAUNCH(TEUK_W_FP64, false, false)
+    TEUK_BLAUNCH(TEUK_W_FP32, false, false)
+    TEUK_BLAUNCH(TEUK_W_FP64, false, true)
+    TEUK_BLAUNCH(TEUK_W_FP32, false, true)
+#undef TEUK_BLAUNCH
+    if (!done) return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }
 

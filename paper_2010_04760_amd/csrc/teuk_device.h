@@ -128,6 +128,48 @@ struct Weno<TEUK_W_FP64> {
     }
 };
 
+// FP64 weights in the hyperboloidal chart, on the first differences
+// g_i = v_{i+1} - v_i, again by identities of the printed formulas:
+//  * (3/4) IS_0 = (g0 - 11/8 g1)^2 + 39/64 g1^2,  (3/4) IS_1 = (g1 - 5/8 g2)^2 + 39/64 g2^2,
+//    (3/4) IS_2 = (g3 - 11/8 g2)^2 + 39/64 g2^2: with eps scaled by 3/4 as well, one
+//    fma for each linear form a_k, one for each square and the term in g1 or g2
+//    shared; the common factor of s_k = (3/4)(eps + IS_k) cancels in omega;
+//  * D = t1 t2 + 6 t0 (t2 + t1/2), t_k = s_k^2;
+//  * 6 (f - v2) = C + omega_0 (A - C) + omega_1 (B - C) with A = 5 g1 - 2 g0,
+//    B = g1 + 2 g2, C = 4 g2 - g3, whose differences reuse the forms:
+//    B - C = a1 + a2, A - C = a2 - 2 a0 + 9/4 g1 - 21/8 g2;
+//  * the flux difference takes its 6 v2 part from the field difference directly
+//    (plus_diff / minus_diff), so that no large value is formed and cancelled.
+// 33 operations and one reciprocal a flux against the 42 of the form above.  (The
+// tortoise chart keeps that form: its fields are sampled far outside a packet,
+// where only the last bits of larger neighbours are left and any other order of
+// operations would show.)
+constexpr int kWeno64H = 16;
+
+struct WenoKH {
+    double e4, k0, k1, kh, k6, ka, kb;
+};
+
+template <>
+struct Weno<kWeno64H> {
+    static constexpr bool kRelative = true;
+    __device__ __forceinline__ static Flux flux(double v0, double v1, double v2, double v3, double v4, const WenoKH& K)
+    {
+#pragma clang fp contract(off)
+        const double g0 = v1 - v0, g1 = v2 - v1, g2 = v3 - v2, g3 = v4 - v3;
+        const double h1 = fmad(K.kh * g1, g1, K.e4), h2 = fmad(K.kh * g2, g2, K.e4);
+        const double a0 = fmad(K.k0, g1, g0), a1 = fmad(K.k1, g2, g1), a2 = fmad(K.k0, g2, g3);
+        const double s0 = fmad(a0, a0, h1), s1 = fmad(a1, a1, h2), s2 = fmad(a2, a2, h2);
+        const double t0 = s0 * s0, t1 = s1 * s1, t2 = s2 * s2;
+        const double z = K.k6 * t0;
+        const double n0 = t1 * t2, n1 = z * t2;
+        const double inv = rcp64(fmad(z, fmad(0.5, t1, t2), n0));
+        const double ac = fmad(K.kb, g2, fmad(K.ka, g1, fmad(-2.0, a0, a2)));
+        const double x = fmad(n1, a1 + a2, n0 * ac);
+        return {fmad(inv, x, fmad(4.0, g2, -g3)), g1, g2};
+    }
+};
+
 // ---------------------------------------------------------------- reduced-precision weights
 // Sec. 3.1.3: the smoothness indicators and nonlinear weights are computed in a
 // lower precision and the weights are made to sum to one in FP64.  Here the six
@@ -275,17 +317,29 @@ struct Weno<TEUK_W_FP16> : WenoLow<LowF16, true> {};
 template <>
 struct Weno<TEUK_W_BF16> : WenoLow<LowBF16, true> {};
 
+template <int WP>
+__device__ __forceinline__ auto weno_consts_for(double eps)
+{
+    if constexpr (WP == kWeno64H) {
+        WenoKH K{0.75 * eps, -1.375, -0.625, 39.0 / 64.0, 6.0, 2.25, -2.625};
+        asm("" : "+s"(K.k0), "+s"(K.k1), "+s"(K.kh), "+s"(K.k6), "+s"(K.ka), "+s"(K.kb));
+        return K;
+    } else {
+        return weno_consts(eps);
+    }
+}
+
 // 6 dx times the derivative at j from this lane's flux at j - 1/2 and the next
 // lane's flux value `yn` at j + 1/2: of f^+ fluxes (v2 = f_{j-1}, so the next
 // lane's v2 is g2 further), and of f^- fluxes (v2 = f_j, mirrored).
-template <int WP>
-__device__ __forceinline__ double plus_diff(const WenoK& K, const Flux& f, double yn)
+template <int WP, class Consts>
+__device__ __forceinline__ double plus_diff(const Consts& K, const Flux& f, double yn)
 {
 #pragma clang fp contract(off)
     return Weno<WP>::kRelative ? fmad(K.k6, f.g2, yn - f.y) : yn - f.y;
 }
-template <int WP>
-__device__ __forceinline__ double minus_diff(const WenoK& K, const Flux& f, double yn)
+template <int WP, class Consts>
+__device__ __forceinline__ double minus_diff(const Consts& K, const Flux& f, double yn)
 {
 #pragma clang fp contract(off)
     return Weno<WP>::kRelative ? fmad(-K.k6, f.g1, yn - f.y) : yn - f.y;

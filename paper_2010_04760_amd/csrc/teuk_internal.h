@@ -129,16 +129,16 @@ int launch_dt_bound(const double* rtab, const double* ttab, const double* ctab, 
 int launch_guard(const double* u, long long n, int* flag, void* stream);
 int launch_coef_dump(const double* rtab, const double* ttab, const double* ctab, int nr, int nth, double* out,
                      void* stream);
-// Temporal blocking: one whole SSP-RK(3,3) step (tortoise chart, FP64 or FP32
+// Temporal blocking: one whole SSP-RK(3,3) step (either chart, FP64 or FP32
 // weights) from a.uk into a.out (distinct buffers) by a.grid workgroups, each an
 // equal share of the rows of the a.nstrips strips of kBlockedPoints radial points
 // (a.grid <= a.nstrips * a.nth).  own_order: the order of one sum that
 // TEUK_RK_SSP33_BLOCKED results have had, else the stage kernels'.
-// blocked_grid(weight_prec) is the resident workgroup count (0 for a precision
+// blocked_grid(weight_prec, chart) is the resident workgroup count (0 for a precision
 // without a blocked kernel).
 constexpr int kBlockedPoints = 114;
-int blocked_grid(int weight_prec);
-int launch_blocked_step(const StageArgs& a, int weight_prec, bool own_order, void* stream);
+int blocked_grid(int weight_prec, int chart);
+int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own_order, void* stream);
 // Pipelined steps (tortoise chart, FP64 state, WENO5): nsteps SSP-RK(3,3)
 // steps in one cooperative launch of `grid` workgroups (at most pipe_grid(),
 // the resident count, and at most the tile count st[0].nstrips * st[0].segs);

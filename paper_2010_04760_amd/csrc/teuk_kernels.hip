@@ -193,7 +193,8 @@ __device__ __forceinline__ void march_strip_h(const StageArgs& A, double (*s)[4]
     const double* __restrict__ ukp[4] = {A.uk, A.uk + P, A.uk + 2 * P, A.uk + 3 * P};
     const double* unp[4] = {A.un, A.un + P, A.un + 2 * P, A.un + 3 * P};   // read where reads_un<kMode>()
 
-    const WenoK K = weno_consts(A.eps);
+    constexpr int HW = WP == TEUK_W_FP64 ? kWeno64H : WP;
+    const auto K = weno_consts_for<HW>(A.eps);
 
     const int n = k1 - k0;
     const int first = dir > 0 ? k0 : k1 - 1;
@@ -267,13 +268,13 @@ __device__ __forceinline__ void march_strip_h(const StageArgs& A, double (*s)[4]
             auto deriv = [&](int p, bool up, bool any_up, bool any_dn) {
                 double d = 0.0;
                 if (any_up) {
-                    const Flux f = Weno<WP>::flux(s[b][p][l], s[b][p][l + 1], s[b][p][l + 2], s[b][p][l + 3], s[b][p][l + 4], K);
-                    const double dp = plus_diff<WP>(K, f, next_lane(f.y));
+                    const Flux f = Weno<HW>::flux(s[b][p][l], s[b][p][l + 1], s[b][p][l + 2], s[b][p][l + 3], s[b][p][l + 4], K);
+                    const double dp = plus_diff<HW>(K, f, next_lane(f.y));
                     if (up) d = dp;
                 }
                 if (any_dn) {
-                    const Flux f = Weno<WP>::flux(s[b][p][l + 5], s[b][p][l + 4], s[b][p][l + 3], s[b][p][l + 2], s[b][p][l + 1], K);
-                    const double dm = minus_diff<WP>(K, f, next_lane(f.y));
+                    const Flux f = Weno<HW>::flux(s[b][p][l + 5], s[b][p][l + 4], s[b][p][l + 3], s[b][p][l + 2], s[b][p][l + 1], K);
+                    const double dm = minus_diff<HW>(K, f, next_lane(f.y));
                     if (!up) d = dm;
                 }
                 return d * A.inv6dx;

@@ -47,6 +47,26 @@ def test_equals_stage_launches(nr, nth, wp):
     b.close()
 
 
+@pytest.mark.parametrize("wp", ["fp64", "fp32"])
+@pytest.mark.parametrize("nr,nth,a,x_min", [(7, 3, 1.0, 20 / 21), (115, 2, 1.0, 20 / 21), (300, 25, 0.8, 1.2),
+                                            (901, 64, 0.8, 1.2)])
+def test_hyperboloidal_equals_stage_launches(nr, nth, a, x_min, wp):
+    """x_min = 1.2 at a = 0.8 reaches inside the horizon: both upwind sides in one wave."""
+    print("case fused chart H", nr, nth, a, wp, flush=True)
+    kw = dict(s=-2, m=1, a=a, nr=nr, ntheta=nth, x_min=x_min, x_max=19.0, chart="H", weight_prec=wp, x_extract=5.0,
+              extract_every=2, max_samples=8)
+    u0 = W.random_state(nr, nth, seed=nr, smooth=True)
+    with T.Solver(T.make_config(**kw)) as x, T.Solver(T.make_config(workgroups=2 * (-(-nr // 63)), **kw)) as y:
+        x.set_initial(u0)
+        y.set_initial(u0)
+        for n in (1, 2, 5):
+            x.step(n)
+            y.step(n)
+            np.testing.assert_array_equal(x.state(), y.state())
+        for p, q in zip(x.horizon(), y.horizon()):
+            np.testing.assert_array_equal(p, q)
+
+
 @pytest.mark.parametrize("chunk", [1, 3, 5, 4])
 def test_odd_graph_chunks(chunk):
     print("case fused graph", chunk, flush=True)
