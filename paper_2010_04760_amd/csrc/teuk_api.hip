@@ -104,6 +104,12 @@ struct GroupBlock {
     size_t start = 0;
     int grid = 0;
     bool solo = false;   // members stepped by their own single-solve launches
+    // Stepped by one temporally blocked launch a step over all members (which moves
+    // every member's state to its other buffer: `turn` says which of the two
+    // descriptor sets reads the current ones).
+    bool fused = false;
+    int turn = 0;
+    long long rows = 0;  // strip-rows of that launch
     long long solo_wg = 0;   // their stage-2/3 workgroups, summed over the members
 };
 
@@ -115,18 +121,21 @@ struct teuk_group {
     int rows = 8;                                   // theta rows per tile (target)
     long long block_bytes = kGroupBlockBytes;       // cache-block size (member footprints)
     std::vector<teuk_solver*> mem;                  // insertion order
-    StageArgs* d_args = nullptr;                    // [3][cap]: per stage, members by weight precision
+    StageArgs* d_args = nullptr;                    // [5][cap]: per stage, members by weight precision; then the
+                                                    // blocked step from u[0] to u[1] and back
     long long* d_start = nullptr;                   // [2 cap + 2]: each block's tile prefix sums, from 0
+    unsigned* d_rows = nullptr;                     // [2 cap + 2]: each block's strip-row prefix sums, from 0
     std::vector<StageArgs> h_args;
     std::vector<long long> h_start;
+    std::vector<unsigned> h_rows;
     std::vector<teuk_solver*> order;                // members in class order, block by block
     std::vector<GroupBlock> blocks;                 // class c = weight_prec + 4 * chart
     long long points = 0;
     // graph mode: each cache block replays a captured graph of graph_chunk steps
     int graph_chunk = 0;                            // 0: off
     hipStream_t cap_stream = nullptr;
-    std::vector<hipGraphExec_t> gexec;              // per block, or null
-    std::vector<std::vector<long long>> gphase;     // per block: its members' steps % extract_every at capture
+    std::vector<hipGraphExec_t> gexec;              // per block and turn, or null
+    std::vector<std::vector<long long>> gphase;     // the same: its members' steps % extract_every at capture
     std::string err;
 };
 
@@ -758,8 +767,11 @@ static int run_stage(const teuk_solver* h, const StageArgs& a, int stage)
 static int rk3_step(teuk_solver* h, StageArgs& a, int64_t k, int64_t n, bool keep, hipStream_t stream)
 {
     if (h->fused && !(keep && n == 1)) {
-        if (keep && (n & 1) && (k == 1 || k == 2)) std::swap(h->u[1], h->u[2]);
-        return blocked_step_once(h, stream);
+        const bool around = keep && (n & 1) && (k == 1 || k == 2);
+        if (around) std::swap(h->u[1], h->u[2]);
+        const int e = blocked_step_once(h, stream);
+        if (around && k == 2) std::swap(h->u[1], h->u[2]);   // the other two buffers back in their places as well
+        return e;
     }
     int e = 0;
     for (int stage = 1; stage <= 3 && !e; ++stage) {
@@ -1205,6 +1217,17 @@ static int group_segs(int nth, int rows)
     return segs;
 }
 
+// Whether cache blocks of class c (weight precision + 4 launch class) step by the
+// temporally blocked launch over all members (as fused_step for one solve: FP64 or
+// FP32 weights, either chart, second-order theta differences).  24 solves of 513 to
+// 2977 by 26 to 95 points, FP64 and FP32 weights: 173 us a step in six stage
+// launches, 126 in two blocked ones.
+static bool fused_class(int c)
+{
+    const int wp = c % 4, chart = c / 4;
+    return (wp == TEUK_W_FP64 || wp == TEUK_W_FP32) && (chart == TEUK_CHART_TORTOISE || chart == TEUK_CHART_HYPERBOLOIDAL);
+}
+
 // Rebuild and upload the members' stage descriptors and tile prefix sums, cut
 // each (precision, chart) class into cache blocks and size each block's launch.
 // The caller has synchronised the group's stream.
@@ -1231,6 +1254,7 @@ static teuk_status group_upload(teuk_group* g)
             blk.first = idx;
             blk.start = soff;
             g->h_start[soff] = 0;
+            g->h_rows[soff] = 0;
             bytes = 0;
             all_fill = true;
             blocked = false;
@@ -1238,6 +1262,7 @@ static teuk_status group_upload(teuk_group* g)
         auto close_block = [&]() {
             blk.grid = (int)(g->workgroups > 0 && g->workgroups < blk.tiles ? g->workgroups : blk.tiles);
             blk.solo = blocked || (TEUK_GROUP_SOLO && all_fill && g->workgroups == 0);
+            blk.fused = !blocked && g->workgroups == 0 && blk.rows <= (1LL << 31) - 1 && fused_class(c);
             g->blocks.push_back(blk);
             soff += (size_t)blk.n + 1;
         };
@@ -1261,8 +1286,11 @@ static teuk_status group_upload(teuk_group* g)
             blk.units += (long long)h->nstrips * h->cfg.ntheta;
             if (blk.tiles > (1LL << 31) - 1)
                 return gfail(g, TEUK_ERR_CAPACITY, "group block too large for one launch (2^31 - 1 tiles)");
+            const int bstrips = (h->cfg.nr + kBlockedPoints - 1) / kBlockedPoints;
+            blk.rows += (long long)bstrips * h->cfg.ntheta;
             ++blk.n;
             g->h_start[soff + blk.n] = blk.tiles;
+            g->h_rows[soff + blk.n] = (unsigned)blk.rows;
             bytes += (long long)h->bytes;
             // stage 1: u1 = u + dt F(u)
             a.uk = a.un = h->u[0]; a.out = h->u[1]; a.ca = 0.0; a.cb = 1.0;
@@ -1273,6 +1301,13 @@ static teuk_status group_upload(teuk_group* g)
             // stage 3: u = 1/3 u + 2/3 (u2 + dt F(u2)), in place
             a.uk = h->u[2]; a.un = h->u[0]; a.out = h->u[0]; a.ca = 1.0 / 3.0; a.cb = 2.0 / 3.0;
             g->h_args[2 * (size_t)cap + idx] = a;
+            // the blocked step, between u[0] and u[1]
+            a.nstrips = bstrips;
+            a.ca = 0.0; a.cb = 1.0;
+            a.uk = a.un = h->u[0]; a.out = h->u[1];
+            g->h_args[3 * (size_t)cap + idx] = a;
+            a.uk = a.un = h->u[1]; a.out = h->u[0];
+            g->h_args[4 * (size_t)cap + idx] = a;
             g->points += h->plane;
             g->order.push_back(h);
             ++idx;
@@ -1283,10 +1318,12 @@ static teuk_status group_upload(teuk_group* g)
                                 hipMemcpyHostToDevice, g->stream);
     if (!e) e = (int)hipMemcpyAsync(g->d_start, g->h_start.data(), g->h_start.size() * sizeof(long long),
                                     hipMemcpyHostToDevice, g->stream);
+    if (!e) e = (int)hipMemcpyAsync(g->d_rows, g->h_rows.data(), g->h_rows.size() * sizeof(unsigned),
+                                    hipMemcpyHostToDevice, g->stream);
     if (!e) e = (int)hipStreamSynchronize(g->stream);
     if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("group upload: ") + hipGetErrorString((hipError_t)e));
-    g->gexec.assign(g->blocks.size(), nullptr);
-    g->gphase.assign(g->blocks.size(), std::vector<long long>());
+    g->gexec.assign(2 * g->blocks.size(), nullptr);
+    g->gphase.assign(2 * g->blocks.size(), std::vector<long long>());
     return TEUK_OK;
 }
 
@@ -1305,12 +1342,15 @@ teuk_status teuk_group_create(const teuk_device_ctx* ctx, int32_t max_members, i
     g->cap = max_members;
     g->workgroups = workgroups;
     g->rows = rows_per_tile > 0 ? rows_per_tile : 8;
-    g->h_args.assign(3 * (size_t)max_members, StageArgs{});
+    g->h_args.assign(5 * (size_t)max_members, StageArgs{});
     g->h_start.assign(2 * (size_t)max_members + 2, 0);   // members + blocks + 1 entries at most
+    g->h_rows.assign(2 * (size_t)max_members + 2, 0);
     int e = (int)hipMalloc(&g->d_args, g->h_args.size() * sizeof(StageArgs));
     if (!e) e = (int)hipMalloc(&g->d_start, g->h_start.size() * sizeof(long long));
+    if (!e) e = (int)hipMalloc(&g->d_rows, g->h_rows.size() * sizeof(unsigned));
     if (e) {
         if (g->d_args) (void)hipFree(g->d_args);
+        if (g->d_start) (void)hipFree(g->d_start);
         (void)hipGetLastError();
         delete g;
         return gfail(nullptr, e == (int)hipErrorOutOfMemory ? TEUK_ERR_OUT_OF_MEMORY : TEUK_ERR_DEVICE,
@@ -1366,24 +1406,28 @@ teuk_status teuk_group_remove(teuk_group* g, teuk_solver* h)
 static teuk_status group_block_eager(teuk_group* g, size_t bi, int64_t nsteps, hipStream_t stream)
 {
     const size_t cap = (size_t)g->cap;
-    const GroupBlock& b = g->blocks[bi];
+    GroupBlock& b = g->blocks[bi];
     const bool blocked = b.solo && g->order[(size_t)b.first]->cfg.integrator == TEUK_RK_SSP33_BLOCKED;
     for (int64_t n = 0; n < nsteps; ++n) {
+        if (b.fused) {   // one launch per step for the whole block
+            const int e = launch_group_blocked(g->d_args + (size_t)(3 + b.turn) * cap + b.first, g->d_rows + b.start, b.n,
+                                               b.rows, b.cls % 4, b.cls / 4, stream);
+            if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("group blocked step launch: ") +
+                                                       hipGetErrorString((hipError_t)e));
+            b.turn ^= 1;
+            for (int k = b.first; k < b.first + b.n; ++k) std::swap(g->order[(size_t)k]->u[0], g->order[(size_t)k]->u[1]);
+        }
         if (blocked) {   // a block of one member with the blocked step: one launch per step
             const int e = blocked_step_once(g->order[(size_t)b.first], stream);
             if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("blocked step launch: ") +
                                                        hipGetErrorString((hipError_t)e));
         }
-        for (int stage = 1; stage <= 3 && !blocked; ++stage) {
+        for (int stage = 1; stage <= 3 && !blocked && !b.fused; ++stage) {
             int e = 0;
             if (b.solo) {
                 for (int k = b.first; k < b.first + b.n && !e; ++k) {
-                    teuk_solver* h = g->order[(size_t)k];
+                    const teuk_solver* h = g->order[(size_t)k];
                     StageArgs a = stage_args(h);
-                    if (h->fused) {
-                        if (stage == 1) e = rk3_step(h, a, n, nsteps, true, stream);
-                        continue;
-                    }
                     rk3_stage(h, a, stage);
                     e = launch_stage(a, stage, h->cfg.weight_prec, kernel_chart(h->cfg), stream);
                 }
@@ -1419,15 +1463,16 @@ static void drop_group_graphs(teuk_group* g)
             (void)hipGraphExecDestroy(x);
             x = nullptr;
         }
-    g->gexec.assign(g->blocks.size(), nullptr);
-    g->gphase.assign(g->blocks.size(), std::vector<long long>());
+    g->gexec.assign(2 * g->blocks.size(), nullptr);
+    g->gphase.assign(2 * g->blocks.size(), std::vector<long long>());
 }
 
 // The graph of graph_chunk steps of block bi, captured for its members'
 // current sampling phases and state buffers (recaptured when they differ).
 static teuk_status capture_block(teuk_group* g, size_t bi)
 {
-    const GroupBlock& b = g->blocks[bi];
+    GroupBlock& b = g->blocks[bi];
+    const size_t gi = 2 * bi + (size_t)b.turn;   // each buffer role has a graph of its own (an odd chunk alternates)
     const int64_t chunk = g->graph_chunk;
     std::vector<long long> phase;
     for (int k = b.first; k < b.first + b.n; ++k) {
@@ -1441,12 +1486,12 @@ static teuk_status capture_block(teuk_group* g, size_t bi)
         phase.push_back(every > 0 ? h->steps % every : 0);
         phase.push_back((long long)(uintptr_t)h->u[0]);   // buffer roles (the blocked step trades them)
     }
-    if (g->gexec[bi] && g->gphase[bi] == phase) return TEUK_OK;
+    if (g->gexec[gi] && g->gphase[gi] == phase) return TEUK_OK;
     int e = 0;
-    if (g->gexec[bi]) {
+    if (g->gexec[gi]) {
         (void)hipStreamSynchronize(g->stream);
-        (void)hipGraphExecDestroy(g->gexec[bi]);
-        g->gexec[bi] = nullptr;
+        (void)hipGraphExecDestroy(g->gexec[gi]);
+        g->gexec[gi] = nullptr;
     }
     if (!g->cap_stream) {
         e = (int)hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking);
@@ -1457,6 +1502,7 @@ static teuk_status capture_block(teuk_group* g, size_t bi)
     }
     std::vector<std::pair<long long, long long>> saved;
     std::vector<std::array<double*, 3>> saved_u;
+    const int saved_turn = b.turn;
     for (int k = b.first; k < b.first + b.n; ++k) {
         const teuk_solver* h = g->order[(size_t)k];
         saved.emplace_back(h->steps, h->samples);
@@ -1467,6 +1513,7 @@ static teuk_status capture_block(teuk_group* g, size_t bi)
     const teuk_status st = group_block_eager(g, bi, chunk, g->cap_stream);
     hipGraph_t graph = nullptr;
     e = (int)hipStreamEndCapture(g->cap_stream, &graph);
+    b.turn = saved_turn;
     for (int k = b.first; k < b.first + b.n; ++k) {
         teuk_solver* h = g->order[(size_t)k];
         h->steps = saved[(size_t)(k - b.first)].first;
@@ -1479,19 +1526,19 @@ static teuk_status capture_block(teuk_group* g, size_t bi)
     }
     if (e || !graph)
         return gfail(g, TEUK_ERR_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString((hipError_t)(e ? e : (int)hipErrorUnknown)));
-    e = (int)hipGraphInstantiate(&g->gexec[bi], graph, nullptr, nullptr, 0);
+    e = (int)hipGraphInstantiate(&g->gexec[gi], graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (e) {
-        g->gexec[bi] = nullptr;
+        g->gexec[gi] = nullptr;
         return gfail(g, TEUK_ERR_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString((hipError_t)e));
     }
-    e = (int)hipGraphUpload(g->gexec[bi], g->stream);   // first replay as cheap as later ones
+    e = (int)hipGraphUpload(g->gexec[gi], g->stream);   // first replay as cheap as later ones
     if (e) {
-        (void)hipGraphExecDestroy(g->gexec[bi]);
-        g->gexec[bi] = nullptr;
+        (void)hipGraphExecDestroy(g->gexec[gi]);
+        g->gexec[gi] = nullptr;
         return gfail(g, TEUK_ERR_DEVICE, std::string("hipGraphUpload: ") + hipGetErrorString((hipError_t)e));
     }
-    g->gphase[bi] = phase;
+    g->gphase[gi] = phase;
     return TEUK_OK;
 }
 
@@ -1501,22 +1548,24 @@ teuk_status teuk_group_step(teuk_group* g, int64_t nsteps)
     if (nsteps < 0) return gfail(g, TEUK_ERR_INVALID_ARG, "nsteps must be >= 0");
     if (g->mem.empty()) return TEUK_OK;
     const int64_t chunk = g->graph_chunk;
-    if (g->gexec.size() != g->blocks.size()) drop_group_graphs(g);
+    if (g->gexec.size() != 2 * g->blocks.size()) drop_group_graphs(g);
     // block by block: a block runs all nsteps steps before the next starts
     for (size_t bi = 0; bi < g->blocks.size(); ++bi) {
         int64_t left = nsteps;
         if (chunk > 0 && nsteps >= chunk) {
-            teuk_status st = capture_block(g, bi);
-            if (st != TEUK_OK) return st;
-            const GroupBlock& b = g->blocks[bi];
+            GroupBlock& b = g->blocks[bi];
             for (int64_t q = nsteps / chunk; q > 0; --q) {
-                const int e = (int)hipGraphLaunch(g->gexec[bi], g->stream);
+                teuk_status st = capture_block(g, bi);
+                if (st != TEUK_OK) return st;
+                const int e = (int)hipGraphLaunch(g->gexec[2 * bi + (size_t)b.turn], g->stream);
                 if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString((hipError_t)e));
                 for (int k = b.first; k < b.first + b.n; ++k) {
                     teuk_solver* h = g->order[(size_t)k];
                     h->steps += chunk;
                     if (h->cfg.extract_every > 0) h->samples += chunk / h->cfg.extract_every;
+                    if (b.fused && (chunk & 1)) std::swap(h->u[0], h->u[1]);
                 }
+                if (b.fused) b.turn ^= (int)(chunk & 1);
             }
             left = nsteps % chunk;
         }
@@ -1702,6 +1751,7 @@ void teuk_group_destroy(teuk_group* g)
     for (teuk_solver* h : g->mem) h->group = nullptr;
     if (g->d_args) (void)hipFree(g->d_args);
     if (g->d_start) (void)hipFree(g->d_start);
+    if (g->d_rows) (void)hipFree(g->d_rows);
     delete g;
 }
 

@@ -100,15 +100,11 @@ __device__ __forceinline__ void row_put(double* row, unsigned off, double v)
     *(__attribute__((address_space(1))) double*)(scalar(row) + off) = v;
 }
 
+// Rows [k0, k1) of radial strip `strip` of one solve.  (Every wave of the workgroup
+// calls it with the same arguments.)
 template <int WP, bool kBtFirst, bool kHyp>
-__global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A, unsigned share, unsigned extra)
+__device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, int strip, int k0, int k1)
 {
-    // per half and plane, three-row rings of u^n (position s = point p0 - 3 + s) and
-    // of u(1) and u(2) (one value per point).  The planes are more than 255 values
-    // apart and the accesses go through opaque addresses plus immediate offsets:
-    // pairs of reads merged by the compiler would need an address of their own
-    // each (20 VALU instructions a step).
-    __shared__ double lds[2 * 4 * 3 * (kBStage + 2 * kBPts)];
     const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBHalf);
     const int tid = (int)threadIdx.x - half * kBHalf;
     const int l = tid - (tid >= kWave ? 1 : 0);          // point of this lane in the tile
@@ -121,278 +117,327 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A,
     double* outp[4] = {A.out, A.out + P, A.out + 2 * P, A.out + 3 * P};
     const int dir = half ? 1 : -1;
     const double ih1 = half ? A.ih1 : -A.ih1;
+    // the middle row, with at least one grid row on either side of it
+    int kb = (k0 + k1) >> 1;
+    if (kb == 0) kb = 1;
+    const int n0 = kb - k0, n1 = k1 - kb;             // rows of the halves (one may be 0)
+    const int n = half ? n1 : n0;
+    const int first = half ? kb : kb - 1;
+    const int lim = half ? nth - kb : kb;             // grid rows from `first` on, in this half's direction
+    const int N1 = min(n + 2, lim), N2 = min(n + 1, lim), NS = min(N1 + 1, lim);
+    const int steps = max(n0, n1) + 2;
 
-    // strip-rows [at, end): share, and one more for the first `extra` ranks (at most
-    // 2^34 / 114 + 2^16 strip-rows, so 32 bits)
-    const unsigned rank = (unsigned)xcd_rank((int)blockIdx.x, (int)gridDim.x);
-    unsigned at = rank * share + min(rank, extra);
-    const unsigned end = at + share + (rank < extra ? 1u : 0u);
-    while (at < end) {                                    // uniform over the workgroup
-        const int strip = (int)(at / (unsigned)nth);
-        const int k0 = (int)(at - (unsigned)strip * (unsigned)nth);
-        const int k1 = min(k0 + (int)(end - at), nth);
-        at += (unsigned)(k1 - k0);
-        // the middle row, with at least one grid row on either side of it
-        int kb = (k0 + k1) >> 1;
-        if (kb == 0) kb = 1;
-        const int n0 = kb - k0, n1 = k1 - kb;             // rows of the halves (one may be 0)
-        const int n = half ? n1 : n0;
-        const int first = half ? kb : kb - 1;
-        const int lim = half ? nth - kb : kb;             // grid rows from `first` on, in this half's direction
-        const int N1 = min(n + 2, lim), N2 = min(n + 1, lim), NS = min(N1 + 1, lim);
-        const int steps = max(n0, n1) + 2;
+    const int p0 = strip * kBW - kBLead;              // grid point of tile point 0
+    const int j = p0 + l;
+    const unsigned oc = (unsigned)clampi(j, 0, nr - 1) * 8u;
+    const unsigned oa = (unsigned)clampi(p0 - 3 + tid, 0, nr - 1) * 8u;            // staged position tid
+    const unsigned ob = (unsigned)clampi(p0 - 3 + kBHalf + tid, 0, nr - 1) * 8u;   // position 128 + tid
+    const bool halo = tid < kBStage - kBHalf;
+    // radial ghosts of u(1), u(2): the end values, by clamping to the points inside the grid
+    const int lo = clampi(-p0, 0, kBPts - 1), hi = clampi(nr - 1 - p0, 0, kBPts - 1);
+    LdsDouble q[6];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) q[t] = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + clampi(l - 3 + t, lo, hi));
+    const LdsDouble own = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + l);
+    const LdsDouble across = lds_at(lds + kBS1 + (half ^ 1) * 4 * 3 * kBPts + l);
+    const LdsDouble rows = lds_at(lds + half * 4 * 3 * kBStage + l), put = lds_at(lds + half * 4 * 3 * kBStage + tid);
+    const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
+    Radial rt;
+    if constexpr (!kHyp) rt = load_radial(A, oc);
 
-        const int p0 = strip * kBW - kBLead;              // grid point of tile point 0
-        const int j = p0 + l;
-        const unsigned oc = (unsigned)clampi(j, 0, nr - 1) * 8u;
-        const unsigned oa = (unsigned)clampi(p0 - 3 + tid, 0, nr - 1) * 8u;            // staged position tid
-        const unsigned ob = (unsigned)clampi(p0 - 3 + kBHalf + tid, 0, nr - 1) * 8u;   // position 128 + tid
-        const bool halo = tid < kBStage - kBHalf;
-        // radial ghosts of u(1), u(2): the end values, by clamping to the points inside the grid
-        const int lo = clampi(-p0, 0, kBPts - 1), hi = clampi(nr - 1 - p0, 0, kBPts - 1);
-        LdsDouble q[6];
+    struct Row { double a[4], b[4]; };
+    auto load_row = [&](Row& x, int i) {
+        const size_t row = (size_t)(first + dir * i) * nr;
 #pragma unroll
-        for (int t = 0; t < 6; ++t) q[t] = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + clampi(l - 3 + t, lo, hi));
-        const LdsDouble own = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + l);
-        const LdsDouble across = lds_at(lds + kBS1 + (half ^ 1) * 4 * 3 * kBPts + l);
-        const LdsDouble rows = lds_at(lds + half * 4 * 3 * kBStage + l), put = lds_at(lds + half * 4 * 3 * kBStage + tid);
-        const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
-        Radial rt;
-        if constexpr (!kHyp) rt = load_radial(A, oc);
+        for (int p = 0; p < 4; ++p) x.a[p] = row_get(ukp[p] + row, oa);
+        if (halo) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) x.b[p] = row_get(ukp[p] + row, ob);
+        }
+    };
+    auto store_row = [&](const Row& x, int b) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage] = x.a[p];
+        if (halo) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage + kBHalf] = x.b[p];
+        }
+    };
 
-        struct Row { double a[4], b[4]; };
-        auto load_row = [&](Row& x, int i) {
-            const size_t row = (size_t)(first + dir * i) * nr;
+    // The point's factors on one row.
+    struct Point {
+        PointCoef t;             // tortoise chart, built by stage 1
+        double hc[kNCH];         // hyperboloidal chart, from the table
+    };
+    // One stage at one row for this lane, from the window w[p][t] (input of plane p
+    // at j - 3 + t): the fluxes first, in the block that reads the window, so that
+    // a plane's flux starts as its values arrive and covers the reads of the next;
+    // then the rest with the input Phi at the own point on the rows ahead and behind.
+    // (hyperboloidal chart: each plane on the side of its own speed at the point, both
+    // sides in a wave whose lanes disagree; c holds the row's coefficients)
+    struct Diffs { double d[4]; };
+    auto fluxes = [&](auto read, double (&w)[4][6], const Point& c) {
+        Diffs r;
+        if constexpr (!kHyp) {
+            Flux f[4];
+            double fn[4];
 #pragma unroll
-            for (int p = 0; p < 4; ++p) x.a[p] = row_get(ukp[p] + row, oa);
-            if (halo) {
+            for (int p = 0; p < 4; ++p)
 #pragma unroll
-                for (int p = 0; p < 4; ++p) x.b[p] = row_get(ukp[p] + row, ob);
-            }
-        };
-        auto store_row = [&](const Row& x, int b) {
+                for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = read(p, t);
 #pragma unroll
-            for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage] = x.a[p];
-            if (halo) {
+            for (int p = 0; p < 2; ++p) f[p] = Weno<W>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
 #pragma unroll
-                for (int p = 0; p < 4; ++p) put[(p * 3 + b) * kBStage + kBHalf] = x.b[p];
-            }
-        };
-
-        // The point's factors on one row.
-        struct Point {
-            PointCoef t;             // tortoise chart, built by stage 1
-            double hc[kNCH];         // hyperboloidal chart, from the table
-        };
-        // One stage at one row for this lane, from the window w[p][t] (input of plane p
-        // at j - 3 + t): the fluxes first, in the block that reads the window, so that
-        // a plane's flux starts as its values arrive and covers the reads of the next;
-        // then the rest with the input Phi at the own point on the rows ahead and behind.
-        // (hyperboloidal chart: each plane on the side of its own speed at the point, both
-        // sides in a wave whose lanes disagree; c holds the row's coefficients)
-        struct Diffs { double d[4]; };
-        auto fluxes = [&](auto read, double (&w)[4][6], const Point& c) {
-            Diffs r;
-            if constexpr (!kHyp) {
-                Flux f[4];
-                double fn[4];
+            for (int p = 2; p < 4; ++p) f[p] = Weno<W>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
+            for (int p = 0; p < 4; ++p) fn[p] = next_lane(f[p].y);
 #pragma unroll
-                    for (int t = p >> 1; t < 5 + (p >> 1); ++t) w[p][t] = read(p, t);
+            for (int p = 0; p < 2; ++p) r.d[p] = plus_diff<W>(K, f[p], fn[p]);
 #pragma unroll
-                for (int p = 0; p < 2; ++p) f[p] = Weno<W>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
+            for (int p = 2; p < 4; ++p) r.d[p] = minus_diff<W>(K, f[p], fn[p]);
+        } else {
+            const bool up[2] = {c.hc[kHLam1] >= 0.0, c.hc[kHLam2] >= 0.0};
 #pragma unroll
-                for (int p = 2; p < 4; ++p) f[p] = Weno<W>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
+            for (int q = 0; q < 2; ++q) {
+                r.d[2 * q] = r.d[2 * q + 1] = 0.0;
+                if (__any(up[q])) {
 #pragma unroll
-                for (int p = 0; p < 4; ++p) fn[p] = next_lane(f[p].y);
+                    for (int p = 2 * q; p < 2 * q + 2; ++p) {
 #pragma unroll
-                for (int p = 0; p < 2; ++p) r.d[p] = plus_diff<W>(K, f[p], fn[p]);
-#pragma unroll
-                for (int p = 2; p < 4; ++p) r.d[p] = minus_diff<W>(K, f[p], fn[p]);
-            } else {
-                const bool up[2] = {c.hc[kHLam1] >= 0.0, c.hc[kHLam2] >= 0.0};
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    r.d[2 * q] = r.d[2 * q + 1] = 0.0;
-                    if (__any(up[q])) {
-#pragma unroll
-                        for (int p = 2 * q; p < 2 * q + 2; ++p) {
-#pragma unroll
-                            for (int t = 0; t < 5; ++t) w[p][t] = read(p, t);
-                            const Flux f = Weno<W>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
-                            const double d = plus_diff<W>(K, f, next_lane(f.y));
-                            if (up[q]) r.d[p] = d;
-                        }
+                        for (int t = 0; t < 5; ++t) w[p][t] = read(p, t);
+                        const Flux f = Weno<W>::flux(w[p][0], w[p][1], w[p][2], w[p][3], w[p][4], K);
+                        const double d = plus_diff<W>(K, f, next_lane(f.y));
+                        if (up[q]) r.d[p] = d;
                     }
-                    if (__any(!up[q])) {
-#pragma unroll
-                        for (int p = 2 * q; p < 2 * q + 2; ++p) {
-#pragma unroll
-                            for (int t = 1; t < 6; ++t) w[p][t] = read(p, t);
-                            const Flux f = Weno<W>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
-                            const double d = minus_diff<W>(K, f, next_lane(f.y));
-                            if (!up[q]) r.d[p] = d;
-                        }
-                    }
-                    r.d[2 * q] *= A.inv6dx;
-                    r.d[2 * q + 1] *= A.inv6dx;
                 }
+                if (__any(!up[q])) {
+#pragma unroll
+                    for (int p = 2 * q; p < 2 * q + 2; ++p) {
+#pragma unroll
+                        for (int t = 1; t < 6; ++t) w[p][t] = read(p, t);
+                        const Flux f = Weno<W>::flux(w[p][5], w[p][4], w[p][3], w[p][2], w[p][1], K);
+                        const double d = minus_diff<W>(K, f, next_lane(f.y));
+                        if (!up[q]) r.d[p] = d;
+                    }
+                }
+                r.d[2 * q] *= A.inv6dx;
+                r.d[2 * q + 1] *= A.inv6dx;
             }
-            return r;
-        };
-        auto finish = [&](const Diffs& r, const double (&w)[4][6], double ahR, double ahI, double bhR, double bhI,
-                          const Point& c) {
-            Four F;
+        }
+        return r;
+    };
+    auto finish = [&](const Diffs& r, const double (&w)[4][6], double ahR, double ahI, double bhR, double bhI,
+                      const Point& c) {
+        Four F;
+        if constexpr (kHyp) {
+            // symmetric in the rows ahead and behind but for the sign of ih1
+            F = rhs_h(c.hc, ih1, A.ih2, r.d[0], r.d[1], r.d[2], r.d[3], w[0][3], w[1][3], w[2][3], w[3][3], ahR, ahI,
+                      bhR, bhI);
+        } else {
+            // second differences as (up - 2 own) + down; a branch, as selects would
+            // cost sixteen instructions
+            Theta xR, xI;
+            if (half) {
+                xR = theta2(w[0][3], ahR, bhR);
+                xI = theta2(w[1][3], ahI, bhI);
+                asm volatile("" : "+v"(xR.d2));
+            } else {
+                xR = theta2(w[0][3], bhR, ahR);
+                xI = theta2(w[1][3], bhI, ahI);
+                asm volatile("" : "+v"(xI.d2));
+            }
+            xR.d1 = ahR - bhR;
+            xI.d1 = ahI - bhI;
+            F = rhs_t<kBtFirst>(A, ih1, c.t, r.d[0], r.d[1], r.d[2], r.d[3], w[0][3], w[1][3], w[2][3], w[3][3], xR, xI);
+        }
+        Four v;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) v.v[p] = euler(w[p][3], A.dt, F.v[p]);
+        return v;
+    };
+
+    Point pc[3];
+    double un[3][4];                     // u^n at the own point, rows i, i - 1, i - 2
+    double b0R, b0I;                     // Phi of u^n on row i - 1
+    double a1R = 0, a1I = 0;             // Phi of u(1) on row i (its parity ghost beyond a pole)
+    double b1R = 0, b1I = 0;             // ... on row i - 2
+    double a2R = 0, a2I = 0;             // Phi of u(2) on row i - 1
+    double b2R = 0, b2I = 0;             // ... on row i - 3
+    // hyperboloidal chart: the coefficients of the next row, loaded one row ahead
+    double hn[kNCH];
+    auto load_coefs = [&](int i) {
+        const double* c = A.ctab + (size_t)(first + dir * i) * nr;
+#pragma unroll
+        for (int q2 = 0; q2 < kNCH; ++q2) hn[q2] = row_get(c + (size_t)q2 * P, oc);
+    };
+    if constexpr (kHyp) load_coefs(0);
+    // every load of the first rows is under way before the first is waited for (rows
+    // past the last staged one are read again and not stored)
+    Row ahead;
+    {
+        Row r0, r1;
+        load_row(r0, 0);
+        load_row(r1, min(1, NS - 1));
+        load_row(ahead, min(2, NS - 1));
+        const size_t row = (size_t)(first - dir) * nr;
+        b0R = row_get(ukp[0] + row, oc);
+        b0I = row_get(ukp[1] + row, oc);
+        store_row(r0, 0);
+        if (NS > 1) store_row(r1, 1);
+    }
+
+    auto step = [&](auto phase, int i) {
+        constexpr int c0 = decltype(phase)::value, c1 = (c0 + 1) % 3, c2 = (c0 + 2) % 3;
+        lds_sync();
+        if (i < N1) {
+            // ---- stage 1 at row i: u(1) = u^n + dt F(u^n)
+            double w[4][6];
+            double ahR = lds_get(rows, c1 * kBStage + 3), ahI = lds_get(rows, (3 + c1) * kBStage + 3);
+            Polar pol;
+            if constexpr (!kHyp) pol = load_polar(A, first + dir * i);
             if constexpr (kHyp) {
-                // symmetric in the rows ahead and behind but for the sign of ih1
-                F = rhs_h(c.hc, ih1, A.ih2, r.d[0], r.d[1], r.d[2], r.d[3], w[0][3], w[1][3], w[2][3], w[3][3], ahR, ahI,
-                          bhR, bhI);
-            } else {
-                // second differences as (up - 2 own) + down; a branch, as selects would
-                // cost sixteen instructions
-                Theta xR, xI;
-                if (half) {
-                    xR = theta2(w[0][3], ahR, bhR);
-                    xI = theta2(w[1][3], ahI, bhI);
-                    asm volatile("" : "+v"(xR.d2));
-                } else {
-                    xR = theta2(w[0][3], bhR, ahR);
-                    xI = theta2(w[1][3], bhI, ahI);
-                    asm volatile("" : "+v"(xI.d2));
-                }
-                xR.d1 = ahR - bhR;
-                xI.d1 = ahI - bhI;
-                F = rhs_t<kBtFirst>(A, ih1, c.t, r.d[0], r.d[1], r.d[2], r.d[3], w[0][3], w[1][3], w[2][3], w[3][3], xR, xI);
+#pragma unroll
+                for (int q2 = 0; q2 < kNCH; ++q2) pc[c0].hc[q2] = hn[q2];
+                if (i + 1 < N1) load_coefs(i + 1);
             }
-            Four v;
+            const Diffs f = fluxes([&](int p, int t) { return lds_get(rows, (p * 3 + c0) * kBStage + t); }, w, pc[c0]);
+            if constexpr (!kHyp) pc[c0].t = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
+            if (i + 1 >= lim) {          // a ghost row (the ring holds an older one)
+                ahR = A.parity * w[0][3];
+                ahI = A.parity * w[1][3];
+            }
+            const Four o = finish(f, w, ahR, ahI, b0R, b0I, pc[c0]);
+            if (!dup) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) v.v[p] = euler(w[p][3], A.dt, F.v[p]);
-            return v;
-        };
-
-        Point pc[3];
-        double un[3][4];                     // u^n at the own point, rows i, i - 1, i - 2
-        double b0R, b0I;                     // Phi of u^n on row i - 1
-        double a1R = 0, a1I = 0;             // Phi of u(1) on row i (its parity ghost beyond a pole)
-        double b1R = 0, b1I = 0;             // ... on row i - 2
-        double a2R = 0, a2I = 0;             // Phi of u(2) on row i - 1
-        double b2R = 0, b2I = 0;             // ... on row i - 3
-        // hyperboloidal chart: the coefficients of the next row, loaded one row ahead
-        double hn[kNCH];
-        auto load_coefs = [&](int i) {
-            const double* c = A.ctab + (size_t)(first + dir * i) * nr;
+                for (int p = 0; p < 4; ++p) own[(p * 3 + c0) * kBPts] = o.v[p];
+            }
 #pragma unroll
-            for (int q2 = 0; q2 < kNCH; ++q2) hn[q2] = row_get(c + (size_t)q2 * P, oc);
-        };
-        if constexpr (kHyp) load_coefs(0);
-        // every load of the first rows is under way before the first is waited for (rows
-        // past the last staged one are read again and not stored)
-        Row ahead;
-        {
-            Row r0, r1;
-            load_row(r0, 0);
-            load_row(r1, min(1, NS - 1));
-            load_row(ahead, min(2, NS - 1));
-            const size_t row = (size_t)(first - dir) * nr;
-            b0R = row_get(ukp[0] + row, oc);
-            b0I = row_get(ukp[1] + row, oc);
-            store_row(r0, 0);
-            if (NS > 1) store_row(r1, 1);
+            for (int p = 0; p < 4; ++p) un[c0][p] = w[p][3];
+            b0R = w[0][3];
+            b0I = w[1][3];
+            a1R = o.v[0];
+            a1I = o.v[1];
+        } else {                         // beyond the pole (or no longer needed)
+            a1R *= A.parity;
+            a1I *= A.parity;
         }
-
-        auto step = [&](auto phase, int i) {
-            constexpr int c0 = decltype(phase)::value, c1 = (c0 + 1) % 3, c2 = (c0 + 2) % 3;
-            lds_sync();
-            if (i < N1) {
-                // ---- stage 1 at row i: u(1) = u^n + dt F(u^n)
-                double w[4][6];
-                double ahR = lds_get(rows, c1 * kBStage + 3), ahI = lds_get(rows, (3 + c1) * kBStage + 3);
-                Polar pol;
-                if constexpr (!kHyp) pol = load_polar(A, first + dir * i);
-                if constexpr (kHyp) {
-#pragma unroll
-                    for (int q2 = 0; q2 < kNCH; ++q2) pc[c0].hc[q2] = hn[q2];
-                    if (i + 1 < N1) load_coefs(i + 1);
-                }
-                const Diffs f = fluxes([&](int p, int t) { return lds_get(rows, (p * 3 + c0) * kBStage + t); }, w, pc[c0]);
-                if constexpr (!kHyp) pc[c0].t = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
-                if (i + 1 >= lim) {          // a ghost row (the ring holds an older one)
-                    ahR = A.parity * w[0][3];
-                    ahI = A.parity * w[1][3];
-                }
-                const Four o = finish(f, w, ahR, ahI, b0R, b0I, pc[c0]);
-                if (!dup) {
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) own[(p * 3 + c0) * kBPts] = o.v[p];
-                }
-#pragma unroll
-                for (int p = 0; p < 4; ++p) un[c0][p] = w[p][3];
-                b0R = w[0][3];
-                b0I = w[1][3];
-                a1R = o.v[0];
-                a1I = o.v[1];
-            } else {                         // beyond the pole (or no longer needed)
-                a1R *= A.parity;
-                a1I *= A.parity;
+        if (i >= 1 && i - 1 < N2) {
+            // ---- stage 2 at row i - 1: u(2) = 3/4 u^n + 1/4 (u(1) + dt F(u(1)))
+            if (c0 == 1 && i == 1) {     // across the middle: the other half's row 0
+                b1R = lds_get(across, c2 * kBPts);
+                b1I = lds_get(across, (3 + c2) * kBPts);
             }
-            if (i >= 1 && i - 1 < N2) {
-                // ---- stage 2 at row i - 1: u(2) = 3/4 u^n + 1/4 (u(1) + dt F(u(1)))
-                if (c0 == 1 && i == 1) {     // across the middle: the other half's row 0
-                    b1R = lds_get(across, c2 * kBPts);
-                    b1I = lds_get(across, (3 + c2) * kBPts);
-                }
-                double w[4][6];
-                const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], (p * 3 + c2) * kBPts); }, w, pc[c2]);
-                const Four o = finish(f, w, a1R, a1I, b1R, b1I, pc[c2]);
-                Four u2;
+            double w[4][6];
+            const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], (p * 3 + c2) * kBPts); }, w, pc[c2]);
+            const Four o = finish(f, w, a1R, a1I, b1R, b1I, pc[c2]);
+            Four u2;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) u2.v[p] = combine(0.75, un[c2][p], 0.25, o.v[p]);
-                if (!dup) {
+            for (int p = 0; p < 4; ++p) u2.v[p] = combine(0.75, un[c2][p], 0.25, o.v[p]);
+            if (!dup) {
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) own[kBS2 + (p * 3 + c2) * kBPts] = u2.v[p];
-                }
-                a2R = u2.v[0];
-                a2I = u2.v[1];
-                b1R = w[0][3];
-                b1I = w[1][3];
-            } else {
-                a2R *= A.parity;
-                a2I *= A.parity;
+                for (int p = 0; p < 4; ++p) own[kBS2 + (p * 3 + c2) * kBPts] = u2.v[p];
             }
-            if (i >= 2 && i - 2 < n) {
-                // ---- stage 3 at row i - 2: u^{n+1} = 1/3 u^n + 2/3 (u(2) + dt F(u(2)))
-                if (c0 == 2 && i == 2) {
-                    b2R = lds_get(across, kBS2 + c1 * kBPts);
-                    b2I = lds_get(across, kBS2 + (3 + c1) * kBPts);
-                }
-                double w[4][6];
-                const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], kBS2 + (p * 3 + c1) * kBPts); }, w, pc[c1]);
-                const Four o = finish(f, w, a2R, a2I, b2R, b2I, pc[c1]);
-                if (out_lane) {
-                    const size_t row = (size_t)(first + dir * (i - 2)) * nr;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) row_put(outp[p] + row, oc, combine(1.0 / 3.0, un[c1][p], 2.0 / 3.0, o.v[p]));
-                }
-                b2R = w[0][3];
-                b2I = w[1][3];
-            }
-            // row i + 2 into the slot of row i - 1
-            if (i + 2 < NS) {
-                store_row(ahead, c2);
-                if (i + 3 < NS) load_row(ahead, i + 3);
-            }
-        };
-        int i = 0;
-        for (;;) {
-            step(std::integral_constant<int, 0>{}, i);
-            if (++i >= steps) break;
-            step(std::integral_constant<int, 1>{}, i);
-            if (++i >= steps) break;
-            step(std::integral_constant<int, 2>{}, i);
-            if (++i >= steps) break;
+            a2R = u2.v[0];
+            a2I = u2.v[1];
+            b1R = w[0][3];
+            b1I = w[1][3];
+        } else {
+            a2R *= A.parity;
+            a2I *= A.parity;
         }
+        if (i >= 2 && i - 2 < n) {
+            // ---- stage 3 at row i - 2: u^{n+1} = 1/3 u^n + 2/3 (u(2) + dt F(u(2)))
+            if (c0 == 2 && i == 2) {
+                b2R = lds_get(across, kBS2 + c1 * kBPts);
+                b2I = lds_get(across, kBS2 + (3 + c1) * kBPts);
+            }
+            double w[4][6];
+            const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], kBS2 + (p * 3 + c1) * kBPts); }, w, pc[c1]);
+            const Four o = finish(f, w, a2R, a2I, b2R, b2I, pc[c1]);
+            if (out_lane) {
+                const size_t row = (size_t)(first + dir * (i - 2)) * nr;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) row_put(outp[p] + row, oc, combine(1.0 / 3.0, un[c1][p], 2.0 / 3.0, o.v[p]));
+            }
+            b2R = w[0][3];
+            b2I = w[1][3];
+        }
+        // row i + 2 into the slot of row i - 1
+        if (i + 2 < NS) {
+            store_row(ahead, c2);
+            if (i + 3 < NS) load_row(ahead, i + 3);
+        }
+    };
+    int i = 0;
+    for (;;) {
+        step(std::integral_constant<int, 0>{}, i);
+        if (++i >= steps) break;
+        step(std::integral_constant<int, 1>{}, i);
+        if (++i >= steps) break;
+        step(std::integral_constant<int, 2>{}, i);
+        if (++i >= steps) break;
+    }
+}
+
+// per half and plane, three-row rings of u^n (position s = point p0 - 3 + s) and
+// of u(1) and u(2) (one value per point).  The planes are more than 255 values
+// apart and the accesses go through opaque addresses plus immediate offsets:
+// pairs of reads merged by the compiler would need an address of their own
+// each (20 VALU instructions a step).
+constexpr int kBLds = 2 * 4 * 3 * (kBStage + 2 * kBPts);
+
+// Strip-rows [at, end) of a rank: `share`, and one more for the first `extra` ranks
+// (a grid has at most 2^34 / 114 + 2^16 strip-rows, a launch less than 2^31).
+__device__ __forceinline__ void share_of(unsigned share, unsigned extra, unsigned& at, unsigned& end)
+{
+    const unsigned rank = (unsigned)xcd_rank((int)blockIdx.x, (int)gridDim.x);
+    at = rank * share + min(rank, extra);
+    end = at + share + (rank < extra ? 1u : 0u);
+}
+
+template <int WP, bool kBtFirst, bool kHyp>
+__global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A, unsigned share, unsigned extra)
+{
+    __shared__ double lds[kBLds];
+    unsigned at, end;
+    share_of(share, extra, at, end);
+    while (at < end) {                                    // uniform over the workgroup
+        const int strip = (int)(at / (unsigned)A.nth);
+        const int k0 = (int)(at - (unsigned)strip * (unsigned)A.nth);
+        const int k1 = min(k0 + (int)(end - at), A.nth);
+        at += (unsigned)(k1 - k0);
+        blocked_tile<WP, kBtFirst, kHyp>(A, lds, strip, k0, k1);
         lds_sync();   // before the next tile's rows go into the rings
+    }
+}
+
+// The same step of several independent solves in one launch: member m owns the
+// strip-rows [start[m], start[m + 1]) of the launch, which its workgroups share
+// equally whatever solve they belong to, so that small solves together fill the
+// GPU and no solve waits for another's last tiles.
+template <int WP, bool kBtFirst, bool kHyp>
+__global__ __launch_bounds__(kBThreads, 2) void group_blocked_kernel(const StageArgs* __restrict__ args,
+                                                                     const unsigned* __restrict__ start, int nmem,
+                                                                     unsigned share, unsigned extra)
+{
+    __shared__ double lds[kBLds];
+    unsigned at, end;
+    share_of(share, extra, at, end);
+    while (at < end) {
+        int lo = 0, hi = nmem - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (start[mid] <= at) lo = mid;
+            else hi = mid - 1;
+        }
+        const StageArgs A = args[lo];
+        const unsigned local = at - start[lo];
+        const int strip = (int)(local / (unsigned)A.nth);
+        const int k0 = (int)(local - (unsigned)strip * (unsigned)A.nth);
+        const int k1 = min(k0 + (int)(end - at), A.nth);
+        at += (unsigned)(k1 - k0);
+        blocked_tile<WP, kBtFirst, kHyp>(A, lds, strip, k0, k1);
+        lds_sync();
     }
 }
 
@@ -438,6 +483,31 @@ int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own
     TEUK_BLAUNCH(TEUK_W_FP64, false, true)
     TEUK_BLAUNCH(TEUK_W_FP32, false, true)
 #undef TEUK_BLAUNCH
+    if (!done) return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
+}
+
+int launch_group_blocked(const StageArgs* args, const unsigned* start, int nmem, long long rows, int weight_prec,
+                         int chart, void* stream)
+{
+    if (nmem < 1 || rows < 1 || rows > (1LL << 31) - 1) return (int)hipErrorInvalidValue;
+    const int resident = blocked_grid(weight_prec, chart);
+    if (resident < 1) return (int)hipErrorInvalidValue;
+    const unsigned g = (unsigned)(rows < resident ? rows : resident), r = (unsigned)rows;
+    const dim3 grid(g), block(kBThreads);
+    hipStream_t st = (hipStream_t)stream;
+    (void)hipGetLastError();
+    bool done = false;
+#define TEUK_GBLAUNCH(W, F, H)                                                                                   \
+    if (!done && weight_prec == W && (chart == TEUK_CHART_HYPERBOLOIDAL) == H) {                                 \
+        hipLaunchKernelGGL((group_blocked_kernel<W, F, H>), grid, block, 0, st, args, start, nmem, r / g, r % g); \
+        done = true;                                                                                             \
+    }
+    TEUK_GBLAUNCH(TEUK_W_FP64, true, false)
+    TEUK_GBLAUNCH(TEUK_W_FP32, false, false)
+    TEUK_GBLAUNCH(TEUK_W_FP64, false, true)
+    TEUK_GBLAUNCH(TEUK_W_FP32, false, true)
+#undef TEUK_GBLAUNCH
     if (!done) return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }

@@ -521,14 +521,17 @@ __device__ __forceinline__ void lds_sync()
 }
 
 // Load a double at a byte offset from a uniform base: the 32-bit offset lets
-// the compiler use the scalar-base addressing form (no 64-bit address math).
+// the compiler use the scalar-base addressing form (no 64-bit address math),
+// and the global address space keeps it from flat accesses where the base came
+// out of memory (the members' descriptors of a batched launch).
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
 __device__ __forceinline__ double ldb(const double* base, unsigned off)
 {
-    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + off);
+    return *(const __attribute__((address_space(1))) double*)((GlobalBytes)base + off);
 }
 __device__ __forceinline__ void stb(double* base, unsigned off, double v)
 {
-    *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) = v;
+    *(__attribute__((address_space(1))) double*)((__attribute__((address_space(1))) char*)base + off) = v;
 }
 
 // Ranks are dealt so that each XCD (which receives every eighth workgroup id)

@@ -139,6 +139,11 @@ int launch_coef_dump(const double* rtab, const double* ttab, const double* ctab,
 constexpr int kBlockedPoints = 114;
 int blocked_grid(int weight_prec, int chart);
 int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own_order, void* stream);
+// The same step of several solves (device arrays): args[0..nmem) with nstrips in
+// strips of kBlockedPoints, start[0..nmem] the prefix sums of their strip-rows
+// (nstrips * nth each), rows = start[nmem].
+int launch_group_blocked(const StageArgs* args, const unsigned* start, int nmem, long long rows, int weight_prec,
+                         int chart, void* stream);
 // Pipelined steps (tortoise chart, FP64 state, WENO5): nsteps SSP-RK(3,3)
 // steps in one cooperative launch of `grid` workgroups (at most pipe_grid(),
 // the resident count, and at most the tile count st[0].nstrips * st[0].segs);

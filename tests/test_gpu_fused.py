@@ -97,3 +97,44 @@ def test_noalloc_keeps_the_callers_buffer(n):
         sv.set_initial(u0)
         sv.step(n)
         np.testing.assert_array_equal(u.cpu().numpy(), sv.state())
+
+
+@pytest.mark.parametrize("chunk", [0, 1, 3, 4])
+def test_group_members_equal_solves_alone(chunk):
+    """One blocked launch over members of both charts and precisions, eagerly and from graphs of odd and
+    even chunks, with a member stepped on its own in between (its state keeps its buffer) and one leaving."""
+    print("case fused group", chunk, flush=True)
+    T1 = dict(x_min=-30.0, x_max=50.0, x_extract=5.0, max_samples=64)
+    TH = dict(x_min=20 / 21, x_max=19.0, x_extract=5.0, max_samples=64, chart="H")
+    specs = [(130, 5, 0, 1, 0.5, "fp64", 1, T1), (700, 33, -2, 2, 0.9, "fp64", 1, T1), (7, 2, 0, 0, 0.3, "fp64", 0, T1),
+             (229, 12, -2, 1, 0.8, "fp32", 1, T1), (300, 9, -2, 0, 1.0, "fp64", 1, TH), (115, 4, 0, 1, 1.0, "fp32", 1, TH)]
+    alone, members = [], []
+    for i, (nr, nth, s_, m, a, wp, every, kw) in enumerate(specs):
+        kw = dict(kw, extract_every=every, max_samples=64 if every else 0)
+        c = [T.make_config(s=s_, m=m, a=a, nr=nr, ntheta=nth, weight_prec=wp, workgroups=w, **kw) for w in (0, 4000)]
+        u0 = W.random_state(nr, nth, seed=i, smooth=True)
+        x, y = T.Solver(c[0]), T.Solver(c[1])
+        x.set_initial(u0)
+        y.set_initial(u0)
+        members.append(x)
+        alone.append(y)
+    g = T.Group(len(specs))
+    for x in members:
+        g.add(x)
+    if chunk:
+        g.set_graph(chunk)
+    for n, own in ((3, 3), (4, 1), (7, 2), (1, 5)):
+        g.step(n)
+        members[1].step(own)
+        alone[1].step(own)
+        for x, y in zip(members, alone):
+            y.step(n)
+    g.remove(members[0])
+    g.step(5)
+    members[0].step(5)
+    for x, y in zip(members, alone):
+        y.step(5)
+        np.testing.assert_array_equal(x.state(), y.state())
+        if x.cfg.extract_every:
+            np.testing.assert_array_equal(x.waveform()[1], y.waveform()[1])
+    g.close()
