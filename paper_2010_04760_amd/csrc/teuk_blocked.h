@@ -63,11 +63,20 @@ static_assert(kBLead + kBW + kBLead + 1 == kBPts, "tile geometry");
 // this load leaves).  The march is unrolled by three so that the values rolling
 // over three rows (coefficients, u^n) and the three-slot rings keep fixed registers
 // and addresses: with the copies, one-ended marches and 1024 one-tile workgroups
-// of the form before it the step took 3.57e7 instructions and 87.5 us, now 77.5.
+// of the form before it the step took 3.57e7 instructions and 87.5 us, now 74.9.
+//
+// Issue priority: the two waves of a SIMD belong to different workgroups, and a
+// wave alone issues FP64 work at half the rate of two, so a stall of either costs
+// its full length.  A wave's priority drops to 0 once the fluxes of its stage 1 are
+// formed and rises stage by stage to 3 over the barrier into the next step: the two
+// settle half a step apart, one computing while the other meets its barrier and
+// its first LDS reads (8192 x 256 77.5 -> 74.9 us a step, 16384 x 512 302 -> 284,
+// 4099 x 131 with FP32 weights 32.0 -> 29.7, chart H 16384 x 64 49.4 -> 46.2; steps
+// down along the march, as in the stage kernel, 77.3, 295, 31.6 and 46.0).
 //
 // Hyperboloidal chart: the ten coefficients of a point are read once a step (loaded
 // one row ahead) instead of once a stage, 144 B a point-step against 496, and a
-// row's fluxes are taken on the side of its own speed: 16384 x 64 in 48.5 us where
+// row's fluxes are taken on the side of its own speed: 16384 x 64 in 46.2 us where
 // three launches of the stage kernel take 87.8 at 5.9 TB/s.
 constexpr int kBS1 = 2 * 4 * 3 * kBStage;            // u(1) rings
 constexpr int kBS2 = 2 * 4 * 3 * kBPts;              // u(2) rings, from the u(1) rings on
@@ -291,6 +300,7 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
         lds_sync();
         if (i < N1) {
             // ---- stage 1 at row i: u(1) = u^n + dt F(u^n)
+            __builtin_amdgcn_s_setprio(3);
             double w[4][6];
             double ahR = lds_get(rows, c1 * kBStage + 3), ahI = lds_get(rows, (3 + c1) * kBStage + 3);
             Polar pol;
@@ -301,7 +311,8 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
                 if (i + 1 < N1) load_coefs(i + 1);
             }
             const Diffs f = fluxes([&](int p, int t) { return lds_get(rows, (p * 3 + c0) * kBStage + t); }, w, pc[c0]);
-            if constexpr (!kHyp) pc[c0].t = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
+            __builtin_amdgcn_s_setprio(0);
+                if constexpr (!kHyp) pc[c0].t = point_coef_t(rt, pol, point_vsig(rt, pol.sn2));
             if (i + 1 >= lim) {          // a ghost row (the ring holds an older one)
                 ahR = A.parity * w[0][3];
                 ahI = A.parity * w[1][3];
@@ -323,6 +334,7 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
         }
         if (i >= 1 && i - 1 < N2) {
             // ---- stage 2 at row i - 1: u(2) = 3/4 u^n + 1/4 (u(1) + dt F(u(1)))
+            __builtin_amdgcn_s_setprio(1);
             if (c0 == 1 && i == 1) {     // across the middle: the other half's row 0
                 b1R = lds_get(across, c2 * kBPts);
                 b1I = lds_get(across, (3 + c2) * kBPts);
@@ -347,6 +359,7 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
         }
         if (i >= 2 && i - 2 < n) {
             // ---- stage 3 at row i - 2: u^{n+1} = 1/3 u^n + 2/3 (u(2) + dt F(u(2)))
+            __builtin_amdgcn_s_setprio(2);
             if (c0 == 2 && i == 2) {
                 b2R = lds_get(across, kBS2 + c1 * kBPts);
                 b2I = lds_get(across, kBS2 + (3 + c1) * kBPts);
