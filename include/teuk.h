@@ -279,9 +279,9 @@ teuk_status teuk_set_initial(teuk_solver* h, const double* u, int32_t on_device)
  * is three fused stage kernels
  *     u1 = u + dt F(u);  u2 = 3/4 u + 1/4 (u1 + dt F(u1));  u = 1/3 u + 2/3 (u2 + dt F(u2)),
  * SSP-RK(10,4) ten (see TEUK_RK_SSP104),
- * or, for SSP-RK(3,3) with workgroups = 0 (FP64 state, WENO5, FP64 or FP32 weights,
- * second-order theta differences), one temporally blocked launch a step with the
- * same bits (unless teuk_tune measured the stage launches
+ * or, for SSP-RK(3,3) with workgroups = 0 (FP64 state, WENO5, second-order theta
+ * differences; with BF16 weights in the tortoise chart up to 2^20 points), one
+ * temporally blocked launch a step with the same bits (unless teuk_tune measured the stage launches
  * faster for this class),
  * with F(u) = -(M d_x u + L u + A u) of eq. evln and WENO5 radial derivatives
  * (Sec. 3.1.2).  A waveform sample is taken after every extract_every-th step.

@@ -282,19 +282,25 @@ int pick_segs(const teuk_config& c, int nstrips, int weight_prec, bool first)
 
 // Whether SSP-RK(3,3) steps of c are taken by the temporally blocked launch (one
 // launch and 64 B of traffic per point-step) instead of three stage launches (256 B):
-// wherever that kernel is built -- FP64 state, WENO5 with FP64 or FP32 weights,
-// second-order theta differences -- unless the caller asks for a
+// wherever that kernel is built -- FP64 state, WENO5, second-order theta
+// differences -- unless the caller asks for a
 // budget of stage workgroups or the tuner found the stage launches faster.  The
 // results are the same to the bit.  Both measured, us a step, FP64 weights:
-// 16384 x 512 299 against 472, 8192 x 256 78.6 against 100.5, 4099 x 131 30.4
-// against 35.8, 2050 x 97 17.7 against 23.5, 1024 x 64 12.3 against 14.0, 512 x 32
+// 16384 x 512 284 against 472, 8192 x 256 74.9 against 98, 4099 x 131 28.5
+// against 35.8, 2050 x 97 17.9 against 23.5, 1024 x 64 12.3 against 14.0, 512 x 32
 // 8.0 against 11.1, 200 x 12 7.8 against 11.0; hyperboloidal chart (144 B against
-// 496 B a point-step) 16384 x 64 48.5 against 87.8, 300 x 24 8.5 against 12.4.
+// 496 B a point-step) 16384 x 64 46.2 against 87.8, 300 x 24 8.5 against 12.4; FP16
+// weights 8192 x 256 120 against 131, 2050 x 97 27.4 against 33.1, 512 x 32 11.4
+// against 13.6.  BF16 weights in the tortoise chart are bound by their own
+// instructions, which the recomputed tile edges multiply: 8192 x 256 165 against
+// 152, 4096 x 200 78.9 against 79.5, 2050 x 97 38.4 against 40.8, so they take it up
+// to 2^20 points.
 bool fused_step(const teuk_config& c)
 {
-    return c.integrator == TEUK_RK_SSP33 && c.state_prec == TEUK_S_FP64 &&
-           c.scheme == TEUK_SCHEME_WENO5 && (c.weight_prec == TEUK_W_FP64 || c.weight_prec == TEUK_W_FP32) &&
-           c.theta_order != 4 && c.workgroups == 0 && !tuned_stage_launches(c);
+    const bool heavy = c.weight_prec == TEUK_W_BF16 && c.chart == TEUK_CHART_TORTOISE &&
+                       (long long)c.nr * c.ntheta > (1LL << 20);
+    return c.integrator == TEUK_RK_SSP33 && c.state_prec == TEUK_S_FP64 && c.scheme == TEUK_SCHEME_WENO5 &&
+           c.theta_order != 4 && c.workgroups == 0 && !heavy && !tuned_stage_launches(c);
 }
 
 // Radial strips and workgroups of the temporally blocked launch: a budget of
@@ -1218,14 +1224,14 @@ static int group_segs(int nth, int rows)
 }
 
 // Whether cache blocks of class c (weight precision + 4 launch class) step by the
-// temporally blocked launch over all members (as fused_step for one solve: FP64 or
-// FP32 weights, either chart, second-order theta differences).  24 solves of 513 to
+// temporally blocked launch over all members (as fused_step for one solve; BF16
+// weights in the tortoise chart, where it depends on the grid, by stage launches).  24 solves of 513 to
 // 2977 by 26 to 95 points, FP64 and FP32 weights: 173 us a step in six stage
 // launches, 126 in two blocked ones.
 static bool fused_class(int c)
 {
     const int wp = c % 4, chart = c / 4;
-    return (wp == TEUK_W_FP64 || wp == TEUK_W_FP32) && (chart == TEUK_CHART_TORTOISE || chart == TEUK_CHART_HYPERBOLOIDAL);
+    return chart == TEUK_CHART_HYPERBOLOIDAL || (chart == TEUK_CHART_TORTOISE && wp != TEUK_W_BF16);
 }
 
 // Rebuild and upload the members' stage descriptors and tile prefix sums, cut

@@ -458,18 +458,23 @@ __global__ __launch_bounds__(kBThreads, 2) void group_blocked_kernel(const Stage
 
 int blocked_grid(int weight_prec, int chart)
 {
-    static ResidentCache cache[2][2];
+    static ResidentCache cache[4][2];
     int dev = 0;
-    const bool f32 = weight_prec == TEUK_W_FP32, hyp = chart == TEUK_CHART_HYPERBOLOIDAL;
-    if ((weight_prec != TEUK_W_FP64 && !f32) || (chart != TEUK_CHART_TORTOISE && !hyp) || hipGetDevice(&dev) != hipSuccess)
+    const bool hyp = chart == TEUK_CHART_HYPERBOLOIDAL;
+    if (weight_prec < 0 || weight_prec > 3 || (chart != TEUK_CHART_TORTOISE && !hyp) || hipGetDevice(&dev) != hipSuccess)
         return 0;
-    return cache[f32][hyp].get(dev, [&] {
+    return cache[weight_prec][hyp].get(dev, [&] {
         int cus = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        const void* fn = hyp ? (f32 ? (const void*)blocked_step_kernel<TEUK_W_FP32, false, true>
-                                    : (const void*)blocked_step_kernel<TEUK_W_FP64, false, true>)
-                             : (f32 ? (const void*)blocked_step_kernel<TEUK_W_FP32, false, false>
-                                    : (const void*)blocked_step_kernel<TEUK_W_FP64, true, false>);
+        const void* fn = nullptr;
+#define TEUK_BGRID(W, F)                                                                                          \
+    if (weight_prec == W)                                                                                         \
+        fn = hyp ? (const void*)blocked_step_kernel<W, F, true> : (const void*)blocked_step_kernel<W, F, false>;
+        TEUK_BGRID(TEUK_W_FP64, bt_first<TEUK_W_FP64>())
+        TEUK_BGRID(TEUK_W_FP32, bt_first<TEUK_W_FP32>())
+        TEUK_BGRID(TEUK_W_FP16, bt_first<TEUK_W_FP16>())
+        TEUK_BGRID(TEUK_W_BF16, bt_first<TEUK_W_BF16>())
+#undef TEUK_BGRID
         const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBThreads, 0);
         return e != hipSuccess || per_cu < 1 ? 0 : cus * per_cu;
     });
@@ -484,17 +489,23 @@ int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own
     const dim3 grid((unsigned)a.grid), block(kBThreads);
     hipStream_t st = (hipStream_t)stream;
     const unsigned rows = (unsigned)((long long)a.nstrips * a.nth), g = (unsigned)a.grid;
+    const bool hyp = chart == TEUK_CHART_HYPERBOLOIDAL;
     bool done = false;
-#define TEUK_BLAUNCH(W, F, H)                                                                                         \
-    if (!done && weight_prec == W && (chart == TEUK_CHART_HYPERBOLOIDAL) == H && (W != TEUK_W_FP64 || H || own_order != F)) { \
-        hipLaunchKernelGGL((blocked_step_kernel<W, F, H>), grid, block, 0, st, a, rows / g, rows % g);                \
-        done = true;                                                                                                  \
+#define TEUK_BLAUNCH(W, F)                                                                                     \
+    if (!done && weight_prec == W && (W != TEUK_W_FP64 || hyp || own_order != F)) {                              \
+        if (hyp) hipLaunchKernelGGL((blocked_step_kernel<W, F, true>), grid, block, 0, st, a, rows / g, rows % g); \
+        else hipLaunchKernelGGL((blocked_step_kernel<W, F, false>), grid, block, 0, st, a, rows / g, rows % g);  \
+        done = true;                                                                                             \
     }
-    TEUK_BLAUNCH(TEUK_W_FP64, true, false)
-    TEUK_BLAUNCH(TEUK_W_FP64, false, false)
-    TEUK_BLAUNCH(TEUK_W_FP32, false, false)
-    TEUK_BLAUNCH(TEUK_W_FP64, false, true)
-    TEUK_BLAUNCH(TEUK_W_FP32, false, true)
+    TEUK_BLAUNCH(TEUK_W_FP64, bt_first<TEUK_W_FP64>())
+    TEUK_BLAUNCH(TEUK_W_FP32, bt_first<TEUK_W_FP32>())
+    TEUK_BLAUNCH(TEUK_W_FP16, bt_first<TEUK_W_FP16>())
+    TEUK_BLAUNCH(TEUK_W_BF16, bt_first<TEUK_W_BF16>())
+    if (!done && weight_prec == TEUK_W_FP64) {
+        hipLaunchKernelGGL((blocked_step_kernel<TEUK_W_FP64, !bt_first<TEUK_W_FP64>(), false>), grid, block, 0, st, a, rows / g,
+                           rows % g);
+        done = true;
+    }
 #undef TEUK_BLAUNCH
     if (!done) return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
@@ -510,16 +521,18 @@ int launch_group_blocked(const StageArgs* args, const unsigned* start, int nmem,
     const dim3 grid(g), block(kBThreads);
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();
+    const bool hyp = chart == TEUK_CHART_HYPERBOLOIDAL;
     bool done = false;
-#define TEUK_GBLAUNCH(W, F, H)                                                                                   \
-    if (!done && weight_prec == W && (chart == TEUK_CHART_HYPERBOLOIDAL) == H) {                                 \
-        hipLaunchKernelGGL((group_blocked_kernel<W, F, H>), grid, block, 0, st, args, start, nmem, r / g, r % g); \
-        done = true;                                                                                             \
+#define TEUK_GBLAUNCH(W, F)                                                                                         \
+    if (weight_prec == W) {                                                                                         \
+        if (hyp) hipLaunchKernelGGL((group_blocked_kernel<W, F, true>), grid, block, 0, st, args, start, nmem, r / g, r % g); \
+        else hipLaunchKernelGGL((group_blocked_kernel<W, F, false>), grid, block, 0, st, args, start, nmem, r / g, r % g);    \
+        done = true;                                                                                                \
     }
-    TEUK_GBLAUNCH(TEUK_W_FP64, true, false)
-    TEUK_GBLAUNCH(TEUK_W_FP32, false, false)
-    TEUK_GBLAUNCH(TEUK_W_FP64, false, true)
-    TEUK_GBLAUNCH(TEUK_W_FP32, false, true)
+    TEUK_GBLAUNCH(TEUK_W_FP64, bt_first<TEUK_W_FP64>())
+    TEUK_GBLAUNCH(TEUK_W_FP32, bt_first<TEUK_W_FP32>())
+    TEUK_GBLAUNCH(TEUK_W_FP16, bt_first<TEUK_W_FP16>())
+    TEUK_GBLAUNCH(TEUK_W_BF16, bt_first<TEUK_W_BF16>())
 #undef TEUK_GBLAUNCH
     if (!done) return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();

@@ -213,8 +213,16 @@ __device__ __forceinline__ bool operator==(Bf16Val a, Bf16Val b) { return a.v ==
 struct LowBF16 {
     typedef Bf16Val T;
     __device__ static T cvt(float x) { return {bf16_round(x)}; }
-    __device__ static T rcp(T x) { return {bf16_round(1.0f / x.v)}; }
-    __device__ static T ratio(T a, T b) { return {bf16_round(a.v / b.v)}; }
+    // A quotient of two 8-bit significands lies at least 2^-16.9 (relative) from every
+    // midpoint between BF16 values, so a times the 1 ulp reciprocal (error below
+    // 2^-21) rounds to what the true quotient rounds to, in 2 instructions instead
+    // of 10.  Where the reciprocal could overflow, a true division.  (Quotients
+    // below 2^-126, whose significands are shorter, vanish when squared.)
+    __device__ static T rcp(T x) { return {bf16_round(__builtin_amdgcn_rcpf(x.v))}; }
+    __device__ static T ratio(T a, T b)
+    {
+        return {bf16_round(b.v >= 0x1p-120f ? a.v * __builtin_amdgcn_rcpf(b.v) : a.v / b.v)};
+    }
     __device__ static float f(T x) { return x.v; }
 };
 

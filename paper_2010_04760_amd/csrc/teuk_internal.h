@@ -129,8 +129,7 @@ int launch_dt_bound(const double* rtab, const double* ttab, const double* ctab, 
 int launch_guard(const double* u, long long n, int* flag, void* stream);
 int launch_coef_dump(const double* rtab, const double* ttab, const double* ctab, int nr, int nth, double* out,
                      void* stream);
-// Temporal blocking: one whole SSP-RK(3,3) step (either chart, FP64 or FP32
-// weights) from a.uk into a.out (distinct buffers) by a.grid workgroups, each an
+// Temporal blocking: one whole SSP-RK(3,3) step (either chart, any weight precision) from a.uk into a.out (distinct buffers) by a.grid workgroups, each an
 // equal share of the rows of the a.nstrips strips of kBlockedPoints radial points
 // (a.grid <= a.nstrips * a.nth).  own_order: the order of one sum that
 // TEUK_RK_SSP33_BLOCKED results have had, else the stage kernels'.

@@ -28,7 +28,7 @@ def pair(nr, nth, wp, **kw):
     return a, b, u0
 
 
-@pytest.mark.parametrize("wp", ["fp64", "fp32"])
+@pytest.mark.parametrize("wp", ["fp64", "fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("nr,nth", [(7, 2), (64, 3), (114, 2), (115, 7), (127, 5), (228, 4), (229, 33), (1000, 190),
                                     (3000, 61)])
 def test_equals_stage_launches(nr, nth, wp):
@@ -47,7 +47,7 @@ def test_equals_stage_launches(nr, nth, wp):
     b.close()
 
 
-@pytest.mark.parametrize("wp", ["fp64", "fp32"])
+@pytest.mark.parametrize("wp", ["fp64", "fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("nr,nth,a,x_min", [(7, 3, 1.0, 20 / 21), (115, 2, 1.0, 20 / 21), (300, 25, 0.8, 1.2),
                                             (901, 64, 0.8, 1.2)])
 def test_hyperboloidal_equals_stage_launches(nr, nth, a, x_min, wp):
