@@ -14,15 +14,25 @@
 //     <= 3u^2), DWPlusFP (2u^2), DWTimesFP3 (2u^2), DWTimesDW3 (4u^2), u = 2^-53;
 //     the reciprocal is the double reciprocal corrected by one Newton step
 //     carried to second order in the residual.
-// Work layout: one wave per (63-point radial strip, theta row), four rows per
-// workgroup.  Lane l of a strip owns point j = 63 strip + l and computes the
-// four interface fluxes at j - 1/2; the flux at j + 1/2 comes from lane l + 1.
-// Values are (hi, lo) pairs stored as double2, [4][ntheta][nr], radial index
-// fastest.  The kernel is bound by FP64 VALU issue: a double-double operation
-// costs 3-20 FP64 instructions.
+// Work layout: one workgroup of four waves per (63-point radial strip, theta
+// row), one wave for each of the four planes.  Lane l of a strip owns point
+// j = 63 strip + l and computes the interface flux of its wave's plane at
+// j - 1/2; the flux at j + 1/2 comes from lane l + 1.  The Phi waves then form the
+// theta differences and hand them and their radial derivatives to the pi waves,
+// which form the coupled sums meanwhile and wait once.  Values are (hi, lo) pairs
+// stored as double2, [4][ntheta][nr], radial index fastest.
+//
+// Bound: FP64 VALU issue, 2 to 20 instructions for each operation, about 3100 a
+// strip-row with double-double weights (4170 with accurate sums, IEEE reciprocals and
+// normalised products everywhere).  How many waves a SIMD gets one after the other
+// decides small grids: with all four planes in one wave, 2048 x 64 gave some SIMDs
+// three of them and most two.  2048 x 64 with double-double weights 83.0 -> 50.7 us a
+// step, with FP64 weights 57.4 -> 46.0; 100 x 20 32.5 -> 13.5; 9000 x 300 1217 -> 911
+// and 848 -> 816.
 #include <hip/hip_runtime.h>
 
 #include "teuk_dd_tables.h"
+#include "teuk_device.h"
 #include "teuk_internal.h"
 
 #pragma clang fp contract(off)
@@ -88,12 +98,56 @@ __device__ __forceinline__ dd dd_mul(dd x, dd y)
     return fast_two_sum(c.hi, c.lo + cl2);
 }
 
-// 1/y: t = fl(1/y.hi), e = 1 - y t (exact up to 2u^2), 1/y = t (1 + e + e^2 + ...)
+// x + y with an error of u^2 (|x| + |y|) instead of 3u^2 |x + y|: for terms of one
+// sign, and where the operands' own errors are as large
+__device__ __forceinline__ dd dd_add_s(dd x, dd y)
+{
+    const dd s = two_sum(x.hi, y.hi);
+    return fast_two_sum(s.hi, s.lo + (x.lo + y.lo));
+}
+__device__ __forceinline__ dd dd_sub_s(dd x, dd y) { return dd_add_s(x, dd_neg(y)); }
+
+// x^2 and x y as pairs whose low words are not normalised (a few u of the high one)
+__device__ __forceinline__ dd sq_raw(dd x)
+{
+    const dd c = two_prod(x.hi, x.hi);
+    return {c.hi, fma(x.hi + x.hi, x.lo, fma(x.lo, x.lo, c.lo))};
+}
+__device__ __forceinline__ dd mul_raw(dd x, double y)
+{
+    const dd c = two_prod(x.hi, y);
+    return {c.hi, fma(x.lo, y, c.lo)};
+}
+
+__device__ __forceinline__ dd mul_raw(dd x, dd y)
+{
+    const dd c = two_prod(x.hi, y.hi);
+    return {c.hi, fma(x.hi, y.lo, fma(x.lo, y.hi, fma(x.lo, y.lo, c.lo)))};
+}
+
+// A running sum of products: the high words summed by TwoSum, everything below
+// them in one low word, normalised once at the end.  Its error is a few u^2 of the
+// sum of the terms' sizes, as is that of products rounded one by one.
+struct Acc {
+    double s, l;
+    __device__ __forceinline__ void add(dd x)
+    {
+        const dd t = two_sum(s, x.hi);
+        s = t.hi;
+        l += t.lo + x.lo;
+    }
+    __device__ __forceinline__ dd get() const { return fast_two_sum(s, l); }
+};
+__device__ __forceinline__ Acc acc(dd x) { return {x.hi, x.lo}; }
+
+// 1/y: t = 1/y.hi to a unit or two of its last place (hardware estimate and two Newton
+// steps), e = 1 - y t (1 - y.hi t is exact to 2u^2), 1/y = t (1 + e + e^2 + ...)
 __device__ __forceinline__ dd dd_recip(dd y)
 {
-    const double t = 1.0 / y.hi;
-    const dd p = dd_mul_d(y, t);
-    const double e = (1.0 - p.hi) - p.lo;
+    double t = __builtin_amdgcn_rcp(y.hi);
+    t = fma(t, fma(-y.hi, t, 1.0), t);
+    t = fma(t, fma(-y.hi, t, 1.0), t);
+    const double e = fma(-y.lo, t, fma(-y.hi, t, 1.0));
     return fast_two_sum(t, t * fma(e, e, e));
 }
 
@@ -112,8 +166,11 @@ __device__ __forceinline__ dd shfl_down1(dd v)
     return {__shfl_down(v.hi, 1, 64), __shfl_down(v.lo, 1, 64)};
 }
 
+// x y + z w
+__device__ __forceinline__ dd two_products(dd x, dd y, dd z, dd w) { return dd_add(dd_mul(x, y), dd_mul(z, w)); }
+
 struct DDK {
-    dd inv_dx, ih1, ih2, ca, cb, sixth, c13_3, d[3];
+    dd inv_dx, ih1, ih2, ca, cb, sixth, eps12;
 };
 
 // Mixed weights (Sec. 3.1.3): the stencil rounded to double, IS_k, alpha_k,
@@ -152,51 +209,70 @@ __device__ __forceinline__ void w64_minus(const double g[5], double eps, double&
 //     6 (q_0 - f_2) = 5 g_1 - 2 g_0,  6 (q_1 - f_2) = g_1 + 2 g_2,  6 (q_2 - f_2) = 4 g_2 - g_3,
 // and the smoothness indicators 4 IS_k = (13/3) d_k^2 + e_k^2 with
 //     d_0 = g_1 - g_0, d_1 = g_2 - g_1, d_2 = g_3 - g_2,
-//     e_0 = 3 g_1 - g_0, e_1 = -(g_1 + g_2), e_2 = g_3 - 3 g_2
-// (identities of the printed formulas).  WM = 1: omega_0, omega_1 given in
-// double, omega_2 = 1 - omega_0 - omega_1 in double-double.
+//     e_0 = 3 g_1 - g_0 = d_0 + 2 g_1, e_1 = g_1 + g_2, e_2 = g_3 - 3 g_2 = d_2 - 2 g_2
+// (identities of the printed formulas; e_1 enters squared).  With double-double
+// weights the differences of the g_i are formed by the short sum: an error of u^2 |g|
+// in them is one of u^2 in IS_k, whose square root is at least of the size of the g_i
+// that enter it, and the candidates carry as much from the g_i themselves.  WM = 1: omega_0, omega_1 given in double, omega_2 = 1 - omega_0 -
+// omega_1 in double-double.
 template <int WM>
-__device__ __forceinline__ dd weno(dd f0, dd f1, dd f2, dd f3, dd f4, const DDK& K, double eps, double w0d,
-                                   double w1d)
+__device__ __forceinline__ dd weno(dd f0, dd f1, dd f2, dd f3, dd f4, const DDK& K, double w0d, double w1d)
 {
     const dd g0 = dd_sub(f1, f0), g1 = dd_sub(f2, f1);
     const dd g2 = dd_sub(f3, f2), g3 = dd_sub(f4, f3);
-    const dd A = dd_sub(dd_mul_d(g1, 5.0), dd_scale(g0, 2.0));
-    const dd B = dd_add(g1, dd_scale(g2, 2.0));
-    const dd C = dd_sub(dd_scale(g2, 4.0), g3);
-    dd s6;
     if constexpr (WM == 1) {
+        const dd A = dd_sub(dd_mul_d(g1, 5.0), dd_scale(g0, 2.0));
+        const dd B = dd_add(g1, dd_scale(g2, 2.0));
+        const dd C = dd_sub(dd_scale(g2, 4.0), g3);
         // 6 (f - f_2) = C + omega_0 (A - C) + omega_1 (B - C)
-        s6 = dd_add(C, dd_add(dd_mul_d(dd_sub(A, C), w0d), dd_mul_d(dd_sub(B, C), w1d)));
+        const dd s6 = dd_add(C, dd_add(dd_mul_d(dd_sub(A, C), w0d), dd_mul_d(dd_sub(B, C), w1d)));
+        return dd_add(f2, dd_mul(s6, K.sixth));
     } else {
-        const dd d0 = dd_sub(g1, g0), d1 = dd_sub(g2, g1), d2 = dd_sub(g3, g2);
-        const dd e0 = dd_sub(dd_mul_d(g1, 3.0), g0);
-        const dd e1 = dd_add(g1, g2);
-        const dd e2 = dd_sub(g3, dd_mul_d(g2, 3.0));
-        // IS_k = ((13/3) d^2 + e^2) / 4; alpha_k = d_k / (eps + IS_k)^2
-        const dd is0 = dd_scale(dd_add(dd_mul(K.c13_3, dd_mul(d0, d0)), dd_mul(e0, e0)), 0.25);
-        const dd is1 = dd_scale(dd_add(dd_mul(K.c13_3, dd_mul(d1, d1)), dd_mul(e1, e1)), 0.25);
-        const dd is2 = dd_scale(dd_add(dd_mul(K.c13_3, dd_mul(d2, d2)), dd_mul(e2, e2)), 0.25);
-        const dd r0 = dd_recip(dd_add_d(is0, eps)), r1 = dd_recip(dd_add_d(is1, eps)), r2 = dd_recip(dd_add_d(is2, eps));
-        const dd a0 = dd_mul(K.d[0], dd_mul(r0, r0));
-        const dd a1 = dd_mul(K.d[1], dd_mul(r1, r1));
-        const dd a2 = dd_mul(K.d[2], dd_mul(r2, r2));
-        const dd inv = dd_recip(dd_add(dd_add(a0, a1), a2));
-        s6 = dd_add(dd_add(dd_mul(dd_mul(a0, inv), A), dd_mul(dd_mul(a1, inv), B)), dd_mul(dd_mul(a2, inv), C));
+        const dd d0 = dd_sub_s(g1, g0), d2 = dd_sub_s(g3, g2);
+        const dd e0 = dd_add_s(d0, dd_scale(g1, 2.0));
+        const dd e1 = dd_add_s(g1, g2);
+        const dd e2 = dd_sub_s(d2, dd_scale(g2, 2.0));
+        const dd A = dd_sub_s(dd_scale(e0, 2.0), g1);
+        const dd B = dd_add_s(e1, g2);
+        const dd C = dd_sub_s(g2, e2);
+        const dd d1 = dd_sub_s(g2, g1);
+        // 1 / (12 (eps + IS_k)), 12 IS_k = 13 d^2 + 3 e^2
+        auto recip_b = [&](dd d, dd e) {
+            Acc b = acc(mul_raw(sq_raw(d), 13.0));
+            b.add(mul_raw(sq_raw(e), 3.0));
+            b.add(K.eps12);
+            return dd_recip(b.get());
+        };
+        // weights times a common factor: alpha = (1, 6, 3) / (12 (eps + IS_k))^2
+        const dd a0 = sq_raw(recip_b(d0, e0));
+        const dd a1 = mul_raw(sq_raw(recip_b(d1, e1)), 6.0);
+        const dd a2 = mul_raw(sq_raw(recip_b(d2, e2)), 3.0);
+        Acc sum = acc(a0);
+        sum.add(a1);
+        sum.add(a2);
+        const dd num = dd_add(two_products(a0, A, a1, B), dd_mul(a2, C));
+        return dd_add(f2, dd_mul(num, dd_recip(dd_mul_d(sum.get(), 6.0))));
     }
-    return dd_add(f2, dd_mul(s6, K.sixth));
 }
+
+// Workgroups of one launch (the threads of a grid are counted in 32 bits).
+constexpr long long kMaxTiles = (1LL << 24) - 1;
 
 template <int WM>
 __global__ __launch_bounds__(256) void dd_stage_kernel(DDStageArgs a, int stage)
 {
+    __shared__ double2 shared[4][64];             // D of the two Phi planes, theta parts of the two pi planes
     const int lane = threadIdx.x & 63;
-    const int k = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (k >= a.nth) return;                       // whole wave
+    const int p = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int q = p & 1;                          // 0 real, 1 imaginary
+    const unsigned tile = (unsigned)xcd_rank((int)blockIdx.x, (int)gridDim.x);
+    const int strip = (int)(tile / (unsigned)a.nth), k = (int)(tile - (unsigned)strip * (unsigned)a.nth);
     const int nr = a.nr;
-    const int j = blockIdx.x * kStripPoints + lane;
+    const int j = strip * kStripPoints + lane;
+    const bool inside = lane < kStripPoints && j < nr;
     const long long plane = a.plane;
     const long long row = (long long)k * nr;
+    const long long i = row + min(j, nr - 1);
     DDK K;
     K.inv_dx = {a.inv_dx[0], a.inv_dx[1]};
     K.ih1 = {a.ih1[0], a.ih1[1]};
@@ -204,85 +280,71 @@ __global__ __launch_bounds__(256) void dd_stage_kernel(DDStageArgs a, int stage)
     K.ca = {a.ca[0], a.ca[1]};
     K.cb = {a.cb[0], a.cb[1]};
     K.sixth = {a.sixth[0], a.sixth[1]};
-    K.c13_3 = {a.c13_3[0], a.c13_3[1]};
-    for (int q = 0; q < 3; ++q) K.d[q] = {a.d[q][0], a.d[q][1]};
+    K.eps12 = two_prod(a.eps, 12.0);
+    auto state = [&](int r) { return (const double2*)a.uk + r * plane; };
+    auto coef = [&](int r) { return ld((const double2*)a.ctab + r * plane, i); };
 
-    // radial derivatives: Phi rows f^+ (speed b > 0), pi rows f^- (speed -b)
-    dd D[4], own[4];
+    // the radial derivative of plane p: f^+ on the Phi rows (speed b > 0, f^+_{j-1/2} from
+    // f_{j-3..j+1}), f^- on the pi rows (speed -b, f^-_{j-1/2} from f_{j+2..j-2}: the f^+
+    // form on the mirrored stencil)
+    dd D, own;
+    {
+        const double2* P = state(p) + row;
+        dd w[5];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const double2* P = (const double2*)a.uk + p * plane + row;
-        dd w[6];
-#pragma unroll
-        for (int t = 0; t < 6; ++t) {
-            int jj = j - 3 + t;
-            jj = jj < 0 ? 0 : (jj > nr - 1 ? nr - 1 : jj);
-            w[t] = ld(P, jj);
-        }
-        own[p] = w[3];
-        dd flux;
+        for (int t = 0; t < 5; ++t) w[t] = ld(P, min(max(p < 2 ? j - 3 + t : j + 2 - t, 0), nr - 1));
+        own = p < 2 ? w[3] : w[2];
         double w0 = 0.0, w1 = 0.0;
-        if (p < 2) {
-            // f^+_{j-1/2} from f_{j-3..j+1}
-            if constexpr (WM == 1) {
+        if constexpr (WM == 1) {
+            if (p < 2) {
                 const double g[5] = {w[0].hi, w[1].hi, w[2].hi, w[3].hi, w[4].hi};
                 w64_plus(g, a.eps, w0, w1);
-            }
-            flux = weno<WM>(w[0], w[1], w[2], w[3], w[4], K, a.eps, w0, w1);
-        } else {
-            // f^-_{j-1/2} from f_{j-2..j+2}: the f^+ form on the mirrored stencil
-            if constexpr (WM == 1) {
-                const double g[5] = {w[1].hi, w[2].hi, w[3].hi, w[4].hi, w[5].hi};
+            } else {
+                const double g[5] = {w[4].hi, w[3].hi, w[2].hi, w[1].hi, w[0].hi};
                 w64_minus(g, a.eps, w0, w1);
             }
-            flux = weno<WM>(w[5], w[4], w[3], w[2], w[1], K, a.eps, w0, w1);
         }
-        const dd right = shfl_down1(flux);
-        D[p] = dd_mul(dd_sub(right, flux), K.inv_dx);
+        const dd flux = weno<WM>(w[0], w[1], w[2], w[3], w[4], K, w0, w1);
+        D = dd_mul(dd_sub(shfl_down1(flux), flux), K.inv_dx);
     }
-    if (lane == 63 || j >= nr) return;
-
-    const long long i = row + j;
-    // theta differences of Phi_R, Phi_I with the pole ghosts
-    dd d1[2], d2[2];
-    for (int p = 0; p < 2; ++p) {
-        const double2* P = (const double2*)a.uk + p * plane;
-        const dd c = own[p];
-        const dd m = k > 0 ? ld(P, i - nr) : (a.parity < 0 ? dd_neg(c) : c);
-        const dd pp = k < a.nth - 1 ? ld(P, i + nr) : (a.parity < 0 ? dd_neg(c) : c);
-        d1[p] = dd_mul(dd_sub(pp, m), K.ih1);
-        d2[p] = dd_mul(dd_add(dd_sub(pp, dd_scale(c, 2.0)), m), K.ih2);
+    dd F;
+    if (p < 2) {
+        // theta differences of this Phi plane with the pole ghosts; F = pi - b D
+        const double2* P = state(p);
+        const dd c = own;
+        const dd ghost = a.parity < 0 ? dd_neg(c) : c;
+        const dd m = k > 0 ? ld(P, i - nr) : ghost;
+        const dd pp = k < a.nth - 1 ? ld(P, i + nr) : ghost;
+        const dd d1 = dd_mul(dd_sub(pp, m), K.ih1);
+        const dd d2 = dd_mul(dd_add(dd_sub(pp, dd_scale(c, 2.0)), m), K.ih2);
+        const dd T = two_products(coef(kDAth), d2, coef(kDBth), d1);
+        shared[q][lane] = make_double2(D.hi, D.lo);
+        shared[2 + q][lane] = make_double2(T.hi, T.lo);
+        lds_sync();
+        F = dd_sub(ld(state(2 + q), i), dd_mul(coef(kDB), D));
+    } else {
+        // F = b D - m3 D_Phi + Bt pi + theta part + C Phi (-lam2 d_x pi = b d_x pi in the
+        // tortoise chart); of a complex product z w the real part is zr wr - zi wi, the
+        // imaginary part zr wi + zi wr, and wave q holds w_q
+        const double sg = q ? 1.0 : -1.0;
+        const dd bp = two_products(coef(kDBtr), own, dd_scale(coef(kDBti), sg), ld(state(3 - q), i));
+        const dd cp = two_products(coef(kDCr), ld(state(q), i), dd_scale(coef(kDCi), sg), ld(state(1 - q), i));
+        F = dd_mul(coef(kDB), D);
+        const dd m3r = coef(kDM3r), m3i = coef(kDM3i);
+        lds_sync();
+        const double2 Dq = shared[q][lane], Do = shared[1 - q][lane], T = shared[2 + q][lane];
+        const dd md = two_products(m3r, {Dq.x, Dq.y}, dd_scale(m3i, sg), {Do.x, Do.y});
+        F = dd_add(dd_add(dd_add(dd_sub(F, md), bp), {T.x, T.y}), cp);
     }
-    const dd b = ld((const double2*)a.ctab + kDB * plane, i);
-    const dd m3r = ld((const double2*)a.ctab + kDM3r * plane, i), m3i = ld((const double2*)a.ctab + kDM3i * plane, i);
-    const dd btr = ld((const double2*)a.ctab + kDBtr * plane, i), bti = ld((const double2*)a.ctab + kDBti * plane, i);
-    const dd cr = ld((const double2*)a.ctab + kDCr * plane, i), ci = ld((const double2*)a.ctab + kDCi * plane, i);
-    const dd ath = ld((const double2*)a.ctab + kDAth * plane, i), bth = ld((const double2*)a.ctab + kDBth * plane, i);
-
-    const dd phR = own[0], phI = own[1], piR = own[2], piI = own[3];
-    const dd mdR = dd_sub(dd_mul(m3r, D[0]), dd_mul(m3i, D[1]));
-    const dd mdI = dd_add(dd_mul(m3r, D[1]), dd_mul(m3i, D[0]));
-    const dd bpR = dd_sub(dd_mul(btr, piR), dd_mul(bti, piI));
-    const dd bpI = dd_add(dd_mul(btr, piI), dd_mul(bti, piR));
-    const dd cpR = dd_sub(dd_mul(cr, phR), dd_mul(ci, phI));
-    const dd cpI = dd_add(dd_mul(cr, phI), dd_mul(ci, phR));
-    dd F[4];
-    F[0] = dd_sub(piR, dd_mul(b, D[0]));
-    F[1] = dd_sub(piI, dd_mul(b, D[1]));
-    // -lam2 d_x pi = b d_x pi in the tortoise chart
-    F[2] = dd_add(dd_add(dd_add(dd_sub(dd_mul(b, D[2]), mdR), bpR), dd_add(dd_mul(ath, d2[0]), dd_mul(bth, d1[0]))), cpR);
-    F[3] = dd_add(dd_add(dd_add(dd_sub(dd_mul(b, D[3]), mdI), bpI), dd_add(dd_mul(ath, d2[1]), dd_mul(bth, d1[1]))), cpI);
-
-    for (int p = 0; p < 4; ++p) {
-        dd v;
-        if (stage == 0) {
-            v = F[p];
-        } else {
-            v = dd_add(own[p], dd_mul_d(F[p], a.dt));
-            if (stage > 1) v = dd_add(dd_mul(K.ca, ld((const double2*)a.un + p * plane, i)), dd_mul(K.cb, v));
-        }
-        st((double2*)a.out + p * plane, i, v);
+    if (!inside) return;
+    dd v;
+    if (stage == 0) {
+        v = F;
+    } else {
+        v = dd_add(own, dd_mul_d(F, a.dt));
+        if (stage > 1) v = dd_add(dd_mul(K.ca, ld((const double2*)a.un + p * plane, i)), dd_mul(K.cb, v));
     }
+    st((double2*)a.out + p * plane, i, v);
 }
 
 __global__ void dd_extract_kernel(const double2* u, long long plane, int nr, int nth, int j_e, double2* slot)
@@ -308,7 +370,9 @@ __global__ void dd_normalise_kernel(double2* u, long long n)
 int launch_dd_stage(const DDStageArgs& a, int stage, int weight_prec, void* stream)
 {
     if (a.nr < 1 || a.nth < 1 || a.nstrips < 1) return (int)hipErrorInvalidValue;
-    const dim3 grid((unsigned)a.nstrips, (unsigned)((a.nth + 3) / 4));
+    const long long tiles = (long long)a.nstrips * a.nth;
+    if (tiles > kMaxTiles) return (int)hipErrorInvalidValue;
+    const dim3 grid((unsigned)tiles);
     if (weight_prec == TEUK_W_FP64)
         hipLaunchKernelGGL(dd_stage_kernel<1>, grid, dim3(256), 0, (hipStream_t)stream, a, stage);
     else
