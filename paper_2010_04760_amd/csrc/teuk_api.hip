@@ -52,7 +52,7 @@ struct teuk_solver {
     int nstrips = 0;
     int segs[2] = {0, 0};                           // theta segments per strip: stage 1, stages 2-3
     int bstrips = 0, bgrid = 0;                     // temporal blocking: radial strips, workgroups per launch
-    bool fused = false;                             // TEUK_RK_SSP33 stepped by the temporally blocked launch
+    bool fused = false;                             // stepped by temporally blocked launches (fused_step)
     long long plane = 0;
     long long steps = 0, samples = 0;
     bool have_init = false;
@@ -288,8 +288,9 @@ int pick_segs(const teuk_config& c, int nstrips, int weight_prec, bool first)
 // Whether SSP-RK(3,3) steps of c are taken by the temporally blocked launch (one
 // launch and 64 B of traffic per point-step) instead of three stage launches (256 B):
 // wherever that kernel is built -- FP64 state, WENO5, second-order theta
-// differences -- unless the caller asks for a
-// budget of stage workgroups or the tuner found the stage launches faster.  The
+// differences -- unless the caller asks for a budget of stage workgroups or the
+// tuner found the stage launches faster; SSP-RK(10,4) steps with FP64 and FP32
+// weights likewise by four such launches instead of ten (figures beside them).  The
 // results are the same to the bit.  Both measured, us a step, FP64 weights:
 // 16384 x 512 284 against 472, 8192 x 256 74.9 against 98, 4099 x 131 28.5
 // against 35.8, 2050 x 97 17.9 against 23.5, 1024 x 64 12.3 against 14.0, 512 x 32
@@ -304,7 +305,8 @@ bool fused_step(const teuk_config& c)
 {
     const bool heavy = c.weight_prec == TEUK_W_BF16 && c.chart == TEUK_CHART_TORTOISE &&
                        (long long)c.nr * c.ntheta > (1LL << 20);
-    return c.integrator == TEUK_RK_SSP33 && c.state_prec == TEUK_S_FP64 && c.scheme == TEUK_SCHEME_WENO5 &&
+    const bool rk104 = c.integrator == TEUK_RK_SSP104 && c.weight_prec <= TEUK_W_FP32;
+    return (c.integrator == TEUK_RK_SSP33 || rk104) && c.state_prec == TEUK_S_FP64 && c.scheme == TEUK_SCHEME_WENO5 &&
            c.theta_order != 4 && c.workgroups == 0 && !heavy && !tuned_stage_launches(c);
 }
 
@@ -758,7 +760,13 @@ teuk_status teuk_create(const teuk_config* cfg, const teuk_device_ctx* ctx, teuk
         }
     }
     h->fused = fused_step(*cfg);
-    if ((h->fused || cfg->integrator == TEUK_RK_SSP33_BLOCKED) &&
+    const bool rk104 = cfg->integrator == TEUK_RK_SSP104;
+    if (h->fused && rk104 &&
+        (part_grid(2, cfg->weight_prec, cfg->chart) < 1 || part_grid(3, cfg->weight_prec, cfg->chart) < 1)) {
+        free_solver(h);
+        return fail(nullptr, TEUK_ERR_UNSUPPORTED, "temporal blocking: occupancy query failed");
+    }
+    if (((h->fused && !rk104) || cfg->integrator == TEUK_RK_SSP33_BLOCKED) &&
         !blocked_shape(*cfg, h->fused ? 0 : eff.workgroups, &h->bstrips, &h->bgrid)) {
         free_solver(h);
         return fail(nullptr, TEUK_ERR_UNSUPPORTED, "temporal blocking: occupancy query failed");
@@ -1004,11 +1012,38 @@ static int rk3_step(teuk_solver* h, StageArgs& a, int64_t k, int64_t n, bool kee
 // into A and q = 1/25 u^n + 9/25 v over U (v = u(4) + dt/6 F(u(4)), u^n read at
 // the own point only); stages 6-9 ping-pong A -> B -> A -> B -> A (= u(9));
 // stage 10 writes u^{n+1} = q + 3/5 (u(9) + dt/6 F(u(9))) over U.
+//
+// Fused (h->fused): the same arithmetic in four launches, stages 1-3 U -> A, 4-5
+// A -> B (and q over U), 6-8 B -> A, 9-10 A -> U.
 static int rk104_step(teuk_solver* h, StageArgs a)
 {
     double* U = h->u[0];
     double* AB[2] = {h->u[1], h->u[2]};
     a.dt = h->dt / 6.0;
+    if (h->fused) {
+        const int wp = h->cfg.weight_prec, chart = h->cfg.chart;
+        a.un = U;
+        a.uk = U;
+        a.out = AB[0];
+        int f = launch_blocked_part(a, 3, wp, chart, h->stream);
+        a.uk = AB[0];
+        a.out = AB[1];
+        a.ca = 3.0 / 5.0;
+        a.cb = 2.0 / 5.0;
+        a.out2 = U;
+        a.ca2 = 1.0 / 25.0;
+        a.cb2 = 9.0 / 25.0;
+        if (!f) f = launch_blocked_part(a, 2, wp, chart, h->stream);
+        a.out2 = nullptr;
+        a.uk = AB[1];
+        a.out = AB[0];
+        if (!f) f = launch_blocked_part(a, 3, wp, chart, h->stream);
+        a.uk = AB[0];
+        a.out = U;
+        a.ca = 1.0;
+        a.cb = 3.0 / 5.0;
+        return f ? f : launch_blocked_part(a, 2, wp, chart, h->stream);
+    }
     a.segs = h->segs[0];
     a.grid = h->nstrips * h->segs[0];
     a.ca = 0.0;

@@ -28,12 +28,22 @@ namespace {
 // never stored).  Stage 1 is valid on points 0 .. 125, stage 2 on 3 .. 122 and
 // stage 3 (the output) on 6 .. 119: 114 outputs per 128 lanes.
 constexpr int kBW = kBlockedPoints;      // output points per tile
-constexpr int kBLead = 6;                // first output point of a tile
 constexpr int kBPts = 2 * kWave - 1;     // points of a tile (the waves share one)
 constexpr int kBStage = kBPts + 6;       // staged u^n positions: q - 3 .. q + 3 of every point
 constexpr int kBHalf = 2 * kWave;        // threads of one half
 constexpr int kBThreads = 2 * kBHalf;    // two halves
-static_assert(kBLead + kBW + kBLead + 1 == kBPts, "tile geometry");
+constexpr int blocked_lead(int stages) { return 3 * (stages - 1); }            // first output point of a tile
+constexpr int blocked_width(int stages) { return kBPts - 1 - 2 * blocked_lead(stages); }
+static_assert(blocked_width(3) == kBW, "tile geometry");
+
+// What the stages of a launch do.
+enum BlockedKind : int {
+    kBStep = 0,      // the three of an SSP-RK(3,3) step
+    kBEuler3 = 1,    // three of the form v + dt F(v)
+    kBLast2 = 2,     // one of that form and one that combines with u^n: out = ca u^n + cb (v + dt F(v)),
+                     // and out2 = ca2 u^n + cb2 (...) if there is an out2, either of which may be u^n's own
+                     // buffer (u^n is read at the own point only)
+};
 
 // Along theta a tile of rows [k0, k1) is marched by two such pairs of waves from
 // its middle row kb outwards: half 1 takes kb, kb + 1, ... and half 0 kb - 1,
@@ -109,11 +119,23 @@ __device__ __forceinline__ void row_put(double* row, unsigned off, double v)
     *(__attribute__((address_space(1))) double*)(scalar(row) + off) = v;
 }
 
+// The four launches of an SSP-RK(10,4) step are made of the same parts: stages 1-3
+// and 6-8 in one launch each (kBEuler3: three stages without u^n in them), 4-5 and
+// 9-10 in one each (kBLast2: two stages, 120 outputs per tile, u^n read from memory
+// for the second).  The split 3 + 2 + 3 + 2 lets the combining stages be the last of
+// their launch, so that u^n is read at the own point alone and q = (u^n + 9 u(5)) / 25
+// can take its buffer.  Ten stage launches took 188 us a step of 4096 x 256, these
+// four 152; 1000 x 100 51 -> 40, 150 x 8 37 -> 27, 16384 x 180 475 -> 374, chart H
+// 4096 x 256 289 -> 166, FP32 weights 4099 x 131 124 -> 104.  (The two-stage launch at
+// three waves per SIMD, which its LDS would allow, spills 108 B a lane: 171 us.)
+//
 // Rows [k0, k1) of radial strip `strip` of one solve.  (Every wave of the workgroup
 // calls it with the same arguments.)
-template <int WP, bool kBtFirst, bool kHyp>
+template <int WP, bool kBtFirst, bool kHyp, int kKind = kBStep>
 __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, int strip, int k0, int k1)
 {
+    constexpr int kStages = kKind == kBLast2 ? 2 : 3;
+    constexpr int kWidth = blocked_width(kStages), kLead = blocked_lead(kStages);
     const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBHalf);
     const int tid = (int)threadIdx.x - half * kBHalf;
     const int l = tid - (tid >= kWave ? 1 : 0);          // point of this lane in the tile
@@ -133,10 +155,10 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
     const int n = half ? n1 : n0;
     const int first = half ? kb : kb - 1;
     const int lim = half ? nth - kb : kb;             // grid rows from `first` on, in this half's direction
-    const int N1 = min(n + 2, lim), N2 = min(n + 1, lim), NS = min(N1 + 1, lim);
-    const int steps = max(n0, n1) + 2;
+    const int N1 = min(n + kStages - 1, lim), N2 = min(n + kStages - 2, lim), NS = min(N1 + 1, lim);
+    const int steps = max(n0, n1) + kStages - 1;
 
-    const int p0 = strip * kBW - kBLead;              // grid point of tile point 0
+    const int p0 = strip * kWidth - kLead;            // grid point of tile point 0
     const int j = p0 + l;
     const unsigned oc = (unsigned)clampi(j, 0, nr - 1) * 8u;
     const unsigned oa = (unsigned)clampi(p0 - 3 + tid, 0, nr - 1) * 8u;            // staged position tid
@@ -150,7 +172,7 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
     const LdsDouble own = lds_at(lds + kBS1 + half * 4 * 3 * kBPts + l);
     const LdsDouble across = lds_at(lds + kBS1 + (half ^ 1) * 4 * 3 * kBPts + l);
     const LdsDouble rows = lds_at(lds + half * 4 * 3 * kBStage + l), put = lds_at(lds + half * 4 * 3 * kBStage + tid);
-    const bool out_lane = !dup && l >= kBLead && l < kBLead + kBW && j < nr;
+    const bool out_lane = !dup && l >= kLead && l < kLead + kWidth && j < nr;
     Radial rt;
     if constexpr (!kHyp) rt = load_radial(A, oc);
 
@@ -298,6 +320,13 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
     auto step = [&](auto phase, int i) {
         constexpr int c0 = decltype(phase)::value, c1 = (c0 + 1) % 3, c2 = (c0 + 2) % 3;
         lds_sync();
+        double un2[4];                   // two-stage launch: u^n at the own point on row i - 1
+        const bool last2 = kKind == kBLast2 && i >= 1 && i - 1 < n;
+        if (last2 && out_lane) {
+            const size_t row = (size_t)(first + dir * (i - 1)) * nr;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) un2[p] = row_get(A.un + p * P + row, oc);
+        }
         if (i < N1) {
             // ---- stage 1 at row i: u(1) = u^n + dt F(u^n)
             __builtin_amdgcn_s_setprio(3);
@@ -322,8 +351,10 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
 #pragma unroll
                 for (int p = 0; p < 4; ++p) own[(p * 3 + c0) * kBPts] = o.v[p];
             }
+            if constexpr (kKind == kBStep) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) un[c0][p] = w[p][3];
+                for (int p = 0; p < 4; ++p) un[c0][p] = w[p][3];
+            }
             b0R = w[0][3];
             b0I = w[1][3];
             a1R = o.v[0];
@@ -342,22 +373,36 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
             double w[4][6];
             const Diffs f = fluxes([&](int p, int t) { return lds_get(q[t], (p * 3 + c2) * kBPts); }, w, pc[c2]);
             const Four o = finish(f, w, a1R, a1I, b1R, b1I, pc[c2]);
-            Four u2;
+            if constexpr (kKind == kBLast2) {
+                if (out_lane) {
+                    const size_t row = (size_t)(first + dir * (i - 1)) * nr;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) u2.v[p] = combine(0.75, un[c2][p], 0.25, o.v[p]);
-            if (!dup) {
+                    for (int p = 0; p < 4; ++p) row_put(outp[p] + row, oc, combine(A.ca, un2[p], A.cb, o.v[p]));
+                    if (A.out2) {
 #pragma unroll
-                for (int p = 0; p < 4; ++p) own[kBS2 + (p * 3 + c2) * kBPts] = u2.v[p];
+                        for (int p = 0; p < 4; ++p) row_put(A.out2 + p * P + row, oc, combine(A.ca2, un2[p], A.cb2, o.v[p]));
+                    }
+                }
+            } else {
+                Four u2 = o;
+                if constexpr (kKind == kBStep) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) u2.v[p] = combine(0.75, un[c2][p], 0.25, o.v[p]);
+                }
+                if (!dup) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) own[kBS2 + (p * 3 + c2) * kBPts] = u2.v[p];
+                }
+                a2R = u2.v[0];
+                a2I = u2.v[1];
             }
-            a2R = u2.v[0];
-            a2I = u2.v[1];
             b1R = w[0][3];
             b1I = w[1][3];
         } else {
             a2R *= A.parity;
             a2I *= A.parity;
         }
-        if (i >= 2 && i - 2 < n) {
+        if (kStages == 3 && i >= 2 && i - 2 < n) {
             // ---- stage 3 at row i - 2: u^{n+1} = 1/3 u^n + 2/3 (u(2) + dt F(u(2)))
             __builtin_amdgcn_s_setprio(2);
             if (c0 == 2 && i == 2) {
@@ -370,7 +415,8 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
             if (out_lane) {
                 const size_t row = (size_t)(first + dir * (i - 2)) * nr;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) row_put(outp[p] + row, oc, combine(1.0 / 3.0, un[c1][p], 2.0 / 3.0, o.v[p]));
+                for (int p = 0; p < 4; ++p)
+                    row_put(outp[p] + row, oc, kKind == kBStep ? combine(1.0 / 3.0, un[c1][p], 2.0 / 3.0, o.v[p]) : o.v[p]);
             }
             b2R = w[0][3];
             b2I = w[1][3];
@@ -398,6 +444,7 @@ __device__ __forceinline__ void blocked_tile(const StageArgs& A, double* lds, in
 // pairs of reads merged by the compiler would need an address of their own
 // each (20 VALU instructions a step).
 constexpr int kBLds = 2 * 4 * 3 * (kBStage + 2 * kBPts);
+constexpr int kBLds2 = 2 * 4 * 3 * (kBStage + kBPts);      // two stages
 
 // Strip-rows [at, end) of a rank: `share`, and one more for the first `extra` ranks
 // (a grid has at most 2^34 / 114 + 2^16 strip-rows, a launch less than 2^31).
@@ -421,6 +468,23 @@ __global__ __launch_bounds__(kBThreads, 2) void blocked_step_kernel(StageArgs A,
         at += (unsigned)(k1 - k0);
         blocked_tile<WP, kBtFirst, kHyp>(A, lds, strip, k0, k1);
         lds_sync();   // before the next tile's rows go into the rings
+    }
+}
+
+// Stages of an SSP-RK(10,4) step (the same walk over the strip-rows).
+template <int WP, bool kHyp, int kKind>
+__global__ __launch_bounds__(kBThreads, 2) void blocked_part_kernel(StageArgs A, unsigned share, unsigned extra)
+{
+    __shared__ double lds[kKind == kBLast2 ? kBLds2 : kBLds];
+    unsigned at, end;
+    share_of(share, extra, at, end);
+    while (at < end) {
+        const int strip = (int)(at / (unsigned)A.nth);
+        const int k0 = (int)(at - (unsigned)strip * (unsigned)A.nth);
+        const int k1 = min(k0 + (int)(end - at), A.nth);
+        at += (unsigned)(k1 - k0);
+        blocked_tile<WP, bt_first<WP>(), kHyp, kKind>(A, lds, strip, k0, k1);
+        lds_sync();
     }
 }
 
@@ -509,6 +573,51 @@ int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own
 #undef TEUK_BLAUNCH
     if (!done) return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
+}
+
+// The kernel of a part, or null.
+static const void* part_kernel(int stages, int weight_prec, int chart)
+{
+#define TEUK_PART(W, H)                                                                        \
+    if (weight_prec == W && chart == (H ? TEUK_CHART_HYPERBOLOIDAL : TEUK_CHART_TORTOISE))     \
+        return stages == 3 ? (const void*)blocked_part_kernel<W, H, kBEuler3>                  \
+                           : (const void*)blocked_part_kernel<W, H, kBLast2>;
+    TEUK_PART(TEUK_W_FP64, false)
+    TEUK_PART(TEUK_W_FP64, true)
+    TEUK_PART(TEUK_W_FP32, false)
+    TEUK_PART(TEUK_W_FP32, true)
+#undef TEUK_PART
+    return nullptr;
+}
+
+int part_grid(int stages, int weight_prec, int chart)
+{
+    static ResidentCache cache[2][2][2];
+    int dev = 0;
+    const void* fn = stages == 2 || stages == 3 ? part_kernel(stages, weight_prec, chart) : nullptr;
+    if (!fn || hipGetDevice(&dev) != hipSuccess) return 0;
+    return cache[stages - 2][weight_prec == TEUK_W_FP32][chart == TEUK_CHART_HYPERBOLOIDAL].get(dev, [&] {
+        int cus = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBThreads, 0) != hipSuccess)
+            return 0;
+        return cus * per_cu;
+    });
+}
+
+int launch_blocked_part(StageArgs a, int stages, int weight_prec, int chart, void* stream)
+{
+    const int resident = part_grid(stages, weight_prec, chart);
+    if (resident < 1 || a.nr < 1 || a.nth < 2 || a.uk == a.out || a.uk == a.out2) return (int)hipErrorInvalidValue;
+    a.nstrips = (a.nr + blocked_width(stages) - 1) / blocked_width(stages);
+    const long long rows = (long long)a.nstrips * a.nth;
+    if (rows > (1LL << 31) - 1) return (int)hipErrorInvalidValue;
+    a.grid = (int)(rows < resident ? rows : resident);
+    unsigned share = (unsigned)rows / (unsigned)a.grid, extra = (unsigned)rows % (unsigned)a.grid;
+    void* args[] = {&a, &share, &extra};
+    (void)hipGetLastError();
+    return (int)hipLaunchKernel(part_kernel(stages, weight_prec, chart), dim3((unsigned)a.grid), dim3(kBThreads), args, 0,
+                                (hipStream_t)stream);
 }
 
 int launch_group_blocked(const StageArgs* args, const unsigned* start, int nmem, long long rows, int weight_prec,

@@ -138,6 +138,14 @@ int launch_coef_dump(const double* rtab, const double* ttab, const double* ctab,
 constexpr int kBlockedPoints = 114;
 int blocked_grid(int weight_prec, int chart);
 int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own_order, void* stream);
+// Consecutive stages of an SSP-RK(10,4) step in one launch, from a.uk into a.out
+// (a.nstrips and a.grid are set here): stages == 3, three of the form v + dt F(v);
+// stages == 2, one of that form and one out = ca un + cb (v + dt F(v)), with out2 =
+// ca2 un + cb2 (v + dt F(v)) if a.out2 is set (out and out2 may alias un, not uk).
+// part_grid: resident workgroups, 0 where the kernel is not built (FP64 and FP32
+// weights, second-order theta differences).
+int part_grid(int stages, int weight_prec, int chart);
+int launch_blocked_part(StageArgs a, int stages, int weight_prec, int chart, void* stream);
 // The same step of several solves (device arrays): args[0..nmem) with nstrips in
 // strips of kBlockedPoints, start[0..nmem] the prefix sums of their strip-rows
 // (nstrips * nth each), rows = start[nmem].

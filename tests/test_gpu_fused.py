@@ -67,6 +67,26 @@ def test_hyperboloidal_equals_stage_launches(nr, nth, a, x_min, wp):
             np.testing.assert_array_equal(p, q)
 
 
+@pytest.mark.parametrize("wp", ["fp64", "fp32"])
+@pytest.mark.parametrize("nr,nth,chart", [(7, 2, "T"), (114, 2, "T"), (115, 3, "T"), (120, 5, "T"), (121, 7, "T"),
+                                          (500, 200, "T"), (7, 3, "H"), (121, 2, "H"), (300, 25, "H")])
+def test_ssprk104_equals_stage_launches(nr, nth, chart, wp):
+    """Ten stages in four launches (114 outputs a tile in two of them, 120 in the others)."""
+    print("case fused rk104", nr, nth, chart, wp, flush=True)
+    kw = dict(s=-2, m=1, a=0.9, nr=nr, ntheta=nth, weight_prec=wp, integrator="rk104", extract_every=2, max_samples=8,
+              x_extract=5.0)
+    kw.update(dict(x_min=-30.0, x_max=50.0) if chart == "T" else dict(chart="H", a=0.8, x_min=1.2, x_max=19.0))
+    u0 = W.random_state(nr, nth, seed=nr, smooth=True)
+    with T.Solver(T.make_config(**kw)) as x, T.Solver(T.make_config(workgroups=2 * (-(-nr // 63)), **kw)) as y:
+        x.set_initial(u0)
+        y.set_initial(u0)
+        for n in (1, 2, 4):
+            x.step(n)
+            y.step(n)
+            np.testing.assert_array_equal(x.state(), y.state())
+        np.testing.assert_array_equal(x.waveform()[1], y.waveform()[1])
+
+
 @pytest.mark.parametrize("chunk", [1, 3, 5, 4])
 def test_odd_graph_chunks(chunk):
     print("case fused graph", chunk, flush=True)
