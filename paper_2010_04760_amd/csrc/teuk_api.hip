@@ -957,6 +957,14 @@ static void rk3_stage(const teuk_solver* h, StageArgs& a, int stage)
     a.grid = h->nstrips * a.segs;
 }
 
+// A temporally blocked SSP-RK(3,3) step by the launch that suits the grid.
+static int launch_fused_step(const StageArgs& a, int weight_prec, int chart, hipStream_t stream)
+{
+    const int rows = thin_rows(a.nr, a.nth);
+    return rows > 0 ? launch_thin_step(a, rows, weight_prec, chart, stream)
+                    : launch_blocked_step(a, weight_prec, chart, false, stream);
+}
+
 // One temporally blocked SSP-RK(3,3) step of h on `stream`: u^n in u[0], u^{n+1}
 // written to u[1], then the two buffers trade roles.
 static int blocked_step_once(teuk_solver* h, hipStream_t stream)
@@ -969,7 +977,9 @@ static int blocked_step_once(teuk_solver* h, hipStream_t stream)
     a.uk = h->u[0];
     a.un = h->u[0];
     a.out = h->u[1];
-    const int e = launch_blocked_step(a, h->cfg.weight_prec, h->cfg.chart, h->cfg.integrator == TEUK_RK_SSP33_BLOCKED, stream);
+    const int e = h->cfg.integrator == TEUK_RK_SSP33_BLOCKED
+                      ? launch_blocked_step(a, h->cfg.weight_prec, h->cfg.chart, true, stream)
+                      : launch_fused_step(a, h->cfg.weight_prec, h->cfg.chart, stream);
     if (!e) std::swap(h->u[0], h->u[1]);             // u^{n+1} is the new state buffer
     return e;
 }
@@ -2134,7 +2144,7 @@ extern "C" teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int6
             if ((nsteps & 1) && n == 1) to = u2;
             a.uk = a.un = at;
             a.out = to;
-            e = launch_blocked_step(a, cfg->weight_prec, cfg->chart, false, st);
+            e = launch_fused_step(a, cfg->weight_prec, cfg->chart, st);
             at = to;
         }
         if (e) return fail(nullptr, TEUK_ERR_DEVICE, std::string("blocked step launch: ") + hipGetErrorString((hipError_t)e));

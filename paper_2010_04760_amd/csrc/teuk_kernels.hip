@@ -26,6 +26,7 @@
 #include <cstdint>
 
 #include "teuk_blocked.h"
+#include "teuk_thin.h"
 #include "teuk_coef.h"
 #include "teuk_device.h"
 #include "teuk_internal.h"

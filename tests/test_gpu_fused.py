@@ -67,6 +67,22 @@ def test_hyperboloidal_equals_stage_launches(nr, nth, a, x_min, wp):
             np.testing.assert_array_equal(p, q)
 
 
+@pytest.mark.parametrize("wp", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("nr,nth", [(51, 2), (52, 5), (102, 256), (103, 257), (700, 230), (653, 24), (3000, 130),
+                                    (8192, 40)])
+def test_low_tiles_and_marched_tiles(nr, nth, wp):
+    """Around the 51 points of the low tiles, from one row a tile to twelve, with a last
+    tile of fewer rows; the last two sizes are marched."""
+    a, b, _ = pair(nr, nth, wp)
+    print("case fused tiles", nr, nth, wp, flush=True)
+    for n in (1, 2):
+        a.step(n)
+        b.step(n)
+        np.testing.assert_array_equal(a.state(), b.state())
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("wp", ["fp64", "fp32"])
 @pytest.mark.parametrize("nr,nth,chart", [(7, 2, "T"), (114, 2, "T"), (115, 3, "T"), (120, 5, "T"), (121, 7, "T"),
                                           (500, 200, "T"), (7, 3, "H"), (121, 2, "H"), (300, 25, "H")])
