@@ -290,7 +290,8 @@ int pick_segs(const teuk_config& c, int nstrips, int weight_prec, bool first)
 // wherever that kernel is built -- FP64 state, WENO5, second-order theta
 // differences -- unless the caller asks for a budget of stage workgroups or the
 // tuner found the stage launches faster; SSP-RK(10,4) steps with FP64 and FP32
-// weights likewise by four such launches instead of ten (figures beside them).  The
+// weights likewise by four such launches instead of ten, and fourth-order theta
+// differences on the grids that the low tiles take (figures beside them).  The
 // results are the same to the bit.  Both measured, us a step, FP64 weights:
 // 16384 x 512 284 against 472, 8192 x 256 74.9 against 98, 4099 x 131 28.5
 // against 35.8, 2050 x 97 17.9 against 23.5, 1024 x 64 12.3 against 14.0, 512 x 32
@@ -307,7 +308,7 @@ bool fused_step(const teuk_config& c)
                        (long long)c.nr * c.ntheta > (1LL << 20);
     const bool rk104 = c.integrator == TEUK_RK_SSP104 && c.weight_prec <= TEUK_W_FP32;
     return (c.integrator == TEUK_RK_SSP33 || rk104) && c.state_prec == TEUK_S_FP64 && c.scheme == TEUK_SCHEME_WENO5 &&
-           c.theta_order != 4 && c.workgroups == 0 && !heavy && !tuned_stage_launches(c);
+           (c.theta_order != 4 || (!rk104 && thin_rows(c.nr, c.ntheta, 4) > 0)) && c.workgroups == 0 && !heavy && !tuned_stage_launches(c);
 }
 
 // Radial strips and workgroups of the temporally blocked launch: a budget of
@@ -960,7 +961,7 @@ static void rk3_stage(const teuk_solver* h, StageArgs& a, int stage)
 // A temporally blocked SSP-RK(3,3) step by the launch that suits the grid.
 static int launch_fused_step(const StageArgs& a, int weight_prec, int chart, hipStream_t stream)
 {
-    const int rows = thin_rows(a.nr, a.nth);
+    const int rows = thin_rows(a.nr, a.nth, chart == kChartTortoise4 ? 4 : 2);
     return rows > 0 ? launch_thin_step(a, rows, weight_prec, chart, stream)
                     : launch_blocked_step(a, weight_prec, chart, false, stream);
 }
@@ -979,7 +980,7 @@ static int blocked_step_once(teuk_solver* h, hipStream_t stream)
     a.out = h->u[1];
     const int e = h->cfg.integrator == TEUK_RK_SSP33_BLOCKED
                       ? launch_blocked_step(a, h->cfg.weight_prec, h->cfg.chart, true, stream)
-                      : launch_fused_step(a, h->cfg.weight_prec, h->cfg.chart, stream);
+                      : launch_fused_step(a, h->cfg.weight_prec, kernel_chart(h->cfg), stream);
     if (!e) std::swap(h->u[0], h->u[1]);             // u^{n+1} is the new state buffer
     return e;
 }
@@ -1035,7 +1036,13 @@ static int rk104_step(teuk_solver* h, StageArgs a)
         a.un = U;
         a.uk = U;
         a.out = AB[0];
-        int f = launch_blocked_part(a, 3, wp, chart, h->stream);
+        // (the launch that suits the grid, as for SSP-RK(3,3))
+        const int rows = thin_rows(a.nr, a.nth, 2);
+        auto part = [&](int stages) {
+            return rows > 0 ? launch_thin_part(a, rows, stages, wp, chart, h->stream)
+                            : launch_blocked_part(a, stages, wp, chart, h->stream);
+        };
+        int f = part(3);
         a.uk = AB[0];
         a.out = AB[1];
         a.ca = 3.0 / 5.0;
@@ -1043,16 +1050,16 @@ static int rk104_step(teuk_solver* h, StageArgs a)
         a.out2 = U;
         a.ca2 = 1.0 / 25.0;
         a.cb2 = 9.0 / 25.0;
-        if (!f) f = launch_blocked_part(a, 2, wp, chart, h->stream);
+        if (!f) f = part(2);
         a.out2 = nullptr;
         a.uk = AB[1];
         a.out = AB[0];
-        if (!f) f = launch_blocked_part(a, 3, wp, chart, h->stream);
+        if (!f) f = part(3);
         a.uk = AB[0];
         a.out = U;
         a.ca = 1.0;
         a.cb = 3.0 / 5.0;
-        return f ? f : launch_blocked_part(a, 2, wp, chart, h->stream);
+        return f ? f : part(2);
     }
     a.segs = h->segs[0];
     a.grid = h->nstrips * h->segs[0];
@@ -2144,7 +2151,7 @@ extern "C" teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int6
             if ((nsteps & 1) && n == 1) to = u2;
             a.uk = a.un = at;
             a.out = to;
-            e = launch_fused_step(a, cfg->weight_prec, cfg->chart, st);
+            e = launch_fused_step(a, cfg->weight_prec, kchart, st);
             at = to;
         }
         if (e) return fail(nullptr, TEUK_ERR_DEVICE, std::string("blocked step launch: ") + hipGetErrorString((hipError_t)e));

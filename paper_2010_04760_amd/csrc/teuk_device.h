@@ -18,6 +18,13 @@ namespace teuk {
 
 namespace {
 
+// Radial chart (TEUK_CHART_*).
+constexpr int kChartT = TEUK_CHART_TORTOISE;
+constexpr int kChartH = TEUK_CHART_HYPERBOLOIDAL;
+// The tortoise chart with fourth-order theta differences (a launch class of
+// its own; the ABI's chart field stays TEUK_CHART_TORTOISE).
+constexpr int kChartT4 = kChartTortoise4;
+
 constexpr int kWave = 64;
 
 __device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }

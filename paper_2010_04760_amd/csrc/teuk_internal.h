@@ -138,11 +138,14 @@ int launch_coef_dump(const double* rtab, const double* ttab, const double* ctab,
 constexpr int kBlockedPoints = 114;
 int blocked_grid(int weight_prec, int chart);
 int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own_order, void* stream);
-// The same step (the stage kernels' order of sums) in tiles of `rows` <= 12 rows by
-// kThinPoints points, one wave a row: for small grids.  thin_rows: the rows to take, 0
+// The same step (the stage kernels' order of sums) in tiles of `rows` rows by
+// 51 points, one wave a row: for small grids.  thin_rows: the rows to take, 0
 // where launch_blocked_step is the better one.
-int thin_rows(int nr, int nth);
+// (chart: the launch class, so fourth-order theta differences as well; those have no
+// marched launch.)  launch_thin_part: launch_blocked_part in such tiles.
+int thin_rows(int nr, int nth, int theta_order);
 int launch_thin_step(const StageArgs& a, int rows, int weight_prec, int chart, void* stream);
+int launch_thin_part(const StageArgs& a, int rows, int stages, int weight_prec, int chart, void* stream);
 // Consecutive stages of an SSP-RK(10,4) step in one launch, from a.uk into a.out
 // (a.nstrips and a.grid are set here): stages == 3, three of the form v + dt F(v);
 // stages == 2, one of that form and one out = ca un + cb (v + dt F(v)), with out2 =

@@ -46,13 +46,6 @@ constexpr int kStageDual = 3;     // v = u^(k) + dt F(u^(k)): out = ca u^n + cb 
 template <int kMode>
 constexpr bool reads_un() { return kMode == kStageLater || kMode == kStageDual; }
 
-// Radial chart (TEUK_CHART_*).
-constexpr int kChartT = TEUK_CHART_TORTOISE;
-constexpr int kChartH = TEUK_CHART_HYPERBOLOIDAL;
-// The tortoise chart with fourth-order theta differences (a launch class of
-// its own; the ABI's chart field stays TEUK_CHART_TORTOISE).
-constexpr int kChartT4 = kChartTortoise4;
-
 // ---------------------------------------------------------------- chart-T row pipeline
 // The tortoise-chart stage streams each theta row of the four planes straight
 // from HBM into a four-row LDS ring with LDS-DMA loads (global_load_lds: every

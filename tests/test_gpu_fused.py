@@ -83,9 +83,23 @@ def test_low_tiles_and_marched_tiles(nr, nth, wp):
     b.close()
 
 
+@pytest.mark.parametrize("wp", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("nr,nth", [(7, 2), (52, 3), (103, 4), (51, 5), (700, 24), (653, 67), (1000, 190)])
+def test_fourth_order_theta_low_tiles(nr, nth, wp):
+    """Poles that reach two rows into a tile, from one row a tile to eight."""
+    a, b, _ = pair(nr, nth, wp, theta_order=4)
+    print("case fused theta4", nr, nth, wp, flush=True)
+    for n in (1, 2, 3):
+        a.step(n)
+        b.step(n)
+        np.testing.assert_array_equal(a.state(), b.state())
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("wp", ["fp64", "fp32"])
 @pytest.mark.parametrize("nr,nth,chart", [(7, 2, "T"), (114, 2, "T"), (115, 3, "T"), (120, 5, "T"), (121, 7, "T"),
-                                          (500, 200, "T"), (7, 3, "H"), (121, 2, "H"), (300, 25, "H")])
+                                          (500, 200, "T"), (3000, 130, "T"), (900, 24, "T"), (7, 3, "H"), (121, 2, "H"), (300, 25, "H")])
 def test_ssprk104_equals_stage_launches(nr, nth, chart, wp):
     """Ten stages in four launches (114 outputs a tile in two of them, 120 in the others)."""
     print("case fused rk104", nr, nth, chart, wp, flush=True)
