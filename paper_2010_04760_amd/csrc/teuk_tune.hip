@@ -203,9 +203,9 @@ teuk_status teuk_tune(const teuk_config* cfg, int32_t steps, teuk_tune_info_t* o
         }
     }
     // the way that solvers of this class step without a budget, where that is
-    // another one than stage launches (SSP-RK(3,3) by the blocked launch)
+    // another one than stage launches (the temporally blocked launches)
     bool stages = false;
-    if (st == TEUK_OK && cfg->integrator == TEUK_RK_SSP33) {
+    if (st == TEUK_OK && (cfg->integrator == TEUK_RK_SSP33 || cfg->integrator == TEUK_RK_SSP104)) {
         {
             std::lock_guard<std::mutex> lock(g_tune_mutex);
             g_tuned.erase(key_of(*cfg, dev));
