@@ -15,20 +15,22 @@
 //     the reciprocal is the double reciprocal corrected by one Newton step
 //     carried to second order in the residual.
 // Work layout: one workgroup of four waves per (63-point radial strip, theta
-// row), one wave for each of the four planes.  Lane l of a strip owns point
+// row), one wave for each of the four planes; workgroups go strip by strip through a
+// row, each XCD through rows of its own (row by row through a strip was 2 % slower on
+// grids that HBM feeds).  Lane l of a strip owns point
 // j = 63 strip + l and computes the interface flux of its wave's plane at
 // j - 1/2; the flux at j + 1/2 comes from lane l + 1.  The Phi waves then form the
 // theta differences and hand them and their radial derivatives to the pi waves,
 // which form the coupled sums meanwhile and wait once.  Values are (hi, lo) pairs
 // stored as double2, [4][ntheta][nr], radial index fastest.
 //
-// Bound: FP64 VALU issue, 2 to 20 instructions for each operation, about 3100 a
-// strip-row with double-double weights (4170 with accurate sums, IEEE reciprocals and
+// Bound: FP64 VALU issue, 2 to 20 instructions for each operation, about 3000 a
+// strip-row with double-double weights (4310 with accurate sums, IEEE reciprocals and
 // normalised products everywhere).  How many waves a SIMD gets one after the other
 // decides small grids: with all four planes in one wave, 2048 x 64 gave some SIMDs
-// three of them and most two.  2048 x 64 with double-double weights 83.0 -> 50.7 us a
-// step, with FP64 weights 57.4 -> 46.0; 100 x 20 32.5 -> 13.5; 9000 x 300 1217 -> 911
-// and 848 -> 816.
+// three of them and most two.  2048 x 64 with double-double weights 82.4 -> 49.3 us a
+// step, with FP64 weights 57.5 -> 44.3; 100 x 20 32.5 -> 13.5; 8192 x 256 898 -> 690
+// and 614 -> 609.
 #include <hip/hip_runtime.h>
 
 #include "teuk_dd_tables.h"
@@ -153,13 +155,25 @@ __device__ __forceinline__ dd dd_recip(dd y)
 
 __device__ __forceinline__ double sqd(double v) { return v * v; }
 
-__device__ __forceinline__ dd ld(const double2* p, long long i)
+// A pair of a row whose address is uniform over the wave (kept in scalar registers, so
+// that an access costs no address arithmetic), at a byte offset within it.
+typedef __attribute__((address_space(1))) char* GlobalChar;
+typedef double Pair __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ GlobalChar scalar(const double2* p)
 {
-    const double2 v = p[i];
+    GlobalChar g = (GlobalChar)const_cast<double2*>(p);
+    asm("" : "+s"(g));
+    return g;
+}
+__device__ __forceinline__ dd ld(const double2* row, unsigned off)
+{
+    const Pair v = *(__attribute__((address_space(1))) const Pair*)(scalar(row) + off);
     return {v.x, v.y};
 }
-
-__device__ __forceinline__ void st(double2* p, long long i, dd v) { p[i] = make_double2(v.hi, v.lo); }
+__device__ __forceinline__ void st(double2* row, unsigned off, dd v)
+{
+    *(__attribute__((address_space(1))) Pair*)(scalar(row) + off) = Pair{v.hi, v.lo};
+}
 
 __device__ __forceinline__ dd shfl_down1(dd v)
 {
@@ -221,12 +235,12 @@ __device__ __forceinline__ dd weno(dd f0, dd f1, dd f2, dd f3, dd f4, const DDK&
     const dd g0 = dd_sub(f1, f0), g1 = dd_sub(f2, f1);
     const dd g2 = dd_sub(f3, f2), g3 = dd_sub(f4, f3);
     if constexpr (WM == 1) {
-        const dd A = dd_sub(dd_mul_d(g1, 5.0), dd_scale(g0, 2.0));
+        const dd A = dd_sub(mul_raw(g1, 5.0), dd_scale(g0, 2.0));
         const dd B = dd_add(g1, dd_scale(g2, 2.0));
         const dd C = dd_sub(dd_scale(g2, 4.0), g3);
         // 6 (f - f_2) = C + omega_0 (A - C) + omega_1 (B - C)
-        const dd s6 = dd_add(C, dd_add(dd_mul_d(dd_sub(A, C), w0d), dd_mul_d(dd_sub(B, C), w1d)));
-        return dd_add(f2, dd_mul(s6, K.sixth));
+        const dd s6 = dd_add(C, dd_add(mul_raw(dd_sub(A, C), w0d), mul_raw(dd_sub(B, C), w1d)));
+        return dd_add(f2, mul_raw(s6, K.sixth));
     } else {
         const dd d0 = dd_sub_s(g1, g0), d2 = dd_sub_s(g3, g2);
         const dd e0 = dd_add_s(d0, dd_scale(g1, 2.0));
@@ -250,8 +264,8 @@ __device__ __forceinline__ dd weno(dd f0, dd f1, dd f2, dd f3, dd f4, const DDK&
         Acc sum = acc(a0);
         sum.add(a1);
         sum.add(a2);
-        const dd num = dd_add(two_products(a0, A, a1, B), dd_mul(a2, C));
-        return dd_add(f2, dd_mul(num, dd_recip(dd_mul_d(sum.get(), 6.0))));
+        const dd num = dd_add(two_products(a0, A, a1, B), mul_raw(a2, C));
+        return dd_add(f2, mul_raw(num, dd_recip(dd_mul_d(sum.get(), 6.0))));
     }
 }
 
@@ -261,18 +275,19 @@ constexpr long long kMaxTiles = (1LL << 24) - 1;
 template <int WM>
 __global__ __launch_bounds__(256) void dd_stage_kernel(DDStageArgs a, int stage)
 {
-    __shared__ double2 shared[4][64];             // D of the two Phi planes, theta parts of the two pi planes
+    __shared__ double2 shared[6][64];             // D of the Phi planes, theta parts and C Phi of the pi planes
     const int lane = threadIdx.x & 63;
     const int p = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int q = p & 1;                          // 0 real, 1 imaginary
     const unsigned tile = (unsigned)xcd_rank((int)blockIdx.x, (int)gridDim.x);
-    const int strip = (int)(tile / (unsigned)a.nth), k = (int)(tile - (unsigned)strip * (unsigned)a.nth);
+    const int k = __builtin_amdgcn_readfirstlane((int)(tile / (unsigned)a.nstrips));
+    const int strip = (int)(tile - (unsigned)k * (unsigned)a.nstrips);
     const int nr = a.nr;
     const int j = strip * kStripPoints + lane;
     const bool inside = lane < kStripPoints && j < nr;
     const long long plane = a.plane;
     const long long row = (long long)k * nr;
-    const long long i = row + min(j, nr - 1);
+    const unsigned at = (unsigned)min(j, nr - 1) * 16u;          // rows are < 2^27 points
     DDK K;
     K.inv_dx = {a.inv_dx[0], a.inv_dx[1]};
     K.ih1 = {a.ih1[0], a.ih1[1]};
@@ -281,18 +296,23 @@ __global__ __launch_bounds__(256) void dd_stage_kernel(DDStageArgs a, int stage)
     K.cb = {a.cb[0], a.cb[1]};
     K.sixth = {a.sixth[0], a.sixth[1]};
     K.eps12 = two_prod(a.eps, 12.0);
-    auto state = [&](int r) { return (const double2*)a.uk + r * plane; };
-    auto coef = [&](int r) { return ld((const double2*)a.ctab + r * plane, i); };
+    auto state = [&](int r) { return (const double2*)a.uk + (r * plane + row); };
+    auto coef = [&](int r) { return ld((const double2*)a.ctab + (r * plane + row), at); };
 
     // the radial derivative of plane p: f^+ on the Phi rows (speed b > 0, f^+_{j-1/2} from
     // f_{j-3..j+1}), f^- on the pi rows (speed -b, f^-_{j-1/2} from f_{j+2..j-2}: the f^+
     // form on the mirrored stencil)
     dd D, own;
     {
-        const double2* P = state(p) + row;
+        const double2* P = state(p);
         dd w[5];
+        if (strip > 0 && (strip + 1) * kStripPoints + 2 < nr) {     // no clamps
 #pragma unroll
-        for (int t = 0; t < 5; ++t) w[t] = ld(P, min(max(p < 2 ? j - 3 + t : j + 2 - t, 0), nr - 1));
+            for (int t = 0; t < 5; ++t) w[t] = ld(P, at + (p < 2 ? t - 3 : 2 - t) * 16);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 5; ++t) w[t] = ld(P, (unsigned)min(max(p < 2 ? j - 3 + t : j + 2 - t, 0), nr - 1) * 16u);
+        }
         own = p < 2 ? w[3] : w[2];
         double w0 = 0.0, w1 = 0.0;
         if constexpr (WM == 1) {
@@ -307,34 +327,37 @@ __global__ __launch_bounds__(256) void dd_stage_kernel(DDStageArgs a, int stage)
         const dd flux = weno<WM>(w[0], w[1], w[2], w[3], w[4], K, w0, w1);
         D = dd_mul(dd_sub(shfl_down1(flux), flux), K.inv_dx);
     }
+    // of a complex product z w the real part is zr wr - zi wi, the imaginary part
+    // zr wi + zi wr, and wave q holds w_q
+    const double sg = q ? 1.0 : -1.0;
     dd F;
     if (p < 2) {
-        // theta differences of this Phi plane with the pole ghosts; F = pi - b D
+        // theta differences of this Phi plane with the pole ghosts, and C Phi (the pi waves'
+        // work without it is about as much); F = pi - b D
         const double2* P = state(p);
         const dd c = own;
         const dd ghost = a.parity < 0 ? dd_neg(c) : c;
-        const dd m = k > 0 ? ld(P, i - nr) : ghost;
-        const dd pp = k < a.nth - 1 ? ld(P, i + nr) : ghost;
+        const dd m = k > 0 ? ld(P - nr, at) : ghost;
+        const dd pp = k < a.nth - 1 ? ld(P + nr, at) : ghost;
         const dd d1 = dd_mul(dd_sub(pp, m), K.ih1);
         const dd d2 = dd_mul(dd_add(dd_sub(pp, dd_scale(c, 2.0)), m), K.ih2);
         const dd T = two_products(coef(kDAth), d2, coef(kDBth), d1);
+        const dd cp = two_products(coef(kDCr), own, dd_scale(coef(kDCi), sg), ld(state(1 - q), at));
         shared[q][lane] = make_double2(D.hi, D.lo);
         shared[2 + q][lane] = make_double2(T.hi, T.lo);
+        shared[4 + q][lane] = make_double2(cp.hi, cp.lo);
         lds_sync();
-        F = dd_sub(ld(state(2 + q), i), dd_mul(coef(kDB), D));
+        F = dd_sub(ld(state(2 + q), at), dd_mul(coef(kDB), D));
     } else {
         // F = b D - m3 D_Phi + Bt pi + theta part + C Phi (-lam2 d_x pi = b d_x pi in the
-        // tortoise chart); of a complex product z w the real part is zr wr - zi wi, the
-        // imaginary part zr wi + zi wr, and wave q holds w_q
-        const double sg = q ? 1.0 : -1.0;
-        const dd bp = two_products(coef(kDBtr), own, dd_scale(coef(kDBti), sg), ld(state(3 - q), i));
-        const dd cp = two_products(coef(kDCr), ld(state(q), i), dd_scale(coef(kDCi), sg), ld(state(1 - q), i));
+        // tortoise chart)
+        const dd bp = two_products(coef(kDBtr), own, dd_scale(coef(kDBti), sg), ld(state(3 - q), at));
         F = dd_mul(coef(kDB), D);
         const dd m3r = coef(kDM3r), m3i = coef(kDM3i);
         lds_sync();
-        const double2 Dq = shared[q][lane], Do = shared[1 - q][lane], T = shared[2 + q][lane];
+        const double2 Dq = shared[q][lane], Do = shared[1 - q][lane], T = shared[2 + q][lane], C = shared[4 + q][lane];
         const dd md = two_products(m3r, {Dq.x, Dq.y}, dd_scale(m3i, sg), {Do.x, Do.y});
-        F = dd_add(dd_add(dd_add(dd_sub(F, md), bp), {T.x, T.y}), cp);
+        F = dd_add(dd_add(dd_add(dd_sub(F, md), bp), {T.x, T.y}), {C.x, C.y});
     }
     if (!inside) return;
     dd v;
@@ -342,9 +365,9 @@ __global__ __launch_bounds__(256) void dd_stage_kernel(DDStageArgs a, int stage)
         v = F;
     } else {
         v = dd_add(own, dd_mul_d(F, a.dt));
-        if (stage > 1) v = dd_add(dd_mul(K.ca, ld((const double2*)a.un + p * plane, i)), dd_mul(K.cb, v));
+        if (stage > 1) v = dd_add(dd_mul(K.ca, ld((const double2*)a.un + (p * plane + row), at)), dd_mul(K.cb, v));
     }
-    st((double2*)a.out + p * plane, i, v);
+    st((double2*)a.out + (p * plane + row), at, v);
 }
 
 __global__ void dd_extract_kernel(const double2* u, long long plane, int nr, int nth, int j_e, double2* slot)
