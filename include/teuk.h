@@ -278,11 +278,12 @@ teuk_status teuk_set_initial(teuk_solver* h, const double* u, int32_t on_device)
 /* Advance nsteps steps of the configured integrator (Sec. 3.2).  SSP-RK(3,3)
  * is three fused stage kernels
  *     u1 = u + dt F(u);  u2 = 3/4 u + 1/4 (u1 + dt F(u1));  u = 1/3 u + 2/3 (u2 + dt F(u2)),
- * SSP-RK(10,4) ten (see TEUK_RK_SSP104),
- * or, for SSP-RK(3,3) with workgroups = 0 (FP64 state, WENO5, second-order theta
- * differences; with BF16 weights in the tortoise chart up to 2^20 points), one
- * temporally blocked launch a step with the same bits (unless teuk_tune measured the stage launches
- * faster for this class),
+ * SSP-RK(10,4) ten (see TEUK_RK_SSP104); or, with workgroups = 0, FP64 state and
+ * WENO5, one temporally blocked launch a step and four, with the same bits: with
+ * second-order theta differences (SSP-RK(3,3): BF16 weights in the tortoise chart
+ * up to 2^20 points only; SSP-RK(10,4): FP64 and FP32 weights only), and with
+ * fourth-order ones and SSP-RK(3,3) on small grids, unless teuk_tune measured the
+ * stage launches faster for this class;
  * with F(u) = -(M d_x u + L u + A u) of eq. evln and WENO5 radial derivatives
  * (Sec. 3.1.2).  A waveform sample is taken after every extract_every-th step.
  * Asynchronous on the solver's stream.  nsteps = 0 is a no-op.
@@ -427,22 +428,23 @@ teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int64_t nsteps,
  *
  * Separating exp(i m phi~) (Sec. 3) leaves one 2+1D problem per (s, m) mode
  * and per background; such solves share nothing, so a group advances all of
- * its members in one stage-kernel launch per SSP-RK stage (one per weight
- * precision present and per cache block of members) instead of three
- * launches per member per step.  A cache block whose every member fills the
- * GPU by itself (63-point strips x theta rows at least the stage kernel's
- * resident workgroups) has no launches to save: with workgroups = 0 it runs
- * its members' own single-solve stage launches, member after member within
- * each stage, which are faster on such grids.  Each
- * member keeps its own grid, coefficients, dt, waveform ring and counters, and
- * its results are bitwise those of teuk_step on the member alone: the tiles
- * of a member run the single-solve stage arithmetic unchanged.
+ * its members together: with workgroups = 0 in one temporally blocked launch per
+ * step (one per weight precision and chart present and per cache block of
+ * members), whose workgroups share the strip-rows of all members equally.  With
+ * a budget of workgroups, with fourth-order theta differences and with BF16 weights in the
+ * tortoise chart it is one stage-kernel launch per SSP-RK stage instead, and with
+ * workgroups = 0 such a cache block whose every member fills the GPU by itself
+ * (63-point strips x theta rows at least the stage kernel's resident workgroups)
+ * runs its members' own single-solve stage launches, member after member within
+ * each stage.  Each member keeps its own grid, coefficients, dt, waveform ring
+ * and counters, and its results are bitwise those of teuk_step on the member
+ * alone: every launch writes each point's operations out in the same order.
  *
  * Members are created with teuk_create as usual and must use the group's
  * stream.  The group does not own its members; teuk_destroy of a member
  * removes it from its group first.  A solver belongs to at most one group.
  * Device memory: the group allocates one small descriptor block at creation
- * (about 3 * max_members * 160 bytes) and nothing per step.
+ * (about 1 KB per member of max_members) and nothing per step.
  */
 typedef struct teuk_group teuk_group;   /* opaque; owned by the library */
 
@@ -457,7 +459,7 @@ typedef struct {
 
 /* Create an empty group on the current HIP device, enqueuing on ctx->stream
  * (ctx may be NULL: null stream; ctx->workspace is not used).  max_members in
- * [1, 65536].  Each member is cut into tiles of one 63-point radial strip by
+ * [1, 65536].  For stage launches each member is cut into tiles of one 63-point radial strip by
  * one theta segment of about rows_per_tile rows (0: 8); the tiles are
  * numbered segment by segment with the strip index fastest, so that the
  * workgroups in flight march neighbouring strips over the same rows.  Each
