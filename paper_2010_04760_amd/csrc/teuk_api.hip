@@ -962,8 +962,9 @@ static void rk3_stage(const teuk_solver* h, StageArgs& a, int stage)
 static int launch_fused_step(const StageArgs& a, int weight_prec, int chart, hipStream_t stream)
 {
     const int rows = thin_rows(a.nr, a.nth, chart == kChartTortoise4 ? 4 : 2);
-    return rows > 0 ? launch_thin_step(a, rows, weight_prec, chart, stream)
-                    : launch_blocked_step(a, weight_prec, chart, false, stream);
+    if (rows > 0) return launch_thin_step(a, rows, weight_prec, chart, stream);
+    if (chart == kChartTortoise4) return (int)hipErrorInvalidValue;      // no marched launch (fused_step)
+    return launch_blocked_step(a, weight_prec, chart, false, stream);
 }
 
 // One temporally blocked SSP-RK(3,3) step of h on `stream`: u^n in u[0], u^{n+1}
