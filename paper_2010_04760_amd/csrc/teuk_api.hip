@@ -479,6 +479,12 @@ int copy_to_host(void* dst, const void* src, size_t bytes, int device, hipStream
         const int e = (int)hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, stream);
         return e ? e : (int)hipStreamSynchronize(stream);
     }
+    // the workers wait by yielding, so they start when the work before the copy is done
+    int e = (int)hipStreamSynchronize(stream);
+    if (e) {
+        give_staging(set);
+        return e;
+    }
     const int n = (int)((bytes + kChunkBytes - 1) / kChunkBytes);
     std::atomic<int> ready{0};                  // chunks that have arrived; n + 1: give up
     std::atomic<int> moved[kChunks];            // per buffer: the last chunk moved out of it, plus 1
@@ -493,7 +499,6 @@ int copy_to_host(void* dst, const void* src, size_t bytes, int device, hipStream
         }
     };
     std::vector<std::thread> threads;
-    int e = 0;
     bool started = true;
     try {
         threads.reserve((size_t)workers);
