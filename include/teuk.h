@@ -287,6 +287,12 @@ teuk_status teuk_set_initial(teuk_solver* h, const double* u, int32_t on_device)
  * with F(u) = -(M d_x u + L u + A u) of eq. evln and WENO5 radial derivatives
  * (Sec. 3.1.2).  A waveform sample is taken after every extract_every-th step.
  * Asynchronous on the solver's stream.  nsteps = 0 is a no-op.
+ * A caller may capture the call (FP64 state, TEUK_RK_SSP33 or TEUK_RK_SSP104) into a
+ * graph of its own and replay that, between other steps as well: the captured work
+ * is kernel launches only and advances the state by nsteps at each replay, and from
+ * the first captured call on the solver (for teuk_group_step, every member) leaves
+ * its state in the buffer that the graph names.  Single steps then take the stage
+ * launches.  The host's step and sample counts do not see replays.
  * Errors: STATE (no initial data), INVALID_ARG (nsteps < 0), DEVICE. */
 teuk_status teuk_step(teuk_solver* h, int64_t nsteps);
 
@@ -444,7 +450,7 @@ teuk_status teuk_step_noalloc(const teuk_config* cfg, double* u, int64_t nsteps,
  * stream.  The group does not own its members; teuk_destroy of a member
  * removes it from its group first.  A solver belongs to at most one group.
  * Device memory: the group allocates one small descriptor block at creation
- * (about 1 KB per member of max_members) and nothing per step.
+ * (about 2 KB per member of max_members) and nothing per step.
  */
 typedef struct teuk_group teuk_group;   /* opaque; owned by the library */
 

@@ -56,6 +56,9 @@ struct teuk_solver {
     long long plane = 0;
     long long steps = 0, samples = 0;
     bool have_init = false;
+    // A graph that the caller captured names the state's buffer: from then on every
+    // call leaves the state in the buffer that it found it in.
+    bool pinned = false;
     bool counted = false;                           // among the solvers that keep the staging buffers
     int device = 0;
     teuk_group* group = nullptr;                    // group holding this solver, if any
@@ -110,8 +113,8 @@ struct GroupBlock {
     int grid = 0;
     bool solo = false;   // members stepped by their own single-solve launches
     // Stepped by one temporally blocked launch a step over all members (which moves
-    // every member's state to its other buffer: `turn` says which of the two
-    // descriptor sets reads the current ones).
+    // every member's state to its other buffer: `turn` says which of the
+    // descriptor sets read the current ones).
     bool fused = false;
     int turn = 0;
     long long rows = 0;  // strip-rows of that launch
@@ -126,8 +129,9 @@ struct teuk_group {
     int rows = 8;                                   // theta rows per tile (target)
     long long block_bytes = kGroupBlockBytes;       // cache-block size (member footprints)
     std::vector<teuk_solver*> mem;                  // insertion order
-    StageArgs* d_args = nullptr;                    // [5][cap]: per stage, members by weight precision; then the
-                                                    // blocked step from u[0] to u[1] and back
+    StageArgs* d_args = nullptr;                    // [8][cap], members by weight precision: the three stages in
+                                                    // u[0], the blocked step from u[0] to u[1] and back, the stages
+                                                    // in u[1] (the buffers' places when the descriptors were made)
     long long* d_start = nullptr;                   // [2 cap + 2]: each block's tile prefix sums, from 0
     unsigned* d_rows = nullptr;                     // [2 cap + 2]: each block's strip-row prefix sums, from 0
     std::vector<StageArgs> h_args;
@@ -548,6 +552,18 @@ int copy_ring(double* dst, const double* ring_mem, long long first, long long n,
         i += run;
     }
     return e;
+}
+
+// Whether work on `stream` is being captured into a graph of the caller's (the
+// library captures its own on streams of its own).
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs != hipStreamCaptureStatusNone;
 }
 
 // Destroy the solver's captured graph (after the work already enqueued on its
@@ -1185,7 +1201,7 @@ static teuk_status step_eager(teuk_solver* h, int64_t nsteps)
     }
     // A solver that a graph or a group's descriptors refer to keeps its state
     // buffer over a call; the temporally blocked step moves it.
-    const bool keep = h->graph_chunk > 0 || h->group;
+    const bool keep = h->graph_chunk > 0 || h->group || h->pinned;
     for (int64_t n = 0; n < nsteps; ++n) {
         const int e = rk3_step(h, a, n, nsteps, keep, h->stream);
         if (e) return hip_fail(h, e, "stage launch");
@@ -1260,6 +1276,7 @@ teuk_status teuk_step(teuk_solver* h, int64_t nsteps)
     if (!h) return fail(nullptr, TEUK_ERR_INVALID_ARG, "solver is NULL");
     if (nsteps < 0) return fail(h, TEUK_ERR_INVALID_ARG, "nsteps must be >= 0");
     if (!h->have_init) return fail(h, TEUK_ERR_STATE, "teuk_step before teuk_set_initial");
+    if (!h->pinned) h->pinned = capturing(h->stream);
     const int64_t chunk = h->graph_chunk;
     if (chunk > 0 && nsteps >= chunk) {
         teuk_status st = capture_chunk(h);
@@ -1570,6 +1587,14 @@ static teuk_status group_upload(teuk_group* g)
             g->h_args[3 * (size_t)cap + idx] = a;
             a.uk = a.un = h->u[1]; a.out = h->u[0];
             g->h_args[4 * (size_t)cap + idx] = a;
+            // the stages where the state is in u[1]
+            a.nstrips = h->nstrips;
+            a.uk = a.un = h->u[1]; a.out = h->u[0];
+            g->h_args[5 * (size_t)cap + idx] = a;
+            a.uk = h->u[0]; a.out = h->u[2]; a.ca = 0.75; a.cb = 0.25;
+            g->h_args[6 * (size_t)cap + idx] = a;
+            a.uk = h->u[2]; a.out = h->u[1]; a.ca = 1.0 / 3.0; a.cb = 2.0 / 3.0;
+            g->h_args[7 * (size_t)cap + idx] = a;
             g->points += h->plane;
             g->order.push_back(h);
             ++idx;
@@ -1604,7 +1629,7 @@ teuk_status teuk_group_create(const teuk_device_ctx* ctx, int32_t max_members, i
     g->cap = max_members;
     g->workgroups = workgroups;
     g->rows = rows_per_tile > 0 ? rows_per_tile : 8;
-    g->h_args.assign(5 * (size_t)max_members, StageArgs{});
+    g->h_args.assign(8 * (size_t)max_members, StageArgs{});
     g->h_start.assign(2 * (size_t)max_members + 2, 0);   // members + blocks + 1 entries at most
     g->h_rows.assign(2 * (size_t)max_members + 2, 0);
     int e = (int)hipMalloc(&g->d_args, g->h_args.size() * sizeof(StageArgs));
@@ -1663,6 +1688,15 @@ teuk_status teuk_group_remove(teuk_group* g, teuk_solver* h)
     return group_upload(g);
 }
 
+// Whether a graph of the caller's names the state buffer of a member of block b, which
+// then ends every run with its members' states where they were.
+static bool keeps_buffers(const teuk_group* g, const GroupBlock& b)
+{
+    for (int k = b.first; k < b.first + b.n; ++k)
+        if (g->order[(size_t)k]->pinned) return true;
+    return false;
+}
+
 // nsteps steps of cache block bi, launch by launch on `stream` (the members'
 // samples too).
 static teuk_status group_block_eager(teuk_group* g, size_t bi, int64_t nsteps, hipStream_t stream)
@@ -1670,8 +1704,11 @@ static teuk_status group_block_eager(teuk_group* g, size_t bi, int64_t nsteps, h
     const size_t cap = (size_t)g->cap;
     GroupBlock& b = g->blocks[bi];
     const bool blocked = b.solo && g->order[(size_t)b.first]->cfg.integrator == TEUK_RK_SSP33_BLOCKED;
+    const bool keep = keeps_buffers(g, b);
     for (int64_t n = 0; n < nsteps; ++n) {
-        if (b.fused) {   // one launch per step for the whole block
+        // (members that keep their buffer take the last of an odd number of steps by stages, in place)
+        const bool fused = b.fused && !(keep && (nsteps & 1) && n + 1 == nsteps);
+        if (fused) {   // one launch per step for the whole block
             const int e = launch_group_blocked(g->d_args + (size_t)(3 + b.turn) * cap + b.first, g->d_rows + b.start, b.n,
                                                b.rows, b.cls % 4, b.cls / 4, stream);
             if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("group blocked step launch: ") +
@@ -1684,7 +1721,7 @@ static teuk_status group_block_eager(teuk_group* g, size_t bi, int64_t nsteps, h
             if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("blocked step launch: ") +
                                                        hipGetErrorString((hipError_t)e));
         }
-        for (int stage = 1; stage <= 3 && !blocked && !b.fused; ++stage) {
+        for (int stage = 1; stage <= 3 && !blocked && !fused; ++stage) {
             int e = 0;
             if (b.solo) {
                 for (int k = b.first; k < b.first + b.n && !e; ++k) {
@@ -1694,7 +1731,7 @@ static teuk_status group_block_eager(teuk_group* g, size_t bi, int64_t nsteps, h
                     e = launch_stage(a, stage, h->cfg.weight_prec, kernel_chart(h->cfg), stream);
                 }
             } else {
-                e = launch_group_stage(g->d_args + (stage - 1) * cap + b.first, g->d_start + b.start, b.n,
+                e = launch_group_stage(g->d_args + (size_t)(b.turn ? 4 + stage : stage - 1) * cap + b.first, g->d_start + b.start, b.n,
                                        b.tiles, b.grid, stage, b.cls % 4, b.cls / 4, stream);
             }
             if (e) return gfail(g, TEUK_ERR_DEVICE, std::string("group stage launch: ") +
@@ -1748,6 +1785,7 @@ static teuk_status capture_block(teuk_group* g, size_t bi)
         phase.push_back(every > 0 ? h->steps % every : 0);
         phase.push_back((long long)(uintptr_t)h->u[0]);   // buffer roles (the blocked step trades them)
     }
+    phase.push_back(keeps_buffers(g, b));
     if (g->gexec[gi] && g->gphase[gi] == phase) return TEUK_OK;
     int e = 0;
     if (g->gexec[gi]) {
@@ -1811,11 +1849,14 @@ teuk_status teuk_group_step(teuk_group* g, int64_t nsteps)
     if (g->mem.empty()) return TEUK_OK;
     const int64_t chunk = g->graph_chunk;
     if (g->gexec.size() != 2 * g->blocks.size()) drop_group_graphs(g);
+    if (capturing(g->stream))
+        for (teuk_solver* h : g->mem) h->pinned = true;
     // block by block: a block runs all nsteps steps before the next starts
     for (size_t bi = 0; bi < g->blocks.size(); ++bi) {
         int64_t left = nsteps;
         if (chunk > 0 && nsteps >= chunk) {
             GroupBlock& b = g->blocks[bi];
+            const bool moved = b.fused && (chunk & 1) && !keeps_buffers(g, b);
             for (int64_t q = nsteps / chunk; q > 0; --q) {
                 teuk_status st = capture_block(g, bi);
                 if (st != TEUK_OK) return st;
@@ -1825,9 +1866,9 @@ teuk_status teuk_group_step(teuk_group* g, int64_t nsteps)
                     teuk_solver* h = g->order[(size_t)k];
                     h->steps += chunk;
                     if (h->cfg.extract_every > 0) h->samples += chunk / h->cfg.extract_every;
-                    if (b.fused && (chunk & 1)) std::swap(h->u[0], h->u[1]);
+                    if (moved) std::swap(h->u[0], h->u[1]);
                 }
-                if (b.fused) b.turn ^= (int)(chunk & 1);
+                if (moved) b.turn ^= 1;
             }
             left = nsteps % chunk;
         }
