@@ -152,7 +152,7 @@ RK104_BYTES_PER_POINT_STEP = 2 * 64 + 128 + 96
 # FP64 operations (FMA counted twice) and VALU instructions per point-stage of
 # the double-double stage kernel, counted in its gfx950 ISA (stages 2 and 3;
 # one lane per point): it is bound by FP64 instruction issue.
-DD_OPS = {"dd_weights": (3250, 3000), "fp64_weights": (2790, 2680)}
+DD_OPS = {"dd_weights": (4310, 4000), "fp64_weights": (2840, 2730)}
 FP64_VECTOR_TFLOPS = 78.6                 # MI355X FP64 vector peak (FMA = 2 flops)
 VALU_ISSUE_PER_S = 256 * 4 * 16 * 2.4e9   # lane-instructions/s: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 

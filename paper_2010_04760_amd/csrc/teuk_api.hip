@@ -896,6 +896,8 @@ static DDStageArgs dd_args(const teuk_solver* h)
     cp(a.ih1, h->ddk.ih1);
     cp(a.ih2, h->ddk.ih2);
     cp(a.sixth, h->ddk.sixth);
+    cp(a.c13_3, h->ddk.c13_3);
+    for (int q = 0; q < 3; ++q) cp(a.d[q], h->ddk.d[q]);
     a.ca[0] = a.ca[1] = a.cb[1] = 0.0;
     a.cb[0] = 1.0;
     a.dt = h->dt;

@@ -157,6 +157,10 @@ bool build_tables_dd(const teuk_config& c, std::vector<double>& dtab, DDScalars*
     put(sc->ih2, 1 / (dth * dth));
     put(sc->third, (Q)1 / 3);
     put(sc->two_thirds, (Q)2 / 3);
+    put(sc->d[0], (Q)1 / 10);
+    put(sc->d[1], (Q)6 / 10);
+    put(sc->d[2], (Q)3 / 10);
+    put(sc->c13_3, (Q)13 / 3);
     put(sc->sixth, (Q)1 / 6);
     return true;
 }

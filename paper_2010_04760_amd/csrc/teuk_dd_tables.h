@@ -20,6 +20,8 @@ struct DDScalars {
     double inv_dx[2];       // 1 / dx
     double ih1[2], ih2[2];  // 1 / (2 dtheta), 1 / dtheta^2
     double third[2], two_thirds[2];
+    double d[3][2];         // WENO5 linear weights 1/10, 6/10, 3/10
+    double c13_3[2];        // 13 / 3
     double sixth[2];        // 1 / 6
 };
 

@@ -96,7 +96,7 @@ struct DDStageArgs {
     int nr, nth, nstrips;
     double inv_dx[2], ih1[2], ih2[2];
     double ca[2], cb[2];   // out = ca un + cb (uk + dt F) for stages 2, 3
-    double sixth[2];
+    double sixth[2], c13_3[2], d[3][2];
     double dt, eps, parity;
 };
 
