@@ -567,6 +567,17 @@ __device__ __forceinline__ void lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders LDS between the lanes of one wave: what a lane wrote before it is what the
+// others read after it.  (The wave barrier alone is no memory operation to the compiler,
+// which may move a read of another lane's value over the write that it cannot see it
+// needs; the hardware runs a wave's LDS operations in order, so the fences cost nothing.)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Load a double at a byte offset from a uniform base: the 32-bit offset lets
 // the compiler use the scalar-base addressing form (no 64-bit address math),
 // and the global address space keeps it from flat accesses where the base came

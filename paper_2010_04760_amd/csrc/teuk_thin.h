@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kThinWaves * kWave, 4) void thin_step_kernel(StageA
 #pragma unroll
         for (int p = 0; p < 4; ++p) r0[p * kThinPlane + kWave + l] = xb[p];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 
     const int lo = clampi(-p0, 0, kWave - 1), hi = clampi(nr - 1 - p0, 0, kWave - 1);
     double own[4], d[4];
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kThinWaves * kWave, 4) void thin_step_kernel(StageA
 #pragma unroll
         for (int p = 0; p < 4; ++p) r1[p * kThinPlane + l] = v.v[p];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     int q[6];
 #pragma unroll
     for (int t = 0; t < 6; ++t) q[t] = clampi(l - 3 + t, lo, hi);
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kThinWaves * kWave, 4) void thin_step_kernel(StageA
         }
     }
     if constexpr (kStages == 3) {
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
 
         // ---- stage 3
         if (final) fluxes([&](int p, int t) { return r2[p * kThinPlane + q[t]]; });
