@@ -124,13 +124,14 @@ def cpu_baseline(wl, u0, target_s: float):
             "cpu": {"model": cpu_model(), "nproc": os.cpu_count(), "affinity": avail}}
 
 
-def fused_roofline(points: float, t_step: float, weights: str = "fp64", per_point: float = FUSED_BYTES_PER_POINT_STEP):
-    """One temporally blocked launch per step."""
+def fused_roofline(points: float, t_step: float, weights: str = "fp64", per_point: float = FUSED_BYTES_PER_POINT_STEP,
+                   low_tiles: bool = False):
+    """One temporally blocked launch per step (marched along theta, or in low tiles)."""
     achieved = per_point * points / t_step / 1e9
     r = {"bound": "alu", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-         "traffic": None, "kernel": "blocked_step_kernel (SSP-RK3 step)",
+         "traffic": None, "kernel": ("thin_step_kernel" if low_tiles else "blocked_step_kernel") + " (SSP-RK3 step)",
          "algorithmic_bytes_per_launch": per_point * points, "avg_launch_us": t_step * 1e6}
-    if per_point == FUSED_BYTES_PER_POINT_STEP:
+    if per_point == FUSED_BYTES_PER_POINT_STEP and not low_tiles:
         r["valu_issue_frac"] = FUSED_VALU[weights] * points / t_step / VALU_ISSUE_PER_S
     return r
 
@@ -142,6 +143,13 @@ def roofline(points_per_launch: float, t_launch: float, traffic):
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
             "kernel": "stage_kernel (fused SSP-RK3 stage)",
             "algorithmic_bytes_per_launch": bytes_launch, "avg_launch_us": t_launch * 1e6}
+
+
+def step_roofline(T, launch, points: float, t_step: float, weights: str, traffic):
+    """Of the SSP-RK(3,3) step that a solver takes (launch: its teuk_step_launch)."""
+    if launch.kind == T.TEUK_STEP_STAGES:
+        return roofline(points, t_step / 3, traffic)
+    return fused_roofline(points, t_step, weights, low_tiles=launch.kind == T.TEUK_STEP_LOW_TILES)
 
 
 # SSP-RK(10,4) step in four launches: stages 1-3 and 6-8 read u and write u (64 B
@@ -369,6 +377,7 @@ def bench_single(args, torch, T, W):
                          "waveform_rel_l2_vs_fp64": float(np.linalg.norm(wave_w - wave64f) / np.linalg.norm(wave64f))}
         mixed["waveform"] = (f"{wave64f.shape[0]} samples x {wl.nth} rows at r* = {wl.x_e}, t = 0 .. "
                              f"{full} steps; the FP64 run is the parity-tested path")
+    launches = {name: sv.step_launch() for name, sv, *_ in chain}
     info, wave = finish(hs)
     results = {name: timed[name] + finish(sv) for name, sv, *_ in chain[1:]}
     do_graph_leg, do_theta4 = "graph" in results, "theta4" in results
@@ -376,20 +385,18 @@ def bench_single(args, torch, T, W):
 
     pu = 3.0 * wl.points * steps
     # The sample kernel (one per 10 steps) is included in the time and is < 0.5 %
-    # of it on C2.  Stage launches: a budget was given, or the tuner found one faster.
-    by_stages = args.workgroups > 0 or ("rk3" in tuned
-                                        and tuned["rk3"]["us_per_step"] < tuned["rk3"]["us_per_step_default"])
+    # of it on C2.
     out = {
         "metric": METRIC, "value": pu / gpu_s, "unit": "point-updates/s", "n_gpus": 1, "steps": steps,
         "warmup": warmup, "ms_per_step": gpu_s / steps * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f64" if weights == "fp64" else f"f64 (weights {weights})",
         "data": "synthetic",
         "config": {"workload": wl.name, "nr": wl.nr, "ntheta": wl.nth, "s": wl.s, "m": wl.m, "a": wl.a,
-                   "weights": weights, "dt": info.dt, "workgroups": info.workgroups,
+                   "weights": weights, "dt": info.dt, "workgroups": int(launches["headline"].workgroups),
                    "extract_every": wl.every, "seed": wl.seed, "graph_chunk_steps": graph,
                    "launch_shape": "autotuned" if "rk3" in tuned else ("given" if args.workgroups else "default")},
-        "roofline": roofline(wl.points, gpu_s / (3 * steps), measured_traffic(weights) if not c1 else None)
-        if by_stages else fused_roofline(wl.points, gpu_s / steps, weights),
+        "roofline": step_roofline(T, launches["headline"], wl.points, gpu_s / steps, weights,
+                                  measured_traffic(weights) if not c1 else None),
         "wall_s": wall,
     }
     if tuned:
@@ -418,7 +425,7 @@ def bench_single(args, torch, T, W):
         out["theta4"] = {"steps": lsteps, "dt": info4.dt, "ms_per_step": sec4 / lsteps * 1e3, "value": lpu / sec4,
                          "speed_vs_second_order": t_step / (sec4 / lsteps),
                          "simulated_time_per_s_vs_second_order": (info4.dt * lsteps / sec4) / (info.dt / t_step),
-                         "hbm_frac": roofline(wl.points, sec4 / (3 * lsteps), None)["frac"]}
+                         "hbm_frac": step_roofline(T, launches["theta4"], wl.points, sec4 / lsteps, weights, None)["frac"]}
     if do_pipe:
         # the same steps in one cooperative launch per waveform interval (tiles
         # wait for their neighbours' previous stage only)
@@ -816,7 +823,9 @@ def bench_batched(args, torch, T, W):
                    "workgroups_per_stage": int(ginfo.workgroups), "tiles_per_stage": int(ginfo.tiles),
                    "rows_per_tile": tuned["rows_per_tile"] if tuned else (args.rows_per_tile or 8),
                    "block_mib": tuned["block_mib"] if tuned else 256, "graph_chunk_steps": graph},
-        "roofline": fused_roofline(points, gpu_s / steps, weights),
+        # (a budget of workgroups and BF16 weights: stage launches over the members)
+        "roofline": roofline(points, gpu_s / (3 * steps), None) if args.workgroups > 0 or weights == "bf16"
+        else fused_roofline(points, gpu_s / steps, weights),
         "alone_sequential": {"value": 3.0 * points * alone_steps / alone_s, "steps": alone_steps},
         "batching_speedup": (pu / gpu_s) / (3.0 * points * alone_steps / alone_s),
         "wall_s": wall,

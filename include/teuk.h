@@ -232,7 +232,10 @@ typedef struct {
     int64_t steps;           /* steps taken since teuk_set_initial                     */
     int64_t samples;         /* waveform samples recorded (may exceed max_samples)     */
     int32_t j_extract;       /* radial index sampled for the waveform                  */
-    int32_t workgroups;      /* stage-kernel workgroups in use (stages 2-3)             */
+    int32_t workgroups;      /* workgroups of a stage launch (stages 2-3) of this solver: of
+                                single steps that keep their buffer, TEUK_X_RHS, and every
+                                step where teuk_step_launch says TEUK_STEP_STAGES;
+                                TEUK_RK_SSP33_BLOCKED and _PIPELINED: of their launches     */
     double dt_bound;         /* stability bound (cfl = 1), from the device reduction   */
 } teuk_info_t;
 
@@ -295,6 +298,25 @@ teuk_status teuk_set_initial(teuk_solver* h, const double* u, int32_t on_device)
  * launches.  The host's step and sample counts do not see replays.
  * Errors: STATE (no initial data), INVALID_ARG (nsteps < 0), DEVICE. */
 teuk_status teuk_step(teuk_solver* h, int64_t nsteps);
+
+/* The launches that teuk_step takes for this solver's steps (two or more in a call;
+ * solvers that keep their state's buffer take a single one by stage launches). */
+enum { TEUK_STEP_STAGES = 0,     /* one launch per stage                                   */
+       TEUK_STEP_BLOCKED = 1,    /* temporally blocked launches, tiles marched along theta */
+       TEUK_STEP_LOW_TILES = 2,  /* the same in low tiles, one wave per row                */
+       TEUK_STEP_PIPELINED = 3   /* many steps in one cooperative launch                   */ };
+
+typedef struct {
+    int32_t kind;            /* TEUK_STEP_*                                             */
+    int32_t launches;        /* kernel launches per step (pipelined: 0)                 */
+    int32_t rows;            /* low tiles: theta rows of a tile; else 0                 */
+    int32_t reserved;
+    int64_t workgroups;      /* workgroups of a launch (stages 2-3; SSP-RK(10,4): the launch of
+                                three stages)                                           */
+} teuk_step_launch_t;
+
+/* Errors: INVALID_ARG (NULL). */
+teuk_status teuk_step_launch(const teuk_solver* h, teuk_step_launch_t* out);
 
 /* Graph mode (HIP graphs).  With chunk_steps > 0, teuk_step runs its steps as
  * replays of one graph that holds chunk_steps steps -- every stage launch and
@@ -457,8 +479,11 @@ typedef struct teuk_group teuk_group;   /* opaque; owned by the library */
 typedef struct {
     int32_t members;         /* solvers in the group                                 */
     int32_t classes;         /* (weight precision, chart) classes present            */
-    int64_t workgroups;      /* workgroups per stage (stages 2-3), summed over the launches */
-    int64_t tiles;           /* tiles (one strip x one theta segment) per stage        */
+    int64_t workgroups;      /* workgroups per stage (stages 2-3), summed over the launches;
+                                of a block stepped by one blocked launch a step, that
+                                launch's                                              */
+    int64_t tiles;           /* tiles (one strip x one theta segment) per stage; of such a
+                                block, its workgroups' shares                          */
     int64_t units;           /* strip-rows per stage (63 radial points x 1 theta row)  */
     int64_t points;          /* grid points over all members                          */
 } teuk_group_info_t;

@@ -55,6 +55,7 @@ INTEGRATOR = {"rk3": TEUK_RK_SSP33, "rk104": TEUK_RK_SSP104, "rk3_blocked": TEUK
 TEUK_SCHEME_WENO5, TEUK_SCHEME_WENO3, TEUK_SCHEME_FD6KO8 = 0, 1, 2
 SCHEME = {"weno5": TEUK_SCHEME_WENO5, "weno3": TEUK_SCHEME_WENO3, "fd6ko8": TEUK_SCHEME_FD6KO8}
 TEUK_X_STATE, TEUK_X_WAVEFORM, TEUK_X_TIMES, TEUK_X_COEFFS, TEUK_X_RHS, TEUK_X_HORIZON = 0, 1, 2, 3, 4, 5
+TEUK_STEP_STAGES, TEUK_STEP_BLOCKED, TEUK_STEP_LOW_TILES, TEUK_STEP_PIPELINED = 0, 1, 2, 3
 TEUK_NCOEF = 10
 CHART = {"T": TEUK_CHART_TORTOISE, "H": TEUK_CHART_HYPERBOLOIDAL}
 WEIGHT_PREC = {"fp64": TEUK_W_FP64, "fp32": TEUK_W_FP32, "fp16": TEUK_W_FP16, "bf16": TEUK_W_BF16, "dd": TEUK_W_DD}
@@ -88,6 +89,11 @@ class teuk_info_t(ctypes.Structure):
                 ("dt_bound", ctypes.c_double)]
 
 
+class teuk_step_launch_t(ctypes.Structure):
+    _fields_ = [("kind", ctypes.c_int32), ("launches", ctypes.c_int32), ("rows", ctypes.c_int32),
+                ("reserved", ctypes.c_int32), ("workgroups", ctypes.c_int64)]
+
+
 _P = ctypes.POINTER
 _dp = _P(ctypes.c_double)
 _lib.teuk_default_config.argtypes = [_P(teuk_config)]
@@ -104,6 +110,8 @@ _lib.teuk_extract.argtypes = [ctypes.c_void_p, ctypes.c_int32, _dp, ctypes.c_siz
 _lib.teuk_extract.restype = ctypes.c_int
 _lib.teuk_info.argtypes = [ctypes.c_void_p, _P(teuk_info_t)]
 _lib.teuk_info.restype = ctypes.c_int
+_lib.teuk_step_launch.argtypes = [ctypes.c_void_p, _P(teuk_step_launch_t)]
+_lib.teuk_step_launch.restype = ctypes.c_int
 _lib.teuk_check_finite.argtypes = [ctypes.c_void_p]
 _lib.teuk_check_finite.restype = ctypes.c_int
 _lib.teuk_destroy.argtypes = [ctypes.c_void_p]
@@ -167,7 +175,7 @@ EXPORTED = ["teuk_default_config", "teuk_footprint_bytes", "teuk_create", "teuk_
             "teuk_host_coefficients", "teuk_group_create", "teuk_group_add", "teuk_group_remove",
             "teuk_group_step", "teuk_group_info", "teuk_group_destroy", "teuk_group_last_error",
             "teuk_step_noalloc", "teuk_set_graph", "teuk_group_set_graph", "teuk_tune", "teuk_tune_forget",
-            "teuk_tune_last_error", "teuk_group_tune"]
+            "teuk_tune_last_error", "teuk_group_tune", "teuk_step_launch"]
 
 
 class TeukError(RuntimeError):
@@ -252,6 +260,12 @@ def teuk_info(h: int) -> teuk_info_t:
     info = teuk_info_t()
     _check(_lib.teuk_info(h, ctypes.byref(info)), h)
     return info
+
+
+def teuk_step_launch(h: int) -> teuk_step_launch_t:
+    out = teuk_step_launch_t()
+    _check(_lib.teuk_step_launch(h, ctypes.byref(out)))
+    return out
 
 
 def teuk_check_finite(h: int) -> None:
@@ -409,6 +423,10 @@ class Solver:
 
     def info(self) -> teuk_info_t:
         return teuk_info(self.h)
+
+    def step_launch(self) -> teuk_step_launch_t:
+        """The launches that steps of this solver take."""
+        return teuk_step_launch(self.h)
 
     def waveform(self):
         inf = self.info()

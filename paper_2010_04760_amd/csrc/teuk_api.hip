@@ -1406,6 +1406,34 @@ teuk_status teuk_info(teuk_solver* h, teuk_info_t* info)
     return TEUK_OK;
 }
 
+teuk_status teuk_step_launch(const teuk_solver* h, teuk_step_launch_t* out)
+{
+    if (!h) return fail(nullptr, TEUK_ERR_INVALID_ARG, "solver is NULL");
+    if (!out) return fail(nullptr, TEUK_ERR_INVALID_ARG, "out is NULL");
+    const teuk_config& c = h->cfg;
+    const bool rk104 = c.integrator == TEUK_RK_SSP104;
+    std::memset(out, 0, sizeof(*out));
+    if (c.integrator == TEUK_RK_SSP33_PIPELINED) {
+        out->kind = TEUK_STEP_PIPELINED;
+        out->workgroups = h->pgrid;
+    } else if (c.integrator == TEUK_RK_SSP33_BLOCKED || h->fused) {
+        out->rows = h->fused ? thin_rows(c.nr, c.ntheta, c.theta_order == 4 ? 4 : 2) : 0;
+        out->kind = out->rows > 0 ? TEUK_STEP_LOW_TILES : TEUK_STEP_BLOCKED;
+        out->launches = rk104 ? 4 : 1;
+        out->workgroups = out->rows > 0 ? thin_tiles(c.nr, c.ntheta, out->rows, 3)
+                          : rk104       ? std::min<long long>((long long)((c.nr + kBlockedPoints - 1) / kBlockedPoints) * c.ntheta,
+                                                              part_grid(3, c.weight_prec, c.chart))
+                                        : h->bgrid;
+    } else {
+        out->kind = TEUK_STEP_STAGES;
+        out->launches = rk104 ? 10 : 3;
+        out->workgroups = h->dd                            ? (long long)h->nstrips * c.ntheta
+                          : c.scheme != TEUK_SCHEME_WENO5 ? (long long)h->nstrips * ((c.ntheta + 3) / 4)
+                                                          : (long long)h->nstrips * h->segs[1];
+    }
+    return TEUK_OK;
+}
+
 teuk_status teuk_check_finite(teuk_solver* h)
 {
     if (!h) return fail(nullptr, TEUK_ERR_INVALID_ARG, "solver is NULL");
@@ -2039,8 +2067,9 @@ teuk_status teuk_group_info(const teuk_group* g, teuk_group_info_t* info)
     for (const GroupBlock& b : g->blocks) {
         info->classes += !seen[b.cls];
         seen[b.cls] = true;
-        info->workgroups += b.solo ? b.solo_wg : b.grid;
-        info->tiles += b.solo ? b.solo_wg : b.tiles;
+        const long long shares = b.fused ? std::min<long long>(b.rows, blocked_grid(b.cls % 4, b.cls / 4)) : 0;
+        info->workgroups += b.fused ? shares : b.solo ? b.solo_wg : b.grid;
+        info->tiles += b.fused ? shares : b.solo ? b.solo_wg : b.tiles;
         info->units += b.units;
     }
     info->points = g->points;

@@ -144,6 +144,8 @@ int launch_blocked_step(const StageArgs& a, int weight_prec, int chart, bool own
 // (chart: the launch class, so fourth-order theta differences as well; those have no
 // marched launch.)  launch_thin_part: launch_blocked_part in such tiles.
 int thin_rows(int nr, int nth, int theta_order);
+// Tiles of that launch (its workgroups), `stages` stages in it.
+long long thin_tiles(int nr, int nth, int rows, int stages);
 int launch_thin_step(const StageArgs& a, int rows, int weight_prec, int chart, void* stream);
 int launch_thin_part(const StageArgs& a, int rows, int stages, int weight_prec, int chart, void* stream);
 // Consecutive stages of an SSP-RK(10,4) step in one launch, from a.uk into a.out

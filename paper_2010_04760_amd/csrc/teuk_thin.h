@@ -322,15 +322,19 @@ int thin_rows(int nr, int nth, int theta_order)
     return 0;
 }
 
+long long thin_tiles(int nr, int nth, int rows, int stages)
+{
+    const int points = thin_points(stages);
+    return ((long long)nr + points - 1) / points * (((long long)nth + rows - 1) / rows);
+}
+
 // stages and kind as in launch_blocked_part
 static int launch_thin(const StageArgs& a, int rows, int stages, const void* fn, int theta_order, void* stream)
 {
     const int waves = rows + 2 * thin_halo(stages, theta_order);
     if (!fn || rows < 1 || waves > kThinWaves || a.nr < 1 || a.nth < 2 || a.uk == a.out || a.uk == a.out2)
         return (int)hipErrorInvalidValue;
-    const int points = thin_points(stages);
-    const long long strips = ((long long)a.nr + points - 1) / points;
-    const long long tiles = strips * (((long long)a.nth + rows - 1) / rows);
+    const long long tiles = thin_tiles(a.nr, a.nth, rows, stages);
     if (tiles > (1LL << 21)) return (int)hipErrorInvalidValue;
     StageArgs b = a;
     void* args[] = {&b, &rows};
