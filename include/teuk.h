@@ -552,7 +552,7 @@ teuk_status teuk_group_set_graph(teuk_group* g, int32_t chunk_steps);
 typedef struct {
     int32_t rows_per_tile, block_mib;                  /* the shape applied            */
     int32_t default_rows_per_tile, default_block_mib;  /* the shape before the call    */
-    int32_t candidates, steps;                         /* shapes timed, steps per run  */
+    int32_t candidates, steps;                         /* shapes compared (those with the same launches share a timing), steps per run */
     double us_per_step, us_per_step_default;           /* microseconds per group step  */
 } teuk_group_tune_info_t;
 teuk_status teuk_group_tune(teuk_group* g, int32_t steps, teuk_group_tune_info_t* info);

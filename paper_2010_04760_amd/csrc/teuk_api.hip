@@ -647,6 +647,10 @@ void dd_coeff_order(const double* t, long long plane, double* out)
 
 }  // namespace
 
+namespace teuk {
+bool steps_fused(const teuk_config& c) { return fused_step(c); }
+}  // namespace teuk
+
 extern "C" {
 
 void teuk_default_config(teuk_config* c)
@@ -763,7 +767,7 @@ teuk_status teuk_create(const teuk_config* cfg, const teuk_device_ctx* ctx, teuk
     // launch class on this device, else (0) all the GPU holds at once
     teuk_config eff = *cfg;
     if (eff.workgroups == 0) eff.workgroups = tuned_workgroups(*cfg);
-    // (the double-double kernel runs one wave per strip and theta row)
+    // (the double-double kernel runs one workgroup per strip and theta row)
     h->segs[0] = dd ? 1 : pick_segs(eff, h->nstrips, cfg->weight_prec, true);
     h->segs[1] = dd ? 1 : pick_segs(eff, h->nstrips, cfg->weight_prec, false);
     if (h->segs[0] <= 0 || h->segs[1] <= 0 || (long long)h->nstrips * h->segs[0] > (1LL << 31) - 1 ||
@@ -2015,22 +2019,36 @@ teuk_status teuk_group_tune(teuk_group* g, int32_t steps, teuk_group_tune_info_t
         if (s2 != TEUK_OK) why = tg->err;
         return s2;
     };
+    // whether the tile height matters: some block steps by stage launches over its members
+    auto tiled = [&]() {
+        for (const GroupBlock& b : tg->blocks)
+            if (!b.fused && !b.solo) return true;
+        return false;
+    };
+    bool default_tiled = false;
     if (st == TEUK_OK) st = try_shape(g->rows, g->block_bytes, &default_us);
     if (st == TEUK_OK) {
         best_us = default_us;
         cand = 1;
+        default_tiled = tiled();
     }
-    for (int r : rows_c) {
-        for (long long mb : mib_c) {
+    for (long long mb : mib_c) {
+        // heights that make no difference share one timing and keep the height in use
+        bool timed = (mb << 20) == g->block_bytes, differ = default_tiled;
+        double us = default_us;
+        for (int r : rows_c) {
             if (st != TEUK_OK) break;
             if (r == g->rows && (mb << 20) == g->block_bytes) continue;
-            double us = 0.0;
-            st = try_shape(r, mb << 20, &us);
-            if (st != TEUK_OK) break;
+            if (!timed || differ) {
+                st = try_shape(r, mb << 20, &us);
+                if (st != TEUK_OK) break;
+                timed = true;
+                differ = tiled();
+            }
             ++cand;
             if (us < best_us) {
                 best_us = us;
-                best_rows = r;
+                best_rows = differ ? r : g->rows;
                 best_bytes = mb << 20;
             }
         }

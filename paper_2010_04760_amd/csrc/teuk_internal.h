@@ -103,9 +103,11 @@ struct DDStageArgs {
 // Workgroup budget that teuk_tune found fastest for c's launch class on the
 // current device, or 0 if it has not been tuned.
 int tuned_workgroups(const teuk_config& c);
-// Whether teuk_tune found c's launch class (SSP-RK(3,3)) faster by stage launches of
-// its tuned budget than by the temporally blocked launch.
+// Whether teuk_tune found c's launch class (SSP-RK(3,3) or SSP-RK(10,4)) faster by stage
+// launches of its tuned budget than by the temporally blocked launches.
 bool tuned_stage_launches(const teuk_config& c);
+// Whether a solver of c steps by temporally blocked launches that it was not asked for.
+bool steps_fused(const teuk_config& c);
 
 // Resident workgroup count of a stage-kernel instantiation on the current
 // device (0 if the weight precision is not built).  The launch uses

@@ -32,10 +32,16 @@ typedef std::tuple<int, int, int, int, int, int, int, int> TuneKey;
 std::mutex g_tune_mutex;
 struct Tuned {
     int workgroups;    // fastest budget of stage workgroups (of tiles, for the blocked integrator)
-    bool stages;       // SSP-RK(3,3): stage launches of that budget beat the blocked launch
+    bool stages;       // stage launches of that budget beat the temporally blocked launches
 };
 std::map<TuneKey, Tuned> g_tuned;
 thread_local std::string g_tune_err;
+// Solvers that this thread creates take no tuned shape (while the tuner times the default).
+thread_local bool t_untuned = false;
+struct Untuned {
+    Untuned() { t_untuned = true; }
+    ~Untuned() { t_untuned = false; }
+};
 
 TuneKey key_of(const teuk_config& c, int device)
 {
@@ -110,7 +116,7 @@ namespace teuk {
 int tuned_workgroups(const teuk_config& c)
 {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (t_untuned || hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     auto it = g_tuned.find(key_of(c, dev));
     return it == g_tuned.end() ? 0 : it->second.workgroups;
@@ -119,7 +125,7 @@ int tuned_workgroups(const teuk_config& c)
 bool tuned_stage_launches(const teuk_config& c)
 {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
+    if (t_untuned || hipGetDevice(&dev) != hipSuccess) return false;
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     auto it = g_tuned.find(key_of(c, dev));
     return it != g_tuned.end() && it->second.stages;
@@ -135,7 +141,7 @@ teuk_status teuk_tune(const teuk_config* cfg, int32_t steps, teuk_tune_info_t* o
     if (steps < 0) return tfail(TEUK_ERR_INVALID_ARG, "steps must be >= 0");
     std::memset(out, 0, sizeof(*out));
     if (cfg->state_prec != TEUK_S_FP64)
-        return tfail(TEUK_ERR_UNSUPPORTED, "the double-double kernel has a fixed launch shape (one wave per strip and row)");
+        return tfail(TEUK_ERR_UNSUPPORTED, "the double-double kernel has a fixed launch shape (four waves per strip and row)");
     if (teuk_footprint_bytes(cfg) == 0) {
         teuk_solver* h = nullptr;
         const teuk_status st = teuk_create(cfg, nullptr, &h);   // reports why cfg is invalid
@@ -202,19 +208,20 @@ teuk_status teuk_tune(const teuk_config* cfg, int32_t steps, teuk_tune_info_t* o
             best_us = us;
         }
     }
-    // the way that solvers of this class step without a budget, where that is
-    // another one than stage launches (the temporally blocked launches)
+    // the way that solvers of this class step without a budget, where that is another
+    // one than stage launches (the temporally blocked launches)
     bool stages = false;
-    if (st == TEUK_OK && (cfg->integrator == TEUK_RK_SSP33 || cfg->integrator == TEUK_RK_SSP104)) {
-        {
-            std::lock_guard<std::mutex> lock(g_tune_mutex);
-            g_tuned.erase(key_of(*cfg, dev));
+    if (st == TEUK_OK) {
+        Untuned as_default;
+        teuk_config c = base;
+        c.workgroups = 0;
+        if (teuk::steps_fused(c)) {
+            double us = 0.0;
+            st = time_budget(base, 0, n, stream, zeros, &us);
+            stages = us > best_us;
+            if (!stages) best_us = us;
+            default_us = us;
         }
-        double us = 0.0;
-        st = time_budget(base, 0, n, stream, zeros, &us);
-        stages = us > best_us;
-        if (!stages) best_us = us;
-        default_us = us;
     }
     (void)hipStreamDestroy(stream);
     if (st != TEUK_OK) return st;

@@ -108,3 +108,17 @@ def test_reported_launches():
             g.add(sv)
         inf = g.info()
         assert inf.workgroups == inf.tiles == 3 * (1 + 3)      # one strip-row each: fewer than the GPU holds
+
+
+def test_group_tuning_keeps_a_height_that_makes_no_difference():
+    """Members stepped by one blocked launch have no tile heights to choose from."""
+    print("case routes group tune", flush=True)
+    members = [T.Solver(T.make_config(nr=nr, ntheta=24, **T_KW)) for nr in (500, 700)]
+    with T.Group(2) as g:
+        for sv in members:
+            sv.set_initial(W.random_state(sv.cfg.nr, 24, seed=1, smooth=True))
+            g.add(sv)
+        for _ in range(3):
+            info = g.tune(5)
+            assert info.rows_per_tile == info.default_rows_per_tile == 8
+            assert info.candidates >= 10 and info.us_per_step <= info.us_per_step_default
