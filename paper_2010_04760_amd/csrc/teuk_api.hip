@@ -2,17 +2,13 @@
 // the SSP-RK(3,3) step loop, waveform ring buffer, guard and extraction.
 #include <hip/hip_runtime.h>
 
-#include <sched.h>
-
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <new>
 #include <string>
-#include <thread>
 #include <utility>
 #include <array>
 #include <vector>
@@ -20,6 +16,7 @@
 #include "teuk_coef.h"
 #include "teuk_dd_tables.h"
 #include "teuk_internal.h"
+#include "teuk_staging.h"
 
 using namespace teuk;
 
@@ -352,7 +349,8 @@ teuk_status hip_fail(teuk_solver* h, int e, const char* what)
 // pinned chunks instead, which worker threads move on (and touch the pages)
 // while the next ones arrive: 2.2 ms; 256 MiB 26.5 -> 7.4 ms, 16 MiB 1.0 -> 0.65.
 // Below, the threads cost as much as they save (6 MiB 0.40 ms both ways, 4 MiB 0.27
-// against 0.34).
+// against 0.34).  The threads sleep while nothing has arrived: 256 MiB cost 43 ms of CPU time
+// in all where yielding threads took 70.
 constexpr size_t kStagedMin = 8u << 20;
 constexpr size_t kChunkBytes = 2u << 20;
 constexpr int kChunks = 8;             // 16 MiB of pinned memory per set
@@ -364,101 +362,40 @@ struct StagingSet {
     hipEvent_t landed[kChunks] = {};
     int device = 0;
 };
+SetPool<StagingSet, kMaxSets> g_staging;
 
-// The sets in the process: handed to one copy at a time, kept between copies
-// while any solver is alive, released with the last one.
-struct StagingPool {
-    std::mutex mutex;
-    StagingSet* idle[kMaxSets] = {};
-    int nidle = 0;
-    int made = 0;
-    long long solvers = 0;
+// (Allocations and releases here are no part of a capture that another thread may have
+// under way.)
+struct OutsideCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
-StagingPool g_staging;
 
 void free_staging(StagingSet* s)
 {
+    OutsideCapture scope;
     for (hipEvent_t e : s->landed)
         if (e) (void)hipEventDestroy(e);
     if (s->mem) (void)hipHostFree(s->mem);
     delete s;
 }
 
-void staging_solver_made()
+StagingSet* make_staging(int device)
 {
-    std::lock_guard<std::mutex> lock(g_staging.mutex);
-    ++g_staging.solvers;
-}
-
-void staging_solver_gone()
-{
-    StagingSet* drop[kMaxSets];
-    int n = 0;
-    {
-        std::lock_guard<std::mutex> lock(g_staging.mutex);
-        if (--g_staging.solvers == 0) {
-            for (; n < g_staging.nidle; ++n) drop[n] = g_staging.idle[n];
-            g_staging.nidle = 0;
-            g_staging.made -= n;
-        }
-    }
-    for (int i = 0; i < n; ++i) free_staging(drop[i]);
-}
-
-StagingSet* take_staging(int device)
-{
-    {
-        std::lock_guard<std::mutex> lock(g_staging.mutex);
-        for (int i = 0; i < g_staging.nidle; ++i)
-            if (g_staging.idle[i]->device == device) {
-                StagingSet* s = g_staging.idle[i];
-                g_staging.idle[i] = g_staging.idle[--g_staging.nidle];
-                return s;
-            }
-        if (g_staging.made >= kMaxSets) return nullptr;
-        ++g_staging.made;
-    }
     StagingSet* s = new (std::nothrow) StagingSet();
-    bool ok = s != nullptr;
-    if (ok) {
-        s->device = device;
-        // (an allocation here is no part of a capture that another thread may have under way)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        void* p = nullptr;
-        ok = hipHostMalloc(&p, kChunkBytes * kChunks, hipHostMallocPortable) == hipSuccess;
-        s->mem = ok ? (char*)p : nullptr;
-        for (int i = 0; i < kChunks && ok; ++i)
-            ok = hipEventCreateWithFlags(&s->landed[i], hipEventDisableTiming) == hipSuccess;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
+    if (!s) return nullptr;
+    s->device = device;
+    OutsideCapture scope;
+    void* p = nullptr;
+    bool ok = hipHostMalloc(&p, kChunkBytes * kChunks, hipHostMallocPortable) == hipSuccess;
+    s->mem = ok ? (char*)p : nullptr;
+    for (int i = 0; i < kChunks && ok; ++i)
+        ok = hipEventCreateWithFlags(&s->landed[i], hipEventDisableTiming) == hipSuccess;
     if (ok) return s;
     (void)hipGetLastError();
-    if (s) free_staging(s);
-    std::lock_guard<std::mutex> lock(g_staging.mutex);
-    --g_staging.made;
-    return nullptr;
-}
-
-void give_staging(StagingSet* s)
-{
-    {
-        std::lock_guard<std::mutex> lock(g_staging.mutex);
-        if (g_staging.solvers > 0) {
-            g_staging.idle[g_staging.nidle++] = s;
-            return;
-        }
-        --g_staging.made;
-    }
     free_staging(s);
-}
-
-// CPUs this process may run on (1 if unknown).
-int usable_cpus()
-{
-    cpu_set_t set;
-    CPU_ZERO(&set);
-    return sched_getaffinity(0, sizeof(set), &set) == 0 ? std::max(1, CPU_COUNT(&set)) : 1;
+    return nullptr;
 }
 
 // Whether dst is host memory that no HIP call knows (pinned memory is fast by itself),
@@ -477,66 +414,31 @@ bool ordinary_memory(const void* dst, int device)
 // the data have arrived when it returns.  hipError_t as int.
 int copy_to_host(void* dst, const void* src, size_t bytes, int device, hipStream_t stream)
 {
-    const int workers = std::min(kCopyThreads, usable_cpus() / 2);
-    StagingSet* set = bytes >= kStagedMin && workers >= 2 && ordinary_memory(dst, device) ? take_staging(device) : nullptr;
-    if (!set) {
-        const int e = (int)hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, stream);
-        return e ? e : (int)hipStreamSynchronize(stream);
-    }
-    // the workers wait by yielding, so they start when the work before the copy is done
-    int e = (int)hipStreamSynchronize(stream);
-    if (e) {
-        give_staging(set);
-        return e;
-    }
-    const int n = (int)((bytes + kChunkBytes - 1) / kChunkBytes);
-    std::atomic<int> ready{0};                  // chunks that have arrived; n + 1: give up
-    std::atomic<int> moved[kChunks];            // per buffer: the last chunk moved out of it, plus 1
-    for (auto& m : moved) m.store(0, std::memory_order_relaxed);
-    auto size_of = [&](int c) { return std::min(kChunkBytes, bytes - (size_t)c * kChunkBytes); };
-    auto work = [&](int w) {
-        for (int c = w; c < n; c += workers) {
-            for (int r; (r = ready.load(std::memory_order_acquire)) <= c;) std::this_thread::yield();
-            if (ready.load(std::memory_order_relaxed) > n) return;
-            std::memcpy((char*)dst + (size_t)c * kChunkBytes, set->mem + (size_t)(c % kChunks) * kChunkBytes, size_of(c));
-            moved[c % kChunks].store(c + 1, std::memory_order_release);
+    const int workers = bytes >= kStagedMin ? std::min(kCopyThreads, usable_cpus() / 2) : 0;
+    StagingSet* set = workers >= 2 && ordinary_memory(dst, device)
+                          ? g_staging.take(device, [&] { return make_staging(device); }, free_staging)
+                          : nullptr;
+    int e = 0;
+    if (set) {
+        // (the threads start when the work before the copy is done)
+        bool started = false;
+        e = (int)hipStreamSynchronize(stream);
+        if (!e) {
+            e = move_chunks(
+                (char*)dst, set->mem, bytes, kChunkBytes, kChunks, workers,
+                [&](long long c, int b, size_t n) {
+                    const int i = (int)hipMemcpyAsync(set->mem + (size_t)b * kChunkBytes, (const char*)src + (size_t)c * kChunkBytes,
+                                                      n, hipMemcpyDeviceToHost, stream);
+                    return i ? i : (int)hipEventRecord(set->landed[b], stream);
+                },
+                [&](int b) { return (int)hipEventSynchronize(set->landed[b]); }, &started);
+            if (e) (void)hipStreamSynchronize(stream);   // nothing may still be landing in the buffers
         }
-    };
-    std::vector<std::thread> threads;
-    bool started = true;
-    try {
-        threads.reserve((size_t)workers);
-        for (int w = 0; w < workers; ++w) threads.emplace_back(work, w);
-    } catch (...) {
-        started = false;
+        g_staging.give(set, free_staging);
+        if (e || started) return e;
     }
-    int issued = 0;
-    for (int landed = 0; started && landed < n && !e;) {
-        while (issued < n && issued - landed < kChunks / 2 && !e) {
-            // the buffer's chunk before this one has been moved on (wait only if nothing is under way)
-            const int b = issued % kChunks;
-            if (issued >= kChunks && moved[b].load(std::memory_order_acquire) != issued - kChunks + 1) {
-                if (issued > landed) break;
-                std::this_thread::yield();
-                continue;
-            }
-            e = (int)hipMemcpyAsync(set->mem + (size_t)b * kChunkBytes, (const char*)src + (size_t)issued * kChunkBytes,
-                                    size_of(issued), hipMemcpyDeviceToHost, stream);
-            if (!e) e = (int)hipEventRecord(set->landed[b], stream);
-            ++issued;
-        }
-        if (!e) e = (int)hipEventSynchronize(set->landed[landed % kChunks]);
-        if (!e) ready.store(++landed, std::memory_order_release);
-    }
-    if (!started || e) ready.store(n + 1, std::memory_order_release);
-    for (std::thread& t : threads) t.join();
-    if (e) (void)hipStreamSynchronize(stream);   // nothing may still be landing in the buffers
-    give_staging(set);
-    if (!started) {
-        e = (int)hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, stream);
-        if (!e) e = (int)hipStreamSynchronize(stream);
-    }
-    return e;
+    e = (int)hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, stream);
+    return e ? e : (int)hipStreamSynchronize(stream);
 }
 
 // `n` ring slots of `per` doubles from the oldest, slot first % ring, on: one copy, or
@@ -585,7 +487,7 @@ void free_solver(teuk_solver* h)
     drop_graph(h);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     if (h->owns && h->base) (void)hipFree(h->base);
-    if (h->counted) staging_solver_gone();
+    if (h->counted) g_staging.user_gone(free_staging);
     delete h;
 }
 
@@ -831,7 +733,7 @@ teuk_status teuk_create(const teuk_config* cfg, const teuk_device_ctx* ctx, teuk
     const double ssp_c = cfg->integrator == TEUK_RK_SSP104 ? 6.0 : 1.0;   // SSP coefficient (Sec. 3.2)
     h->dt = cfg->dt > 0.0 ? cfg->dt : cfg->cfl * ssp_c * h->dt_bound;
     h->counted = true;
-    staging_solver_made();
+    g_staging.user_made();
     *out = h;
     return TEUK_OK;
 }
