@@ -632,16 +632,19 @@ int launch_group_blocked(const StageArgs* args, const unsigned* start, int nmem,
     (void)hipGetLastError();
     const bool hyp = chart == TEUK_CHART_HYPERBOLOIDAL;
     bool done = false;
-#define TEUK_GBLAUNCH(W, F)                                                                                         \
-    if (weight_prec == W) {                                                                                         \
-        if (hyp) hipLaunchKernelGGL((group_blocked_kernel<W, F, true>), grid, block, 0, st, args, start, nmem, r / g, r % g); \
-        else hipLaunchKernelGGL((group_blocked_kernel<W, F, false>), grid, block, 0, st, args, start, nmem, r / g, r % g);    \
+#define TEUK_GBLAUNCH(W, H)                                                                                         \
+    if (weight_prec == W && hyp == H) {                                                                             \
+        hipLaunchKernelGGL((group_blocked_kernel<W, bt_first<W>(), H>), grid, block, 0, st, args, start, nmem, r / g, r % g); \
         done = true;                                                                                                \
     }
-    TEUK_GBLAUNCH(TEUK_W_FP64, bt_first<TEUK_W_FP64>())
-    TEUK_GBLAUNCH(TEUK_W_FP32, bt_first<TEUK_W_FP32>())
-    TEUK_GBLAUNCH(TEUK_W_FP16, bt_first<TEUK_W_FP16>())
-    TEUK_GBLAUNCH(TEUK_W_BF16, bt_first<TEUK_W_BF16>())
+    TEUK_GBLAUNCH(TEUK_W_FP64, false)
+    TEUK_GBLAUNCH(TEUK_W_FP64, true)
+    TEUK_GBLAUNCH(TEUK_W_FP32, false)
+    TEUK_GBLAUNCH(TEUK_W_FP32, true)
+    TEUK_GBLAUNCH(TEUK_W_FP16, false)
+    TEUK_GBLAUNCH(TEUK_W_FP16, true)
+    // (BF16 weights in the tortoise chart: groups step by stage launches)
+    TEUK_GBLAUNCH(TEUK_W_BF16, true)
 #undef TEUK_GBLAUNCH
     if (!done) return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
