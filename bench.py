@@ -49,9 +49,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 BYTES_PER_POINT_STEP = 256.0   # stage launches: 64 + 96 + 96 (fields only; coefficients rebuilt on chip)
 FUSED_BYTES_PER_POINT_STEP = 64.0      # one launch per step: u^n read, u^{n+1} written
 FUSED_H_BYTES_PER_POINT_STEP = 144.0   # hyperboloidal chart: the ten coefficients as well
-# VALU instructions per point-step of the marched blocked kernel, counted in its gfx950
-# ISA (one step of the unrolled march) times 128 lanes per 114 output points
-FUSED_VALU = {"fp64": 815 * 128 / 114, "fp32": 1234 * 128 / 114, "fp16": 1693 * 128 / 114, "bf16": 2592 * 128 / 114}
+# VALU lane-instructions per point-step of the marched blocked kernel, recomputed tile edges
+# included: SQ_INSTS_VALU on 8192 x 256 (BF16: 8192 x 126).  (A count of the code overstates
+# FP32 by a third: lanes seldom take the branch to the FP64 weights.)
+FUSED_VALU = {"fp64": 890, "fp32": 1032, "fp16": 1944, "bf16": 2581}
 KERNEL_SRC = os.path.join(ROOT, "paper_2010_04760_amd", "csrc", "teuk_kernels.hip")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "stage_kernel_c2_traffic.json")
 METRIC = "WENO5 RHS point-updates/s, %HBM peak; mixed vs FP64 speedup at equal error"
